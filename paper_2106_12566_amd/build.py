@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libkrpe.so")
 SOURCES = [os.path.join(HERE, "csrc", "kernels.hip"), os.path.join(HERE, "csrc", "grad_bias.hip"),
-           os.path.join(HERE, "csrc", "long_seq.hip"), os.path.join(HERE, "csrc", "api.hip")]
+           os.path.join(HERE, "csrc", "direct.hip"), os.path.join(HERE, "csrc", "long_seq.hip"), os.path.join(HERE, "csrc", "api.hip")]
 # The convolution kernel at N = 16384, compiled on its own with LLVM's
 # maximum-ILP machine scheduler (measured faster for that length only).
 TOP = os.path.join(HERE, "csrc", "conv_top.hip")

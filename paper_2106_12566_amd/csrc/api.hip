@@ -281,9 +281,29 @@ LongLayout long_layout(int B, int H, int n, int d, int M) {
 
 // Workspace of the forward pass for these sizes (the blocked layout for long
 // sequences on the FFT route, else the one-transform layout).
-size_t fwd_workspace(int B, int H, int n, int d, int M, bool direct) {
-  if (n > (1 << kMaxLog2N) && !direct) return long_layout(B, H, n, d, M).total;
+size_t fwd_workspace(int B, int H, int n, int d, int m, int M, int kind, bool direct) {
+  if (direct) {
+    if (const int ks = direct_ksteps(kind, d, m)) return direct_layout(B, H, n, d, ks).total;
+  } else if (n > (1 << kMaxLog2N)) {
+    return long_layout(B, H, n, d, M).total;
+  }
   return attn_layout(B, H, n, d, M).total;
+}
+
+// The direct route on the fp16 matrix cores (up to 256 features).
+krpe_status_t run_direct(const DirectLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
+                         const float* b, const float* W, float* z, int BHi, int H, int n, int d, int m, int kind,
+                         bool nprf, hipStream_t st, void* const* events) {
+  for (int e = 0; e < 2; ++e)
+    if (krpe_status_t s = record(events, e, st)) return s;
+  if (krpe_status_t s = hip_check(launch_direct_prep(L, w, q, k, v, bf16, b, W, BHi, H, n, d, m, nprf, kind, st),
+                                  "operand launch"))
+    return s;
+  for (int e = 2; e < 4; ++e)
+    if (krpe_status_t s = record(events, e, st)) return s;
+  if (krpe_status_t s = hip_check(launch_direct(L, w, v, bf16, z, nullptr, BHi, H, n, d, st), "direct launch"))
+    return s;
+  return record(events, 4, st);
 }
 
 ConvLayout conv_layout(int B, int H, int C, int n) {
@@ -730,7 +750,13 @@ size_t krpe_attention_fwd_workspace_ex(int B, int H, int n, int d, int m, unsign
   if (B < 0 || H < 0 || n < 1 || n > (1 << kMaxLongLog2N) || d < 1 || d > kMaxD || m < 1 || m > kMaxM) return 0;
   int kind = kFeatPrf, M = m;
   if (feature_kind(flags, d, m, &kind, &M) != KRPE_OK) return 0;
-  return fwd_workspace(B, H, n, d, M, use_direct(flags, static_cast<long long>(B) * H, n, M, d));
+  // Up to one transform the size serves either route, so that a workspace
+  // stays valid when the route bits or the causal hint of a call differ.
+  const bool direct = use_direct(flags, static_cast<long long>(B) * H, n, M, d);
+  const size_t need = fwd_workspace(B, H, n, d, m, M, kind, direct);
+  if (n > (1 << kMaxLog2N)) return need;
+  const size_t other = fwd_workspace(B, H, n, d, m, M, kind, !direct);
+  return need > other ? need : other;
 }
 
 size_t krpe_attention_fwd_workspace(int B, int H, int n, int d, int m) {
@@ -754,7 +780,7 @@ krpe_status_t krpe_attention_fwd_profiled(const void* q, const void* k, const vo
       misaligned(z) || misaligned(ws))
     return fail(KRPE_ERR_ALIGN, "all pointers must be 16-byte aligned");
   const bool direct = use_direct(flags, static_cast<long long>(B) * H, n, M, d);
-  const size_t need = fwd_workspace(B, H, n, d, M, direct);
+  const size_t need = fwd_workspace(B, H, n, d, m, M, kind, direct);
   if (!ws || ws_bytes < need) return fail(KRPE_ERR_WORKSPACE, "workspace needs " + std::to_string(need) + " bytes");
   const size_t qkv_bytes = bh * n * d * dtype_size(qkv_dtype);
   const Range ins[] = {{q, qkv_bytes},
@@ -768,6 +794,10 @@ krpe_status_t krpe_attention_fwd_profiled(const void* q, const void* k, const vo
   for (const Range& r : ins)
     if (overlaps(rz, r) || overlaps(rws, r)) return fail(KRPE_ERR_ALIAS, "z or the workspace overlaps an input");
 
+  if (const int ks = direct ? direct_ksteps(kind, d, m) : 0)
+    return run_direct(direct_layout(B, H, n, d, ks), static_cast<char*>(ws), q, k, v, qkv_dtype == KRPE_BF16, b, W, z,
+                      static_cast<int>(bh), H, n, d, m, kind, (flags & KRPE_NPRF) != 0,
+                      static_cast<hipStream_t>(stream), events);
   if (n > (1 << kMaxLog2N) && !direct)
     return run_forward_long(long_layout(B, H, n, d, M), static_cast<char*>(ws), q, k, v, qkv_dtype == KRPE_BF16, b,
                             W, z, static_cast<int>(bh), H, n, d, m, M, kind, (flags & KRPE_NPRF) != 0,

@@ -1,0 +1,883 @@
+// The direct route: Eq. (10) evaluated as (phi(Q) phi(K)^T o C) [v, 1] on the
+// fp16 matrix cores at fp32 accuracy (wprod.hpp), two launches (three where
+// the keys of a row tile are split over work-groups):
+//
+//  k_prep          phi(q), phi(k) and v as fragments, the table of c = exp(b).
+//  k_direct        the two products of 128 rows over their keys.
+//  k_direct_parts  sums the parts of a split row tile.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <cstdint>
+#include <type_traits>
+
+#include "common.hpp"
+#include "launch.hpp"
+#include "wprod.hpp"
+
+namespace krpe {
+
+// ----------------------------------------------------------------- prep --
+// One launch, three kinds of work-group (by block index):
+//  phi  128 positions of one (source, batch-head): the projections s = W x on
+//       the bf16 matrix cores (operands in three bf16 terms, split in
+//       registers and LDS; six products, three for bf16 x), the feature map
+//       of Sec. 2 on the accumulators, and the result, scaled by the power of
+//       two of the position's largest feature, as S fragments, whose lane
+//       order is the accumulators'.  Features of the trigonometric map: sines
+//       in k steps [0, KS / 2), cosines in the rest (the contraction does not
+//       see their order; unused slots are zero, as are positions >= n).
+//  v    128 positions of one batch-head as Z fragments.  An element that is
+//       not finite is stored as zero and its block flagged: k_direct adds
+//       its contribution separately (a split of it would give inf - inf).
+//  c    2048 entries of one head's table and the range of its finite ones.
+// The features are written once and read once per 128 rows; at 96 heads, n =
+// 4096, m = 128 the kernel is bound by its 0.5 GB of stores.
+struct PrepArgs {
+  const void *q, *k, *v;
+  const float *W, *b;
+  uint4 *X, *Y, *Z;
+  float* krec;      // [BH][nblk][64] (KeyRec)
+  unsigned* vflag;  // [BH][nblk]
+  float* ctab;      // [H][ctab_stride]
+  int2* crange;     // [H][ctab_chunks]
+  unsigned* fix;    // fix[BH] = rows evaluated exactly (all of them)
+  int* rexp;        // [BH][32 nblk] powers of phi(q) (NULL: not wanted)
+  int BH, H, n, nblk, d, m, KS, ct_total, kind, nprf, tiles, phi_blocks, v_blocks;
+  float inv_sqrt_m;
+  float log2_m_hi, log2_m_lo;  // -log2(sqrt(m)) in two floats
+};
+// Record of a 32-key block, 64 words: [0, 32) 2^(e_j - E) per key, e_j the
+// power of phi(k_j) and E = word 32 (int); word 33 (int) the power of its
+// values.
+constexpr int kRecWords = 64, kRecE = 32, kRecV = 33;
+// S of two positions is at most 2^30 M in units of their powers: E carries 30
+// of them, so that P stays near c_{j-i}'s range.
+constexpr int kRecBias = 30;
+
+// 8 values of a row from position p (zeros past `count` values of the row)
+template <typename T>
+__device__ __forceinline__ void load8(const T* __restrict__ p, int count, bool vec, float (&x)[8]) {
+  if (vec && count >= 8) {
+    if constexpr (std::is_same<T, float>::value) {
+      const float4 a = reinterpret_cast<const float4*>(p)[0], c = reinterpret_cast<const float4*>(p)[1];
+      x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w, x[4] = c.x, x[5] = c.y, x[6] = c.z, x[7] = c.w;
+    } else {
+      const uint4 u = *reinterpret_cast<const uint4*>(p);
+      const unsigned w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        x[2 * j] = __uint_as_float(w[j] << 16);
+        x[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = j < count ? to_f32(p[j]) : 0.f;
+  }
+}
+
+constexpr float kLn2 = 0.69314718055994531f;
+
+// 2^((s + sl) (r + rl) + (c + cl)) with the exponent in two floats (its rounding
+// at a size of about 10 is the largest error of phi otherwise): t + tl, then
+// 2^rint(t) 2^(t - rint(t)) (1 + tl ln 2).  Zero below 2^-400, infinite
+// arguments included.
+__device__ __forceinline__ float exp2_two(float s, float sl, float r, float rl, float c, float cl) {
+#pragma clang fp contract(off)
+  const float sum = s + sl, sb = sum - s;
+  sl = (s - (sum - sb)) + (sl - sb);
+  s = sum;
+  const float p = s * r, pl = fmaf(s, rl, fmaf(sl, r, fmaf(s, r, -p)));
+  const float t = p + c, b = t - p, tl = (((p - (t - b)) + (c - b)) + pl) + cl;
+  const float ti = rintf(t), y = __builtin_amdgcn_exp2f(t - ti);
+  const float f = ldexpf(fmaf(y, tl * kLn2, y), static_cast<int>(fminf(fmaxf(ti, -300.f), 300.f)));
+  return t < -400.f ? 0.f : f;
+}
+
+// DK: k steps of the head dimension, d <= 16 DK.  NT: 32-feature tiles of
+// projections held in registers until the position's largest feature is known.
+template <typename TX, int DK, int NT>
+__device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __restrict__ smem) {
+  constexpr int XS = 16 * DK + 4;  // floats per staged row (16 lanes' 16-byte reads fall in distinct banks)
+  constexpr int NSX = sizeof(TX) == 2 ? 1 : 3;
+  constexpr int GT = DK <= 4 ? 4 : 2;  // tiles of W staged at a time
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lh = lane >> 5;
+  const int pt = bid % a.tiles, rest = bid / a.tiles, bh = rest % a.BH, src = rest / a.BH;
+  const int h = bh % a.H, n = a.n, d = a.d;
+  const TX* __restrict__ x = static_cast<const TX*>(src == 0 ? a.q : a.k) + static_cast<size_t>(bh) * n * d;
+  const int p0 = pt * 128, rows = min(128, n - p0);
+  // x rows to LDS (zeros past n and past d); rows of 8-element multiples are
+  // 16-byte aligned (the base is)
+  const bool vec = d % 8 == 0;
+  for (int e = tid; e < 128 * 2 * DK; e += 256) {
+    const int r = e / (2 * DK), c8 = 8 * (e % (2 * DK));
+    float v8[8];
+    load8(x + static_cast<size_t>(p0 + min(r, rows - 1)) * d + c8, r < rows ? d - c8 : 0, vec, v8);
+    *reinterpret_cast<float4*>(smem + r * XS + c8) = make_float4(v8[0], v8[1], v8[2], v8[3]);
+    *reinterpret_cast<float4*>(smem + r * XS + c8 + 4) = make_float4(v8[4], v8[5], v8[6], v8[7]);
+  }
+  __syncthreads();
+  // this lane's position: dimensions 16 ks + 8 lh + t as B operands; its
+  // squared norm in fp64 (it is the same for every feature: an error of it
+  // weighs on the whole position)
+  uint4 xf[DK][NSX];
+  double sqd = 0.0;
+  const float* __restrict__ row = smem + (32 * wave + lr) * XS;
+#pragma unroll
+  for (int ks = 0; ks < DK; ++ks) {
+    const float4 u = *reinterpret_cast<const float4*>(row + 16 * ks + 8 * lh);
+    const float4 w = *reinterpret_cast<const float4*>(row + 16 * ks + 8 * lh + 4);
+    const float v8[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int t = 0; t < 8; ++t) sqd = fma(static_cast<double>(v8[t]), static_cast<double>(v8[t]), sqd);
+    uint4 t3[3];
+    split_bf16x8(v8, t3);
+#pragma unroll
+    for (int s = 0; s < NSX; ++s) xf[ks][s] = t3[s];
+  }
+  sqd += __shfl_xor(sqd, 32);  // ||x||^2
+  // phi of x / ||x|| when normalising (Algorithm 1, first step): the
+  // projections scale by 1 / ||x|| and ||x||^2 / 2 becomes 1/2 (a zero row
+  // stays zero).
+  const bool nz = sqd > 0.0;
+  const double half_sq = a.nprf ? (nz ? 0.5 : 0.0) : 0.5 * sqd;
+  const float row_scale = a.nprf ? (nz ? static_cast<float>(1.0 / sqrt(sqd)) : 0.f) : 1.f;
+  // PRF: phi = 2^(s rs + e0), rs and e0 in two floats each
+  const double rsd = (a.nprf ? (nz ? 1.0 / sqrt(sqd) : 0.0) : 1.0) * 1.4426950408889634;
+  const double e0d = -half_sq * 1.4426950408889634 + (static_cast<double>(a.log2_m_hi) + static_cast<double>(a.log2_m_lo));
+  const float rs = static_cast<float>(rsd), rs_lo = static_cast<float>(rsd - static_cast<double>(rs));
+  const float e0 = static_cast<float>(e0d), e0_lo = static_cast<float>(e0d - static_cast<double>(e0));
+  const bool pos_ok = p0 + 32 * wave + lr < n;
+  const int blk = 4 * pt + wave;
+  const bool store = blk < a.nblk;  // uniform
+  const size_t block = static_cast<size_t>(bh) * a.nblk + min(blk, a.nblk - 1);
+  uint4* __restrict__ ob = (src == 0 ? a.X : a.Y) + block * a.KS * 2 * kFragLanes + lane;
+  const int ksp = a.kind == kFeatTrf ? a.KS / 2 : a.KS;  // k steps of projections (of x for elu + 1)
+  const int ftiles = (ksp + 1) / 2;
+  const float* __restrict__ Wh = a.W + static_cast<size_t>(h) * a.m * d;
+  uint4* __restrict__ wf = reinterpret_cast<uint4*>(smem);  // [tile][ks][term][64]
+  // rows 32 t0 .. of W (up to GT tiles) split into LDS
+  auto stage_w = [&](int t0) {
+    __syncthreads();  // x rows / the previous features consumed
+    const int gt = min(GT, ftiles - t0);
+    for (int e = tid; e < gt * 32 * 2 * DK; e += 256) {
+      const int fl = e / (2 * DK), c = e % (2 * DK), f = 32 * t0 + fl;
+      float v8[8];
+      load8(Wh + static_cast<size_t>(min(f, a.m - 1)) * d + 8 * c, f < a.m ? d - 8 * c : 0, d % 4 == 0, v8);
+      uint4 t3[3];
+      split_bf16x8(v8, t3);
+      uint4* __restrict__ o = wf + ((fl >> 5) * DK + (c >> 1)) * 3 * kFragLanes + (c & 1) * 32 + (fl & 31);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) o[s * kFragLanes] = t3[s];
+    }
+    __syncthreads();
+  };
+  // projections of staged tile tt: the products of the largest terms, and the
+  // small ones, apart
+  auto project = [&](int tt, floatx16& acc, floatx16& lo) {
+    acc = zero16();
+    lo = zero16();
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) {
+      uint4 w3[3];
+#pragma unroll
+      for (int s = 0; s < 3; ++s) w3[s] = wf[((tt * DK + ks) * 3 + s) * kFragLanes + lane];
+#pragma unroll
+      for (int s = 2; s >= 1; --s)
+#pragma unroll
+        for (int i = 0; i <= s; ++i)
+          if (s - i < NSX) lo = mfma_bf16(w3[i], xf[ks][s - i], lo);
+      acc = mfma_bf16(w3[0], xf[ks][0], acc);
+    }
+  };
+  auto emit = [&](int ks, const float (&v8)[8]) {
+    uint4 hh, ll;
+    split_f16x8(v8, kLoScale, hh, ll);
+    ob[(ks * 2 + 0) * kFragLanes] = hh;
+    ob[(ks * 2 + 1) * kFragLanes] = ll;
+  };
+  int ex;  // the position's power: its largest feature is brought to [2^14, 2^15)
+  bool any_phi;
+  if (a.kind == kFeatTrf) {
+    // every feature is at most the amplitude: no need to see them first
+    const float amp = pos_ok ? static_cast<float>(exp(half_sq)) * a.inv_sqrt_m : 0.f;
+    ex = __builtin_amdgcn_frexp_expf(amp) - 15;
+    const float as = ldexpf(amp, -ex);
+    any_phi = amp > 0.f;
+    for (int t0 = 0; t0 < ftiles; t0 += GT) {
+      stage_w(t0);
+      for (int tt = 0; tt < min(GT, ftiles - t0) && store; ++tt) {
+        floatx16 acc, lo;
+        project(tt, acc, lo);
+        float s16[16], c16[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const bool in = 32 * (t0 + tt) + 8 * (e >> 2) + 4 * lh + (e & 3) < a.m;
+          sincosf((acc[e] + lo[e]) * row_scale, &s16[e], &c16[e]);
+          s16[e] = in ? s16[e] * as : 0.f;
+          c16[e] = in ? c16[e] * as : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int ks = 2 * (t0 + tt) + j;
+          if (ks >= ksp) continue;  // uniform
+          float v8[8];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) v8[t] = s16[8 * j + t];
+          emit(ks, v8);
+#pragma unroll
+          for (int t = 0; t < 8; ++t) v8[t] = c16[8 * j + t];
+          emit(ksp + ks, v8);
+        }
+      }
+    }
+  } else {
+    float val[NT][16];
+    if (a.kind == kFeatElu) {
+      constexpr_for<NT>([&](auto tc) {
+        constexpr int t0 = decltype(tc)::value;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          // x_f + 1 for x_f > 0, exp(x_f) otherwise
+          const int f = 32 * t0 + 8 * (e >> 2) + 4 * lh + (e & 3);
+          const float y = f < d ? row[f] * row_scale : 0.f;
+          val[t0][e] = f < d && pos_ok ? (y > 0.f ? y + 1.f : expf(y)) : 0.f;
+        }
+      });
+    } else {
+      constexpr_for<NT>([&](auto tc) {
+        constexpr int ti = decltype(tc)::value, t0 = ti / GT * GT;
+        if (ti >= ftiles) return;  // uniform
+        if constexpr (ti == t0) stage_w(t0);
+        floatx16 acc, lo;
+        project(ti - t0, acc, lo);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          val[ti][e] = pos_ok ? exp2_two(acc[e], lo[e], rs, rs_lo, e0, e0_lo) : 0.f;
+        }
+        if (32 * ti + 32 > a.m) {  // uniform: unused slots are zero
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (32 * ti + 8 * (e >> 2) + 4 * lh + (e & 3) >= a.m) val[ti][e] = 0.f;
+        }
+      });
+    }
+    float mx = 0.f;
+    constexpr_for<NT>([&](auto tc) {
+      constexpr int ti = decltype(tc)::value;
+      if (ti < ftiles) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, val[ti][e]);
+      }
+    });
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    ex = __builtin_amdgcn_frexp_expf(mx) - 15;  // (-15 for zero, infinite and NaN maxima)
+    any_phi = mx > 0.f;
+    constexpr_for<2 * NT>([&](auto kc) {
+      constexpr int ks = decltype(kc)::value;
+      if (ks >= ksp || !store) return;  // uniform
+      float v8[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v8[t] = ldexpf(val[ks / 2][8 * (ks % 2) + t], -ex);
+      emit(ks, v8);
+    });
+  }
+  if (!store) return;
+  if (src == 0) {
+    if (a.rexp && lh == 0) a.rexp[block * kBlk + lr] = ex;
+  } else {
+    // (positions without features have no power of their own)
+    int E = any_phi ? ex : -400;
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) E = max(E, __shfl_xor(E, off));
+    float* __restrict__ rec = a.krec + block * kRecWords;
+    if (lh == 0) rec[lr] = any_phi ? ldexpf(1.f, ex - E - kRecBias) : 0.f;
+    if (lane == 0) rec[kRecE] = __int_as_float(E + kRecBias);
+  }
+}
+
+template <typename TX>
+__device__ __forceinline__ void prep_v(const PrepArgs& a, int bid) {
+  // (bf16 values: 8 significant bits, one fp16 term holds them)
+  constexpr int NSZ = sizeof(TX) == 2 ? 1 : 2;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 31, lh = lane >> 5, n = a.n, d = a.d;
+  const int pt = bid % a.tiles, bh = bid / a.tiles, blk = 4 * pt + wave;
+  if (blk >= a.nblk) return;  // uniform per wave; no barrier in this role
+  const TX* __restrict__ v = static_cast<const TX*>(a.v) + static_cast<size_t>(bh) * n * d;
+  const size_t block = static_cast<size_t>(bh) * a.nblk + blk;
+  uint4* __restrict__ out = a.Z + block * a.ct_total * 2 * NSZ * kFragLanes + lane;
+  bool odd = false;
+  float x[kMaxD / 32][16];
+  float mx = 0.f;
+#pragma unroll
+  for (int ct = 0; ct < kMaxD / 32; ++ct) {
+    if (ct >= a.ct_total) continue;  // uniform
+    const int col = 32 * ct + lr;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int pos = 32 * blk + 8 * (e >> 2) + 4 * lh + (e & 3);
+      x[ct][e] = pos < n && col < d ? to_f32(v[static_cast<size_t>(pos) * d + col]) : 0.f;
+    }
+  }
+#pragma unroll
+  for (int ct = 0; ct < kMaxD / 32; ++ct) {
+    if (ct >= a.ct_total) continue;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      if (!isfinite(x[ct][e])) {
+        x[ct][e] = 0.f;
+        odd = true;
+      }
+      mx = fmaxf(mx, fabsf(x[ct][e]));
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  const int ex = __builtin_amdgcn_frexp_expf(mx) - 15;
+#pragma unroll
+  for (int ct = 0; ct < kMaxD / 32; ++ct) {
+    if (ct >= a.ct_total) continue;
+#pragma unroll
+    for (int k2 = 0; k2 < 2; ++k2) {
+      float v8[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v8[t] = ldexpf(x[ct][8 * k2 + t], -ex);
+      uint4 hh, ll;
+      split_f16x8(v8, kLoScale, hh, ll);
+      out[((ct * 2 + k2) * NSZ + 0) * kFragLanes] = hh;
+      if (NSZ > 1) out[((ct * 2 + k2) * NSZ + NSZ - 1) * kFragLanes] = ll;
+    }
+  }
+  const bool any = __any(odd);
+  if (lane == 0) {
+    a.vflag[block] = any ? 1u : 0u;
+    a.krec[block * kRecWords + kRecV] = __int_as_float(ex);
+  }
+}
+
+__device__ __forceinline__ void prep_c(const PrepArgs& a, int bid) {
+  __shared__ int2 wr[4];
+  const int chunks = ctab_chunks(a.n), stride = ctab_stride(a.n), len = 2 * a.n - 1;
+  const int h = bid / chunks, ch = bid % chunks;
+  const float* __restrict__ bh = a.b + static_cast<size_t>(h) * len;
+  float* __restrict__ ct = a.ctab + static_cast<size_t>(h) * stride;
+  int lo = 1 << 30, hi = -1;
+  float v[kCChunk / 256];
+#pragma unroll
+  for (int j = 0; j < kCChunk / 256; ++j) {
+    const int s = ch * kCChunk + 256 * j + static_cast<int>(threadIdx.x) - kCPad;
+    v[j] = s >= 0 && s < len ? bh[s] : -INFINITY;
+  }
+#pragma unroll
+  for (int j = 0; j < kCChunk / 256; ++j) {
+    const int e = ch * kCChunk + 256 * j + static_cast<int>(threadIdx.x), s = e - kCPad;
+    if (e < stride) ct[e] = s >= 0 && s < len ? expf(v[j]) : 0.f;
+    if (s >= 0 && s < len && v[j] != -INFINITY) {
+      lo = min(lo, s);
+      hi = max(hi, s);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = min(lo, __shfl_xor(lo, off));
+    hi = max(hi, __shfl_xor(hi, off));
+  }
+  if ((threadIdx.x & 63) == 0) wr[threadIdx.x >> 6] = make_int2(lo, hi);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    a.crange[static_cast<size_t>(h) * chunks + ch] =
+        make_int2(min(min(wr[0].x, wr[1].x), min(wr[2].x, wr[3].x)), max(max(wr[0].y, wr[1].y), max(wr[2].y, wr[3].y)));
+    if (bid == 0) a.fix[a.BH] = static_cast<unsigned>(a.BH) * static_cast<unsigned>(a.n);
+  }
+}
+
+template <typename TX, int DK, int NT>
+__global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
+  constexpr int kX = 128 * (16 * DK + 4), kW = (DK <= 4 ? 4 : 2) * DK * 3 * 256;
+  __shared__ __align__(16) float smem[kX > kW ? kX : kW];
+  const int bid = blockIdx.x;
+  if (bid < a.phi_blocks) {
+    prep_phi<TX, DK, NT>(a, bid, smem);
+  } else if (bid < a.phi_blocks + a.v_blocks) {
+    prep_v<TX>(a, bid - a.phi_blocks);
+  } else {
+    prep_c(a, bid - a.phi_blocks - a.v_blocks);
+  }
+}
+
+// --------------------------------------------------------------- direct --
+// One work-group: 32 NW consecutive rows of one (batch, head), each wave its
+// own 32, over the 32-key blocks of its part of the rows' finite-b range.  A
+// block's fragments of phi(k) and v, its strip of c and its record are staged
+// to LDS one block ahead by direct loads and shared by the waves; phi(q) stays
+// in registers.  Per block and wave: S^T = phi(k) phi(q)^T (lane: row lr, keys
+// along the registers), P = S^T 2^(e_j - E) c_{j-i}, P split with the power of
+// its row's largest entry, and Z^T = [v]^T P^T (lane: row lr again, so that
+// the row's power applies lane by lane), whose fp32 sums over the 32 keys are
+// added into fp64 totals; the denominator is the fp32 sum of P added likewise.
+// The power of phi(q_i) cancels in z.  P's small term is stored unscaled (its
+// largest entry is at 2^14, terms below 2^-40 of that are lost).  A wave skips
+// the blocks outside its own rows' range (it still stages and meets the
+// barriers).
+struct DirectArgs {
+  const uint4 *X, *Y, *Z;
+  const float* krec;
+  const unsigned* vflag;
+  const float* ctab;
+  const int2* crange;
+  const void* v;
+  float *z, *den;
+  const int* rexp;
+  double* part;
+  int BH, H, n, nblk, d, ct_total, tiles, passes, nparts, remap;
+};
+
+template <typename TV, int KS, int CT, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void k_direct(DirectArgs a) {
+  constexpr int NSZ = sizeof(TV) == 2 ? 1 : 2;
+  constexpr int kRows = 32 * NW;
+  constexpr int NY = KS * 2, NF = NY + CT * 2 * NSZ;  // fragments per key block
+  constexpr int NC = (kRows + 31 + 63) / 64;          // 64-entry pieces of the c strip (kRows + 31 entries used)
+  __shared__ uint4 tiles_lds[2][NF * kFragLanes];
+  __shared__ __align__(16) float strip[2][NC * 64 + kRecWords];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lh = lane >> 5;
+  int b = a.remap ? xcd_block(blockIdx.x, gridDim.x) : static_cast<int>(blockIdx.x);
+  const int pi = b % a.nparts;
+  b /= a.nparts;
+  const int tile = a.tiles - 1 - b % a.tiles;  // (under a causal mask the last rows see the most keys)
+  b /= a.tiles;
+  const int pass = b % a.passes, bh = b / a.passes, h = bh % a.H;
+  const int n = a.n, row0 = tile * kRows, wrow0 = row0 + 32 * wave;
+  const int2 br = head_range(a.crange + static_cast<size_t>(h) * ctab_chunks(n), ctab_chunks(n), lane);
+  // key blocks [lo, hi) of rows r0 .. r1
+  auto key_blocks = [&](int r0, int r1, int& lo, int& hi) {
+    const int jlo = max(0, r0 + br.x - (n - 1)), jhi = min(n - 1, r1 + br.y - (n - 1));
+    lo = jhi >= jlo ? jlo >> 5 : 0;
+    hi = jhi >= jlo ? (jhi >> 5) + 1 : 0;
+  };
+  int b0, b1, wlo = 0, whi = 0;
+  key_blocks(row0, min(row0 + kRows, n) - 1, b0, b1);
+  if (wrow0 < n) key_blocks(wrow0, min(wrow0 + 32, n) - 1, wlo, whi);
+  {
+    const int nb = b1 - b0, s = b0;
+    b0 = s + static_cast<int>(static_cast<long long>(nb) * pi / a.nparts);
+    b1 = s + static_cast<int>(static_cast<long long>(nb) * (pi + 1) / a.nparts);
+  }
+  // phi(q) of this wave's rows
+  const size_t xblk = static_cast<size_t>(bh) * a.nblk + min(wrow0 >> 5, a.nblk - 1);
+  uint4 x[KS][2];
+  {
+    const uint4* __restrict__ xp = a.X + xblk * NY * kFragLanes + lane;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) x[ks][s] = xp[(ks * 2 + s) * kFragLanes];
+  }
+  const uint32_t zbytes = static_cast<uint32_t>(a.ct_total) * 2 * NSZ * 1024u;  // per key block
+  const int stride = ctab_stride(n);
+  const size_t hb = static_cast<size_t>(bh) * a.nblk;
+  const __amdgpu_buffer_rsrc_t ry = buffer_of(a.Y + hb * NY * kFragLanes, static_cast<size_t>(a.nblk) * NY * 1024);
+  const __amdgpu_buffer_rsrc_t rz =
+      buffer_of(reinterpret_cast<const char*>(a.Z) + hb * zbytes, static_cast<size_t>(a.nblk) * zbytes);
+  const __amdgpu_buffer_rsrc_t rc = buffer_of(a.ctab + static_cast<size_t>(h) * stride, static_cast<size_t>(stride) * 4);
+  const __amdgpu_buffer_rsrc_t rr = buffer_of(a.krec + hb * kRecWords, static_cast<size_t>(a.nblk) * kRecWords * 4);
+  const uint32_t lds0 = lds_address(&tiles_lds[0][0]), str0 = lds_address(&strip[0][0]);
+  const uint32_t zpass = static_cast<uint32_t>(pass * CT * 2 * NSZ) * 1024u;
+  // pieces of block blk into buffer `buf`: wave w stages pieces w, w + NW, ..:
+  // the fragments, the c entries from key 32 blk and row row0 + kRows - 1 on,
+  // the record
+  auto stage = [&](int blk, int buf) {
+    const uint32_t base = lds0 + static_cast<uint32_t>(buf) * (NF * 1024u), v16 = lane * 16u;
+    const uint32_t sb = str0 + static_cast<uint32_t>(buf) * (NC * 64 + kRecWords) * 4u;
+    const uint32_t yo = static_cast<uint32_t>(blk) * (NY * 1024u), zo = static_cast<uint32_t>(blk) * zbytes + zpass;
+    const uint32_t co = static_cast<uint32_t>(32 * blk - row0 - (kRows - 1) + n - 1 + kCPad) * 4u;
+#pragma unroll
+    for (int i = 0; i < (NF + NC + 1 + NW - 1) / NW; ++i) {
+      const int f = NW * i + wave;
+      if (f < NY)
+        stage_lds<16>(ry, base + f * 1024u, v16, yo + f * 1024u);
+      else if (f < NF)
+        stage_lds<16>(rz, base + f * 1024u, v16, zo + (f - NY) * 1024u);
+      else if (f < NF + NC)
+        stage_lds<4>(rc, sb + (f - NF) * 256u, lane * 4u, co + (f - NF) * 256u);
+      else if (f == NF + NC)
+        stage_lds<4>(rr, sb + NC * 256u, lane * 4u, static_cast<uint32_t>(blk) * (kRecWords * 4u));
+    }
+  };
+  double zt[CT][16];
+  double dsum = 0.0;
+#pragma unroll
+  for (int t = 0; t < CT; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) zt[t][e] = 0.0;
+  if (b0 < b1) stage(b0, 0);
+  for (int blk = b0; blk < b1; ++blk) {
+    const int buf = (blk - b0) & 1;
+    // this block's pieces are in LDS, the other buffer is consumed
+    stage_wait();
+    __syncthreads();
+    if (blk + 1 < b1) stage(blk + 1, buf ^ 1);
+    if (blk < wlo || blk >= whi) continue;
+    const uint4* __restrict__ y = &tiles_lds[buf][lane];
+    const uint4* __restrict__ zf = y + NY * kFragLanes;
+    const float* __restrict__ rec = &strip[buf][NC * 64];
+    const float* __restrict__ cs = &strip[buf][kRows - 1 - 32 * wave - lr + 4 * lh];
+    floatx16 s = zero16(), s1 = zero16();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const uint4 yh = y[(ks * 2 + 0) * kFragLanes], yl = y[(ks * 2 + 1) * kFragLanes];
+      s = mfma_f16(yh, x[ks][0], s);
+      s1 = mfma_f16(yh, x[ks][1], s1);
+      s1 = mfma_f16(yl, x[ks][0], s1);
+    }
+    // P: lane row lr, keys 8 (e / 4) + 4 lh + e % 4
+    float p[16];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 kr = *reinterpret_cast<const float4*>(rec + 8 * g + 4 * lh);
+      const float k4[4] = {kr.x, kr.y, kr.z, kr.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        p[4 * g + j] = fmaf(s1[4 * g + j], kLoInv, s[4 * g + j]) * k4[j] * cs[8 * g + j];
+    }
+    if (32 * blk + 32 > n) {  // uniform: keys past n (phi(k) = 0 there, but c may be infinite)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (32 * blk + 8 * (e >> 2) + 4 * lh + (e & 3) >= n) p[e] = 0.f;
+    }
+    float ds = 0.f, mx = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      ds += p[e];
+      mx = fmaxf(mx, fabsf(p[e]));
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    // the row's power in this block: its largest P is brought to [2^14, 2^15)
+    // (zero and NaN maxima: 2^15, any power serves)
+    const int ex = max(__builtin_amdgcn_frexp_expf(mx), -100) - 15;
+    const float sc = __int_as_float((127 - ex) << 23);
+    const int kexp = __float_as_int(rec[kRecE]);
+    const double zs = exp2_int(kexp + __float_as_int(rec[kRecV]) + ex);
+    dsum = fma(static_cast<double>(ds), exp2_int(kexp), dsum);
+    uint4 ph[2], pl[2];
+#pragma unroll
+    for (int k2 = 0; k2 < 2; ++k2) {
+      float v8[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v8[t] = p[8 * k2 + t] * sc;
+      split_f16x8(v8, 1.f, ph[k2], pl[k2]);
+    }
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+      floatx16 zc = zero16(), z1 = zero16();
+#pragma unroll
+      for (int k2 = 0; k2 < 2; ++k2) {
+        const uint4 vh = zf[((t * 2 + k2) * NSZ + 0) * kFragLanes];
+        zc = mfma_f16(vh, pl[k2], zc);
+        zc = mfma_f16(vh, ph[k2], zc);
+        if constexpr (NSZ > 1) z1 = mfma_f16(zf[((t * 2 + k2) * NSZ + 1) * kFragLanes], ph[k2], z1);
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float zz = NSZ > 1 ? fmaf(z1[e], kLoInv, zc[e]) : zc[e];
+        zt[t][e] = fma(static_cast<double>(zz), zs, zt[t][e]);
+      }
+    }
+  }
+  if (wrow0 >= n) return;  // uniform per wave; no barrier follows
+  dsum += __shfl_xor(dsum, 32);  // the other half-wave's keys of row lr
+  const int i = wrow0 + lr;
+  // this lane: row i, columns 32 (pass CT + t) + 8 (e / 4) + 4 lh + e % 4
+  constexpr int cw = CT * 32 + 1;
+  const int c0 = pass * CT * 32 + 4 * lh;
+  double* __restrict__ part = a.part + ((static_cast<size_t>(bh * a.passes + pass) * a.tiles + tile) * a.nparts + pi) *
+                                           (kRows * cw) + 32 * wave + lr;  // [column][row]
+  float* __restrict__ zr = a.z + (static_cast<size_t>(bh) * n + i) * a.d;
+  if (a.nparts == 1) {
+    const double inv = 1.0 / dsum;
+    if (i < n) {
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int c = c0 + 32 * t + 8 * g;
+          float4 o;
+          o.x = static_cast<float>(zt[t][4 * g] * inv);
+          o.y = static_cast<float>(zt[t][4 * g + 1] * inv);
+          o.z = static_cast<float>(zt[t][4 * g + 2] * inv);
+          o.w = static_cast<float>(zt[t][4 * g + 3] * inv);
+          if (a.d % 4 == 0) {  // rows 16-byte aligned
+            if (c < a.d) *reinterpret_cast<float4*>(zr + c) = o;
+          } else {
+            if (c < a.d) zr[c] = o.x;
+            if (c + 1 < a.d) zr[c + 1] = o.y;
+            if (c + 2 < a.d) zr[c + 2] = o.z;
+            if (c + 3 < a.d) zr[c + 3] = o.w;
+          }
+        }
+      if (pass == 0 && lh == 0 && a.den)
+        a.den[static_cast<size_t>(bh) * n + i] = static_cast<float>(dsum * exp2_int(a.rexp[xblk * kBlk + lr]));
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part[(32 * t + 8 * (e >> 2) + 4 * lh + (e & 3)) * kRows] = zt[t][e];
+    if (lh == 0) part[CT * 32 * kRows] = dsum;
+  }
+  // Values that are not finite (stored as zero fragments, their blocks
+  // flagged): P v added in fp64, one key at a time; rare.
+  const unsigned* __restrict__ vf = a.vflag + hb;
+  const int f0 = max(b0, wlo), f1 = min(b1, whi);
+  bool odd = false;
+  for (int blk = f0 + lane; blk < f1; blk += 64) odd |= vf[blk] != 0u;
+  if (!__any(odd)) return;
+  __threadfence();  // the rows stored above are read back below, by other lanes
+  const TV* __restrict__ v = static_cast<const TV*>(a.v) + static_cast<size_t>(bh) * n * a.d;
+  const float* __restrict__ ct = a.ctab + static_cast<size_t>(h) * stride + kCPad + n - 1;
+  const int cbeg = pass * CT * 32, cend = min(a.d, cbeg + CT * 32);
+  auto value = [](uint4 hh, uint4 ll, int j) {  // element j of a pair of fragments
+    const uint32_t w[4] = {hh.x, hh.y, hh.z, hh.w}, u[4] = {ll.x, ll.y, ll.z, ll.w};
+    const halfx2 hp = __builtin_bit_cast(halfx2, w[j >> 1]), lp = __builtin_bit_cast(halfx2, u[j >> 1]);
+    return fmaf(static_cast<float>(lp[j & 1]), kLoInv, static_cast<float>(hp[j & 1]));
+  };
+  for (int blk = f0; blk < f1; ++blk) {
+    if (vf[blk] == 0u) continue;
+    const float* __restrict__ rec = a.krec + (hb + blk) * kRecWords;
+    for (int key = 32 * blk; key < min(32 * blk + 32, n); ++key) {
+      bool any = false;
+      for (int c = cbeg + lane; c < cend; c += 64) any |= !isfinite(to_f32(v[static_cast<size_t>(key) * a.d + c]));
+      if (!__any(any)) continue;
+      // S of (row, key): this lane half's slots, then the other half's
+      float s = 0.f;
+      const uint4* __restrict__ yp = a.Y + (hb + blk) * NY * kFragLanes + 32 * lh + (key & 31);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const uint4 yh = yp[(ks * 2 + 0) * kFragLanes], yl = yp[(ks * 2 + 1) * kFragLanes];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s = fmaf(value(x[ks][0], x[ks][1], j), value(yh, yl, j), s);
+      }
+      s += __shfl_xor(s, 32);
+      if (lh != 0 || i >= n || ct[key - i] == 0.f) continue;  // (a masked key reaches no row)
+      const double p = static_cast<double>(s * rec[key & 31] * ct[key - i]) * exp2_int(__float_as_int(rec[kRecE]));
+      for (int c = cbeg; c < cend; ++c) {
+        const float x1 = to_f32(v[static_cast<size_t>(key) * a.d + c]);
+        if (isfinite(x1)) continue;
+        if (a.nparts == 1)
+          zr[c] = static_cast<float>(zr[c] + p * x1 / dsum);
+        else
+          part[(c - cbeg) * kRows] += p * x1;
+      }
+    }
+  }
+}
+
+// z of a split row tile: its parts' numerators and denominators summed in
+// part order.  Work-group: the tile's rows and 8 of its columns (lanes along
+// the rows, the order of the parts in memory).
+template <int CT, int NW>
+__global__ __launch_bounds__(64 * NW) void k_direct_parts(DirectArgs a) {
+  constexpr int cw = CT * 32 + 1, kRows = 32 * NW;
+  const int row = threadIdx.x % kRows, cg = threadIdx.x / kRows;
+  int b = blockIdx.x;
+  const int grp = b % (CT * 4);
+  b /= CT * 4;
+  const int tile = b % a.tiles;
+  b /= a.tiles;
+  const int pass = b % a.passes, bh = b / a.passes, i = tile * kRows + row;
+  const int cl = 8 * grp + 4 * cg, c = pass * CT * 32 + cl;
+  if (i >= a.n || c >= a.d) return;
+  const double* __restrict__ part =
+      a.part + (static_cast<size_t>(bh * a.passes + pass) * a.tiles + tile) * a.nparts * (kRows * cw) + row;
+  double num[4] = {0.0, 0.0, 0.0, 0.0}, den = 0.0;
+  for (int p = 0; p < a.nparts; ++p) {
+    const double* __restrict__ q = part + static_cast<size_t>(p) * (kRows * cw);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) num[j] += q[(cl + j) * kRows];
+    den += q[CT * 32 * kRows];
+  }
+  float* __restrict__ zr = a.z + (static_cast<size_t>(bh) * a.n + i) * a.d;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (c + j < a.d) zr[c + j] = static_cast<float>(num[j] / den);
+  if (c == 0 && a.den)
+    a.den[static_cast<size_t>(bh) * a.n + i] =
+        static_cast<float>(den * exp2_int(a.rexp[static_cast<size_t>(bh) * a.nblk * kBlk + i]));
+}
+
+// ------------------------------------------------------------ launchers --
+namespace {
+
+// k steps the kernels are compiled for
+int round_ks(int ks) {
+  for (int k : {2, 4, 6, 8, 12, 16})
+    if (ks <= k) return k;
+  return 0;
+}
+
+// Waves (of 32 rows) per work-group.
+constexpr int direct_waves(int KS) { return 4; }
+
+template <typename TV, int KS, int CT>
+hipError_t direct_go(const DirectArgs& a, hipStream_t st) {
+  constexpr int NW = direct_waves(KS);
+  const long long blocks = static_cast<long long>(a.BH) * a.passes * a.tiles * a.nparts;
+  hipLaunchKernelGGL((k_direct<TV, KS, CT, NW>), dim3(static_cast<unsigned>(blocks)), dim3(64 * NW), 0, st, a);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || a.nparts == 1) return e;
+  hipLaunchKernelGGL((k_direct_parts<CT, NW>),
+                     dim3(static_cast<unsigned>(static_cast<long long>(a.BH) * a.passes * a.tiles * (CT * 4))),
+                     dim3(64 * NW), 0, st, a);
+  return hipGetLastError();
+}
+
+template <typename TV, int CT>
+hipError_t direct_ks(int KS, const DirectArgs& a, hipStream_t st) {
+  switch (KS) {
+    case 2: return direct_go<TV, 2, CT>(a, st);
+    case 4: return direct_go<TV, 4, CT>(a, st);
+    case 6: return direct_go<TV, 6, CT>(a, st);
+    case 8: return direct_go<TV, 8, CT>(a, st);
+    case 12: return direct_go<TV, 12, CT>(a, st);
+    case 16: return direct_go<TV, 16, CT>(a, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename TX, int DK>
+hipError_t prep_nt(const PrepArgs& a, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>(a.phi_blocks + a.v_blocks + a.H * ctab_chunks(a.n)));
+  const int ftiles = ((a.kind == kFeatTrf ? a.KS / 2 : a.KS) + 1) / 2;
+  if (ftiles <= 2)
+    hipLaunchKernelGGL((k_prep<TX, DK, 2>), grid, dim3(256), 0, st, a);
+  else if (ftiles <= 4)
+    hipLaunchKernelGGL((k_prep<TX, DK, 4>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_prep<TX, DK, 8>), grid, dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+template <typename TX>
+hipError_t prep_go(const PrepArgs& a, hipStream_t st) {
+  if (a.d <= 32) return prep_nt<TX, 2>(a, st);
+  if (a.d <= 64) return prep_nt<TX, 4>(a, st);
+  return prep_nt<TX, 8>(a, st);
+}
+
+}  // namespace
+
+int direct_ksteps(int kind, int d, int m) {
+  const int rows = kind == kFeatElu ? d : m;
+  const int ks = (rows + 15) / 16;
+  return round_ks(kind == kFeatTrf ? 2 * ks : ks);
+}
+
+// Parts a row tile's key blocks are split into.  W work-groups of nb key
+// blocks each fill the chip in rounds of its resident ones (two per CU, one
+// with more than 128 features); p parts cost ceil(W p / resident) rounds of
+// nb / p blocks and a fixed two, plus the partial sums' round trip (33 KB of
+// fp64 per 32 columns and part at about 4 TB/s, in units of a key block's
+// about 1 us).
+int direct_parts(long long BH, int n, int ct_total, int KS) {
+  const int ct = ct_total >= 2 ? 2 : 1, passes = (ct_total + ct - 1) / ct;
+  const int nb = (n + kBlk - 1) / kBlk;
+  const int rows = 32 * direct_waves(KS);
+  const long long W = BH * passes * ((n + rows - 1) / rows);
+  const long long resident = KS <= 8 ? 512 : 256;
+  if (W >= 4 * resident) return 1;
+  int best = 1;
+  double cost = 0.0;
+  for (int p = 1; p <= 32 && (p == 1 || nb / p >= 4); ++p) {
+    const double rounds = static_cast<double>((W * p + resident - 1) / resident);
+    const double c = rounds * (static_cast<double>(nb) / p + 2.0) +
+                     (p > 1 ? 4.0 + static_cast<double>(W) * p * ct * 33e3 * 2.0 / 4e6 : 0.0);
+    if (p == 1 || c < cost) {
+      best = p;
+      cost = c;
+    }
+  }
+  return best;
+}
+
+DirectLayout direct_layout(int B, int H, int n, int d, int ks) {
+  DirectLayout L{};
+  const size_t bh = static_cast<size_t>(B) * H;
+  L.nblk = (n + kBlk - 1) / kBlk;
+  L.ks = ks;
+  const int ct = (d + 31) / 32;
+  L.passes = (ct + 1) / 2;
+  L.ct_total = ct >= 2 ? 2 * L.passes : 1;
+  L.nparts = direct_parts(static_cast<long long>(bh), n, L.ct_total, ks);
+  size_t off = 0;
+  auto take = [&off](size_t bytes) {
+    const size_t at = off;
+    off = (off + bytes + 255) & ~static_cast<size_t>(255);
+    return at;
+  };
+  constexpr size_t kFrag = kFragLanes * sizeof(uint4);
+  L.fix = take((bh + 1) * sizeof(unsigned));
+  L.x = take(bh * L.nblk * ks * 2 * kFrag);
+  L.y = take(bh * L.nblk * ks * 2 * kFrag);
+  L.z = take(bh * L.nblk * L.ct_total * 2 * 2 * kFrag);
+  L.krec = take(bh * L.nblk * kRecWords * sizeof(float));
+  L.vflag = take(bh * L.nblk * sizeof(unsigned));
+  L.ctab = take(static_cast<size_t>(H) * ctab_stride(n) * sizeof(float));
+  L.crange = take(static_cast<size_t>(H) * ctab_chunks(n) * sizeof(int2));
+  const size_t rows = 32 * direct_waves(ks), tiles = (static_cast<size_t>(n) + rows - 1) / rows;
+  const size_t cw = (L.ct_total >= 2 ? 64 : 32) + 1;
+  L.part = take(L.nparts > 1 ? bh * L.passes * tiles * L.nparts * rows * cw * sizeof(double) : 0);
+  L.total = off;
+  return L;
+}
+
+hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
+                              const float* b, const float* W, int BH, int H, int n, int d, int m, bool nprf, int kind,
+                              hipStream_t st) {
+  PrepArgs p{};
+  p.q = q, p.k = k, p.v = v, p.W = W, p.b = b;
+  p.X = reinterpret_cast<uint4*>(w + L.x);
+  p.Y = reinterpret_cast<uint4*>(w + L.y);
+  p.Z = reinterpret_cast<uint4*>(w + L.z);
+  p.vflag = reinterpret_cast<unsigned*>(w + L.vflag);
+  p.ctab = reinterpret_cast<float*>(w + L.ctab);
+  p.crange = reinterpret_cast<int2*>(w + L.crange);
+  p.fix = reinterpret_cast<unsigned*>(w + L.fix);
+  p.BH = BH, p.H = H, p.n = n, p.nblk = L.nblk, p.d = d, p.m = m, p.KS = L.ks, p.ct_total = L.ct_total;
+  p.kind = kind, p.nprf = nprf ? 1 : 0;
+  p.krec = reinterpret_cast<float*>(w + L.krec);
+  p.tiles = (n + 127) / 128;
+  p.phi_blocks = 2 * BH * p.tiles;
+  p.v_blocks = BH * p.tiles;
+  p.inv_sqrt_m = static_cast<float>(1.0 / std::sqrt(static_cast<double>(m)));
+  const double lm = -0.5 * std::log2(static_cast<double>(m));
+  p.log2_m_hi = static_cast<float>(lm);
+  p.log2_m_lo = static_cast<float>(lm - static_cast<double>(p.log2_m_hi));
+  return bf16 ? prep_go<uint16_t>(p, st) : prep_go<float>(p, st);
+}
+
+hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf16, float* z, float* den, int BH, int H,
+                         int n, int d, hipStream_t st) {
+  DirectArgs a{};
+  a.X = reinterpret_cast<const uint4*>(w + L.x);
+  a.Y = reinterpret_cast<const uint4*>(w + L.y);
+  a.Z = reinterpret_cast<const uint4*>(w + L.z);
+  a.vflag = reinterpret_cast<const unsigned*>(w + L.vflag);
+  a.ctab = reinterpret_cast<const float*>(w + L.ctab);
+  a.crange = reinterpret_cast<const int2*>(w + L.crange);
+  a.v = v, a.z = z, a.den = den, a.part = reinterpret_cast<double*>(w + L.part);
+  a.BH = BH, a.H = H, a.n = n, a.nblk = L.nblk, a.d = d, a.ct_total = L.ct_total;
+  a.krec = reinterpret_cast<const float*>(w + L.krec);
+  const int rows = 32 * direct_waves(L.ks);
+  a.tiles = (n + rows - 1) / rows;
+  a.passes = L.passes, a.nparts = L.nparts;
+  // (one XCD's L2 then serves the work-groups of a head; with few heads the
+  // plain order spreads the row tiles, whose lengths differ, over the XCDs)
+  a.remap = BH >= 16 || BH % 8 == 0;
+  if (L.ct_total >= 2)
+    return bf16 ? direct_ks<uint16_t, 2>(L.ks, a, st) : direct_ks<float, 2>(L.ks, a, st);
+  return bf16 ? direct_ks<uint16_t, 1>(L.ks, a, st) : direct_ks<float, 1>(L.ks, a, st);
+}
+
+}  // namespace krpe

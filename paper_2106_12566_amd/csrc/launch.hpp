@@ -87,7 +87,33 @@ LongLayout long_layout(int B, int H, int n, int d, int M);
 // Feature splits of a forward convolution launch over nkb key blocks.
 int conv_fsplit(int l2, int BH, int cols, int M, int nkb);
 
-// Workspace of krpe_toeplitz_conv.
+// Workspace of the direct route for up to 256 features (csrc/direct.hip;
+// operands as the fragments of wprod.hpp, one KiB each).
+struct DirectLayout {
+  int nblk;      // 32-position blocks
+  int ks;        // 16-feature steps of phi
+  int ct_total;  // 32-column tiles of v (a multiple of the tiles per pass)
+  int passes;    // column passes of up to two tiles
+  int nparts;    // parts a row tile's keys are split into
+  size_t fix;    // uint  [BH + 1]  (first, as in AttnLayout; the total is written)
+  size_t x, y;   // phi(q), phi(k): S fragments [BH][nblk][ks][2]
+  size_t z;      // v: Z fragments [BH][nblk][ct_total][2][2 or 1]
+  size_t krec;   // float [BH][nblk][64]  powers of two of the keys and values of each block
+  size_t vflag;  // uint  [BH][nblk]  blocks with values that are not finite
+  size_t ctab;   // float [H][ctab_stride(n)]  c = exp(b), zero-padded
+  size_t crange; // int2  [H][ctab_chunks(n)]  range of finite b per table chunk
+  size_t part;   // double [BH][passes][tiles][nparts][columns + 1][rows] partial sums
+  size_t total;
+};
+// k steps of the direct kernels for these features (0: not covered, more than 256)
+int direct_ksteps(int kind, int d, int m);
+DirectLayout direct_layout(int B, int H, int n, int d, int ks);
+hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
+                              const float* b, const float* W, int BH, int H, int n, int d, int m, bool nprf, int kind,
+                              hipStream_t st);
+hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf16, float* z, float* den, int BH, int H,
+                         int n, int d, hipStream_t st);
+
 // Workspace of krpe_toeplitz_conv.  For n > 2^kMaxLog2N the Toeplitz matrix is
 // taken in nb x nb blocks of nbk = 2^kMaxLog2N positions (nb = 1 otherwise):
 // hs, hnorm and bwin then hold the spectra, norms and bias windows of one

@@ -1,0 +1,108 @@
+"""GPU tests of the direct route's kernels (csrc/direct.hip) at the sizes where they can go wrong:
+edges of the 32-key blocks and of the row tiles, feature counts around the 16-feature steps and the
+compiled step counts, column tiles and passes of v, row tiles split over work-groups, powers of two
+that differ by far more than fp16 holds, and values that are not finite.
+
+Tolerance: 2e-5 of a row's largest entry.  z is a ratio of sums of positive weights (PRF, elu + 1):
+its error is at most twice the relative error of a weight phi(q).phi(k) c plus that of a value.  A
+weight carries the errors of two phi (the exponent, of size up to 2^5, is rounded to 2^-24 of its
+terms in each of d / 16 partial sums of the projection: below 2^-19 in all), three products per
+term (2^-22) and fp32 sums over m features (2^-24 sqrt(m)): below 2^-17 = 7.6e-6; doubled, 1.5e-5.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2106_12566_amd import synth
+from parity_util import rownorm_err, sample_rows, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-5
+
+
+def _check(lib, d, nprf=False, features="prf", causal=False, rows=64):
+    wl = d["workload"]
+    B, H, n = wl.B, d["H"], wl.n
+    W = None if features == "elu" else d["W"]
+    print(f"direct {wl.name} {wl.qkv_dtype} {wl.bias} {features} nprf={nprf}", flush=True)
+    q, k, v = (to_gpu(d[x], wl.qkv_dtype) for x in ("q", "k", "v"))
+    z = lib.attention_fwd(q, k, v, to_gpu(d["b"]), None if W is None else to_gpu(W), nprf=nprf, features=features,
+                          route="direct", causal=causal).cpu().numpy()
+    assert np.all(np.isfinite(z))
+    sel = sample_rows(B, H, n, min(rows, B * H * n), seed=n, extra=[(0, 0, i) for i in (31, 32, 127, 128) if i < n])
+    ref, _ = oracle.attention_rows(d["q"], d["k"], d["v"], d["b"], W, sel, nprf=nprf, kind=features)
+    err = rownorm_err(np.stack([z[s] for s in sel]), ref)
+    print(f"  row-normwise error {err:.3e}", flush=True)
+    assert err <= TOL, err
+    return z
+
+
+@pytest.mark.parametrize("B,H,n,d,m,dt,bias", [
+    (1, 1, 1, 1, 1, "f32", "normal"),
+    (1, 2, 31, 8, 16, "f32", "causal"),
+    (2, 1, 32, 31, 17, "bf16", "normal"),
+    (1, 2, 33, 32, 33, "f32", "decay"),
+    (1, 1, 127, 33, 64, "f32", "causal"),
+    (3, 1, 129, 64, 65, "bf16", "causal"),
+    (1, 8, 257, 65, 97, "f32", "normal"),      # two column passes; XCD order of the work-groups
+    (1, 1, 640, 128, 129, "f32", "decay"),     # four column tiles, 12 k steps, d = 128
+    (1, 2, 500, 100, 200, "bf16", "normal"),   # 16 k steps
+    (1, 1, 300, 63, 256, "f32", "causal"),     # 16 k steps, fp32 values, columns not a multiple of 4
+    (1, 1, 2049, 64, 128, "f32", "normal"),    # row tiles split into parts
+    (1, 1, 3000, 40, 48, "bf16", "causal"),    # parts of unequal spans
+    (2, 16, 1000, 64, 128, "f32", "decay"),
+])
+def test_direct_edges(gpu_lib, B, H, n, d, m, dt, bias):
+    _check(gpu_lib, synth.custom(B, H, n, d, m, seed=5 + n, qkv_dtype=dt, bias=bias), causal=bias == "causal")
+
+
+@pytest.mark.parametrize("features,n,d,m", [("trf", 130, 20, 15), ("trf", 333, 64, 128), ("elu", 200, 33, 33),
+                                            ("elu", 90, 128, 128), ("prf", 70, 96, 40)])
+def test_direct_feature_maps(gpu_lib, features, n, d, m):
+    _check(gpu_lib, synth.custom(1, 2, n, d, m, seed=n, bias="decay", bias_sigma=0.3), nprf=True, features=features)
+
+
+def test_direct_powers_far_apart(gpu_lib):
+    """Keys, queries and values whose sizes differ by far more than fp16 holds inside one 32-key
+    block (phi(k) from 2^-103 to 2^7): each position's features carry a power of their own, so the
+    first rows of a causal mask, which see only small ones, keep their accuracy (row 0 is v_0
+    whatever its weight).  The exponents of phi reach 2^7 here, where their rounding is eight times
+    that of the other tests."""
+    B, H, n, d, m = 1, 1, 200, 16, 32
+    dd = synth.custom(B, H, n, d, m, seed=9, bias="causal", qk_scale=0.5)
+    for i in range(0, n, 7):
+        dd["k"][..., i, :] *= 6.0
+        dd["q"][..., i, :] *= 3.0
+    dd["k"][..., 0, :] = 2.0
+    dd["v"][..., 64:96, :] *= 2.0 ** 30
+    z = gpu_lib.attention_fwd(*(to_gpu(dd[x]) for x in ("q", "k", "v", "b", "W")), route="direct",
+                              causal=True).cpu().numpy()
+    ref, _ = oracle.attention(dd["q"], dd["k"], dd["v"], dd["b"], dd["W"])
+    assert np.all(np.isfinite(z))
+    np.testing.assert_allclose(z[0, 0, 0], dd["v"][0, 0, 0], rtol=1e-6)
+    err = rownorm_err(z, ref)
+    print(f"powers far apart: {err:.3e}", flush=True)
+    assert err <= 8 * TOL, err
+
+
+@pytest.mark.parametrize("dt,n,d,parts", [("f32", 100, 64, False), ("bf16", 160, 40, False), ("f32", 2100, 24, True)])
+def test_direct_values_not_finite(gpu_lib, dt, n, d, parts):
+    """An infinite or NaN value reaches its column of the rows that see it and nothing else."""
+    dd = synth.custom(1, 1, n, d, 32, seed=n, qkv_dtype=dt, bias="causal")
+    q, k, v, b, W = (to_gpu(dd[x], dt) if x in "qkv" else to_gpu(dd[x]) for x in ("q", "k", "v", "b", "W"))
+    clean = gpu_lib.attention_fwd(q, k, v, b, W, route="direct", causal=True).cpu().numpy()
+    vi = v.clone()
+    j0, j1, j2 = n // 3, n // 2, n - 2
+    vi[0, 0, j0, 3] = float("inf")
+    vi[0, 0, j1, 5] = float("-inf")
+    vi[0, 0, j2, 7] = float("nan")
+    z = gpu_lib.attention_fwd(q, k, vi, b, W, route="direct", causal=True).cpu().numpy()
+    want = np.zeros_like(clean, dtype=bool)
+    want[0, 0, j0:, 3] = want[0, 0, j1:, 5] = want[0, 0, j2:, 7] = True
+    assert np.all(z[0, 0, j0:, 3] == np.inf) and np.all(z[0, 0, j1:, 5] == -np.inf)
+    assert np.all(np.isnan(z[0, 0, j2:, 7]))
+    # elsewhere only the elements themselves left the sums, where no row sees them: equal to 2e-5
+    scale = np.max(np.abs(clean), axis=-1, keepdims=True)
+    assert np.max(np.where(want, 0.0, np.abs(np.where(want, 0.0, z) - clean)) / scale) <= TOL
