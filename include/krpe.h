@@ -259,8 +259,7 @@ size_t krpe_attention_bwd_workspace(int B, int H, int n, int d, int m, unsigned 
 
 /*
  * Backward pass of krpe_attention_fwd_ex (PRF features of Eq. (5), optional
- * KRPE_NPRF, the route bits and KRPE_HINT_CAUSAL for the recomputed forward;
- * W fixed): the gradients of L = sum(dz * z) with respect to q, k,
+ * KRPE_NPRF, the route bits and KRPE_HINT_CAUSAL; W fixed): the gradients of L = sum(dz * z) with respect to q, k,
  * v and b, z from Eq. (10).  The paper states no backward pass; these are the
  * derivatives of its forward definition.  With A = C o (phi(Q) phi(K)^T),
  * den = A 1 and Gh = [dz / den, -(dz . z) / den] per row:
@@ -268,8 +267,14 @@ size_t krpe_attention_bwd_workspace(int B, int H, int n, int d, int m, unsigned 
  *   dphi(K) = ((Gh [v, 1]^T) o C)^T phi(Q),  dx = (dphi o phi) W - x rowsum(dphi o phi)
  * (through the row normalisation when KRPE_NPRF).  Each of the three
  * products is one run of the forward's FFT convolution kernel, with the
- * transposed Toeplitz matrix (the reversed b) where C^T appears; the forward
- * pass is recomputed inside (its exact-row evaluation included).
+ * transposed Toeplitz matrix (the reversed b) where C^T appears, or, on the
+ * direct route (m <= 256), a weighted product on the matrix cores like the
+ * direct forward; the forward pass is recomputed inside (its exact-row
+ * evaluation included).  Without a route bit the route follows the forward's
+ * cost model, except that a stated causal mask without KRPE_NPRF keeps the
+ * FFT products: their rounding, spread over the sequence, reaches 1e-4 to
+ * 4e-1 of a gradient's norm there (rows with small denominators), that of
+ * KRPE_ROUTE_DIRECT's 1e-6.
  * q, k, v : [B, H, n, d] in qkv_dtype    b : [H, 2n-1]    W : [H, m, d]
  * dz      : [B, H, n, d] fp32             dq, dk, dv : [B, H, n, d] fp32 (outputs)
  * db      : [H, 2n-1] fp32 (output, summed over the batch), or NULL to skip it:

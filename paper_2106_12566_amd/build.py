@@ -12,12 +12,13 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libkrpe.so")
-SOURCES = [os.path.join(HERE, "csrc", "kernels.hip"), os.path.join(HERE, "csrc", "grad_bias.hip"),
-           os.path.join(HERE, "csrc", "direct.hip"), os.path.join(HERE, "csrc", "long_seq.hip"), os.path.join(HERE, "csrc", "api.hip")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "grad_bias.hip", "direct.hip", "bwd_direct.hip",
+                                                   "long_seq.hip", "api.hip")]
 # The convolution kernel at N = 16384, compiled on its own with LLVM's
 # maximum-ILP machine scheduler (measured faster for that length only).
 TOP = os.path.join(HERE, "csrc", "conv_top.hip")
@@ -41,15 +42,17 @@ def _flags() -> list[str]:
     ]
 
 
-def command(out: str = LIB, top: str = TOP) -> list[str]:
-    """One hipcc run linking every source (`top`: conv_top.hip, or its object built by
-    top_command) into `out`."""
-    # (the object goes first: hipcc marks every input after a .hip file as HIP source)
-    return [hipcc(), *_flags(), "-shared", "-o", out, top, *SOURCES]
+def command(out: str = LIB) -> list[str]:
+    """One hipcc run compiling and linking every source into `out`."""
+    return [hipcc(), *_flags(), "-shared", "-o", out, TOP, *SOURCES]
 
 
-def top_command(obj: str) -> list[str]:
-    return [hipcc(), *_flags(), *TOP_FLAGS, "-c", "-o", obj, TOP]
+def object_command(src: str, obj: str) -> list[str]:
+    return [hipcc(), *_flags(), *(TOP_FLAGS if src == TOP else []), "-c", "-o", obj, src]
+
+
+def link_command(objs: list[str], out: str) -> list[str]:
+    return [hipcc(), f"--offload-arch={ARCH}", "-fPIC", "-shared", "-o", out, *objs]
 
 
 def _run(cmd: list[str], verbose: bool) -> None:
@@ -61,11 +64,18 @@ def _run(cmd: list[str], verbose: bool) -> None:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile libkrpe.so (always recompiles); return its path."""
-    tmp, obj = LIB + ".tmp", LIB + ".top.o"
-    _run(top_command(obj), verbose)
-    _run(command(tmp, obj), verbose)
-    os.remove(obj)
+    """Compile libkrpe.so (always recompiles, the sources side by side); return its path."""
+    tmp = LIB + ".tmp"
+    sources = [TOP, *SOURCES]
+    objs = [f"{LIB}.{os.path.splitext(os.path.basename(s))[0]}.o" for s in sources]
+    try:
+        with ThreadPoolExecutor(max_workers=min(len(sources), os.cpu_count() or 1)) as pool:
+            list(pool.map(lambda so: _run(object_command(*so), verbose), zip(sources, objs)))
+        _run(link_command(objs, tmp), verbose)
+    finally:
+        for o in objs:
+            if os.path.exists(o):
+                os.remove(o)
     os.replace(tmp, LIB)
     return LIB
 

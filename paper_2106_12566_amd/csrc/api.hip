@@ -101,7 +101,7 @@ bool direct_is_faster(long long BH, int n, int M, int d, bool causal) {
   const double heads = static_cast<double>(BH);
   const double pairs = causal ? 0.5 * static_cast<double>(n) * (n + 1) : static_cast<double>(n) * n;
   // (both direct kernels run the features in steps of 64)
-  const double per_pair = direct_rows_path(BH, n, M) ? 1.74e-14 : 1.9e-14;
+  const double per_pair = M <= 128 && BH * ((n + 31) / 32) >= 1536 ? 1.74e-14 : 1.9e-14;
   const double direct = per_pair * heads * pairs * (((M + 63) / 64) * 64 + d + 1) + 7.4e-5;
   const double rate = l2 <= 12 ? 1.65e-13 : (l2 == 13 ? 3.8e-13 : 3.1e-13);
   // (a causal mask leaves nb (nb + 1) / 2 of the block pairs live; the others are skipped)
@@ -116,6 +116,22 @@ bool direct_is_faster(long long BH, int n, int M, int d, bool causal) {
 bool use_direct(unsigned flags, long long BH, int n, int M, int d) {
   if (flags & KRPE_ROUTE_DIRECT) return true;
   if (flags & KRPE_ROUTE_FFT) return false;
+  return direct_is_faster(BH, n, M, d, (flags & KRPE_HINT_CAUSAL) != 0);
+}
+
+// Route of the backward pass's products (up to 256 features): the direct ones
+// of bwd_direct.hip or the transforms.  A call that states a causal mask, with
+// neither row normalisation nor a route, keeps the transforms (and with them
+// every bit of its results): where rows with small denominators weigh in, the
+// rounding that a transform spreads over the sequence is 1e-4 to 4e-1 of a
+// gradient's norm against 64 bits (the direct products 4e-7), so the two
+// routes differ by more than the results of one call may change.
+// KRPE_ROUTE_DIRECT asks for the direct ones (64 tokens, 12 heads: 0.08 ms
+// against 0.80).
+bool use_direct_products(unsigned flags, long long BH, int n, int M, int d) {
+  if (flags & KRPE_ROUTE_DIRECT) return true;
+  if (flags & KRPE_ROUTE_FFT) return false;
+  if ((flags & KRPE_HINT_CAUSAL) && !(flags & KRPE_NPRF)) return false;
   return direct_is_faster(BH, n, M, d, (flags & KRPE_HINT_CAUSAL) != 0);
 }
 
@@ -296,7 +312,8 @@ krpe_status_t run_direct(const DirectLayout& L, char* w, const void* q, const vo
                          bool nprf, hipStream_t st, void* const* events) {
   for (int e = 0; e < 2; ++e)
     if (krpe_status_t s = record(events, e, st)) return s;
-  if (krpe_status_t s = hip_check(launch_direct_prep(L, w, q, k, v, bf16, b, W, BHi, H, n, d, m, nprf, kind, st),
+  if (krpe_status_t s = hip_check(launch_direct_prep(L, w, q, k, v, bf16, b, W, BHi, H, n, d, m, nprf, kind, nullptr,
+                                                       nullptr, nullptr, st),
                                   "operand launch"))
     return s;
   for (int e = 2; e < 4; ++e)
@@ -362,10 +379,9 @@ krpe_status_t run_forward(const AttnLayout& L, char* w, const void* q, const voi
   const int pairs = (d + 2) / 2;
 
   if (direct) {
-    // phi(q), phi(k), then every row evaluated directly: by the row-parallel
-    // kernel, or by the exact-row kernel over a queue of every row.  The queue
-    // is marked on both paths: its count is the number of rows evaluated
-    // exactly that krpe_attention_fwd_stats reports.
+    // More than 256 features (run_direct takes the others): phi(q), phi(k),
+    // then every row through the exact-row kernel.  The queue's count is the
+    // number of rows evaluated exactly that krpe_attention_fwd_stats reports.
     for (int e = 0; e < 2; ++e)
       if (krpe_status_t s = record(events, e, st)) return s;
     if (krpe_status_t s = hip_check(launch_feature_map(bf16, q, k, W, phiq, phik, 2, true, N, BHi, H, n, d, m,
@@ -831,7 +847,10 @@ int krpe_attention_fwd_route(int B, int H, int n, int d, int m, unsigned flags) 
 size_t krpe_attention_bwd_workspace(int B, int H, int n, int d, int m, unsigned flags) {
   if (B < 0 || H < 0 || n < 1 || n > (1 << kMaxLog2N) || d < 1 || d > kMaxD || m < 1 || m > kMaxM) return 0;
   if (flags & ~kBwdFlags) return 0;
-  return bwd_layout(B, H, n, d, m).total;
+  // serves either route, whatever the route bits and the hint of a call
+  const size_t fft = bwd_layout(B, H, n, d, m).total;
+  const size_t direct = direct_bwd_ksteps(m) ? direct_bwd_layout(B, H, n, d, m).total : 0;
+  return fft > direct ? fft : direct;
 }
 
 krpe_status_t krpe_attention_bwd(const void* q, const void* k, const void* v, int qkv_dtype, const float* b,
@@ -853,8 +872,11 @@ krpe_status_t krpe_attention_bwd(const void* q, const void* k, const void* v, in
   for (const void* p : ptrs)
     if (misaligned(p)) return fail(KRPE_ERR_ALIGN, "all pointers must be 16-byte aligned");
   const BwdLayout L = bwd_layout(B, H, n, d, m);
-  if (!ws || ws_bytes < L.total)
-    return fail(KRPE_ERR_WORKSPACE, "workspace needs " + std::to_string(L.total) + " bytes");
+  const bool direct = use_direct(flags, static_cast<long long>(B) * H, n, m, d);
+  const bool products = direct_bwd_ksteps(m) != 0 && use_direct_products(flags, static_cast<long long>(B) * H, n, m, d);
+  const size_t need = products ? direct_bwd_layout(B, H, n, d, m).total : L.total;
+  if (!ws || ws_bytes < need)
+    return fail(KRPE_ERR_WORKSPACE, "workspace needs " + std::to_string(need) + " bytes");
   const size_t qkv_bytes = bh * n * d * dtype_size(qkv_dtype), g_bytes = bh * n * d * sizeof(float);
   const Range ins[] = {{q, qkv_bytes},
                        {k, qkv_bytes},
@@ -893,8 +915,11 @@ krpe_status_t krpe_attention_bwd(const void* q, const void* k, const void* v, in
   const float* phik = reinterpret_cast<const float*>(w + L.f.phik);
   const long long fstride = static_cast<long long>(m) * N, gstride = static_cast<long long>(d + 1) * N;
 
+  if (products)
+    return hip_check(launch_direct_bwd(direct_bwd_layout(B, H, n, d, m), w, q, k, v, bf16, b, W, dz, dq, dk, dv, db, BHi,
+                                       H, n, d, m, nprf, st),
+                     "direct backward launch");
   // forward: phi(q), phi(k), z and the denominators
-  const bool direct = use_direct(flags, static_cast<long long>(B) * H, n, m, d);
   if (krpe_status_t s = run_forward(L.f, w, q, k, v, bf16, b, W, zf, den, BHi, H, n, d, m, m, kFeatPrf, nprf, direct,
                                     st, nullptr))
     return s;

@@ -13,6 +13,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "direct_kernel.hpp"
 #include "wprod.hpp"
 
 namespace krpe {
@@ -41,42 +42,14 @@ struct PrepArgs {
   unsigned* vflag;  // [BH][nblk]
   float* ctab;      // [H][ctab_stride]
   int2* crange;     // [H][ctab_chunks]
+  float* crev;      // the table and ranges of c_{-t} (NULL: not wanted)
+  int2* rrange;
   unsigned* fix;    // fix[BH] = rows evaluated exactly (all of them)
-  int* rexp;        // [BH][32 nblk] powers of phi(q) (NULL: not wanted)
+  int* kpow;        // [BH][32 nblk] powers of phi(k) (NULL: not wanted)
   int BH, H, n, nblk, d, m, KS, ct_total, kind, nprf, tiles, phi_blocks, v_blocks;
   float inv_sqrt_m;
   float log2_m_hi, log2_m_lo;  // -log2(sqrt(m)) in two floats
 };
-// Record of a 32-key block, 64 words: [0, 32) 2^(e_j - E) per key, e_j the
-// power of phi(k_j) and E = word 32 (int); word 33 (int) the power of its
-// values.
-constexpr int kRecWords = 64, kRecE = 32, kRecV = 33;
-// S of two positions is at most 2^30 M in units of their powers: E carries 30
-// of them, so that P stays near c_{j-i}'s range.
-constexpr int kRecBias = 30;
-
-// 8 values of a row from position p (zeros past `count` values of the row)
-template <typename T>
-__device__ __forceinline__ void load8(const T* __restrict__ p, int count, bool vec, float (&x)[8]) {
-  if (vec && count >= 8) {
-    if constexpr (std::is_same<T, float>::value) {
-      const float4 a = reinterpret_cast<const float4*>(p)[0], c = reinterpret_cast<const float4*>(p)[1];
-      x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w, x[4] = c.x, x[5] = c.y, x[6] = c.z, x[7] = c.w;
-    } else {
-      const uint4 u = *reinterpret_cast<const uint4*>(p);
-      const unsigned w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        x[2 * j] = __uint_as_float(w[j] << 16);
-        x[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = j < count ? to_f32(p[j]) : 0.f;
-  }
-}
-
 constexpr float kLn2 = 0.69314718055994531f;
 
 // 2^((s + sl) (r + rl) + (c + cl)) with the exponent in two floats (its rounding
@@ -285,9 +258,8 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
     });
   }
   if (!store) return;
-  if (src == 0) {
-    if (a.rexp && lh == 0) a.rexp[block * kBlk + lr] = ex;
-  } else {
+  if (src == 1) {
+    if (a.kpow && lh == 0) a.kpow[block * kBlk + lr] = ex;
     // (positions without features have no power of their own)
     int E = any_phi ? ex : -400;
 #pragma unroll
@@ -374,7 +346,17 @@ __device__ __forceinline__ void prep_c(const PrepArgs& a, int bid) {
 #pragma unroll
   for (int j = 0; j < kCChunk / 256; ++j) {
     const int e = ch * kCChunk + 256 * j + static_cast<int>(threadIdx.x), s = e - kCPad;
-    if (e < stride) ct[e] = s >= 0 && s < len ? expf(v[j]) : 0.f;
+    const float cv = s >= 0 && s < len ? expf(v[j]) : 0.f;
+    if (e < stride) ct[e] = cv;
+    if (a.crev && e < stride) {
+      // (the pads of the reversed table are written by the entries past len)
+      float* __restrict__ cr = a.crev + static_cast<size_t>(h) * stride;
+      if (s >= 0 && s < len) {
+        cr[kCPad + len - 1 - s] = cv;
+      } else {
+        cr[e] = 0.f;
+      }
+    }
     if (s >= 0 && s < len && v[j] != -INFINITY) {
       lo = min(lo, s);
       hi = max(hi, s);
@@ -388,8 +370,10 @@ __device__ __forceinline__ void prep_c(const PrepArgs& a, int bid) {
   if ((threadIdx.x & 63) == 0) wr[threadIdx.x >> 6] = make_int2(lo, hi);
   __syncthreads();
   if (threadIdx.x == 0) {
-    a.crange[static_cast<size_t>(h) * chunks + ch] =
-        make_int2(min(min(wr[0].x, wr[1].x), min(wr[2].x, wr[3].x)), max(max(wr[0].y, wr[1].y), max(wr[2].y, wr[3].y)));
+    lo = min(min(wr[0].x, wr[1].x), min(wr[2].x, wr[3].x));
+    hi = max(max(wr[0].y, wr[1].y), max(wr[2].y, wr[3].y));
+    a.crange[static_cast<size_t>(h) * chunks + ch] = make_int2(lo, hi);
+    if (a.crev) a.rrange[static_cast<size_t>(h) * chunks + ch] = hi < 0 ? make_int2(lo, hi) : make_int2(len - 1 - hi, len - 1 - lo);
     if (bid == 0) a.fix[a.BH] = static_cast<unsigned>(a.BH) * static_cast<unsigned>(a.n);
   }
 }
@@ -405,274 +389,6 @@ __global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
     prep_v<TX>(a, bid - a.phi_blocks);
   } else {
     prep_c(a, bid - a.phi_blocks - a.v_blocks);
-  }
-}
-
-// --------------------------------------------------------------- direct --
-// One work-group: 32 NW consecutive rows of one (batch, head), each wave its
-// own 32, over the 32-key blocks of its part of the rows' finite-b range.  A
-// block's fragments of phi(k) and v, its strip of c and its record are staged
-// to LDS one block ahead by direct loads and shared by the waves; phi(q) stays
-// in registers.  Per block and wave: S^T = phi(k) phi(q)^T (lane: row lr, keys
-// along the registers), P = S^T 2^(e_j - E) c_{j-i}, P split with the power of
-// its row's largest entry, and Z^T = [v]^T P^T (lane: row lr again, so that
-// the row's power applies lane by lane), whose fp32 sums over the 32 keys are
-// added into fp64 totals; the denominator is the fp32 sum of P added likewise.
-// The power of phi(q_i) cancels in z.  P's small term is stored unscaled (its
-// largest entry is at 2^14, terms below 2^-40 of that are lost).  A wave skips
-// the blocks outside its own rows' range (it still stages and meets the
-// barriers).
-struct DirectArgs {
-  const uint4 *X, *Y, *Z;
-  const float* krec;
-  const unsigned* vflag;
-  const float* ctab;
-  const int2* crange;
-  const void* v;
-  float *z, *den;
-  const int* rexp;
-  double* part;
-  int BH, H, n, nblk, d, ct_total, tiles, passes, nparts, remap;
-};
-
-template <typename TV, int KS, int CT, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void k_direct(DirectArgs a) {
-  constexpr int NSZ = sizeof(TV) == 2 ? 1 : 2;
-  constexpr int kRows = 32 * NW;
-  constexpr int NY = KS * 2, NF = NY + CT * 2 * NSZ;  // fragments per key block
-  constexpr int NC = (kRows + 31 + 63) / 64;          // 64-entry pieces of the c strip (kRows + 31 entries used)
-  __shared__ uint4 tiles_lds[2][NF * kFragLanes];
-  __shared__ __align__(16) float strip[2][NC * 64 + kRecWords];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lr = lane & 31, lh = lane >> 5;
-  int b = a.remap ? xcd_block(blockIdx.x, gridDim.x) : static_cast<int>(blockIdx.x);
-  const int pi = b % a.nparts;
-  b /= a.nparts;
-  const int tile = a.tiles - 1 - b % a.tiles;  // (under a causal mask the last rows see the most keys)
-  b /= a.tiles;
-  const int pass = b % a.passes, bh = b / a.passes, h = bh % a.H;
-  const int n = a.n, row0 = tile * kRows, wrow0 = row0 + 32 * wave;
-  const int2 br = head_range(a.crange + static_cast<size_t>(h) * ctab_chunks(n), ctab_chunks(n), lane);
-  // key blocks [lo, hi) of rows r0 .. r1
-  auto key_blocks = [&](int r0, int r1, int& lo, int& hi) {
-    const int jlo = max(0, r0 + br.x - (n - 1)), jhi = min(n - 1, r1 + br.y - (n - 1));
-    lo = jhi >= jlo ? jlo >> 5 : 0;
-    hi = jhi >= jlo ? (jhi >> 5) + 1 : 0;
-  };
-  int b0, b1, wlo = 0, whi = 0;
-  key_blocks(row0, min(row0 + kRows, n) - 1, b0, b1);
-  if (wrow0 < n) key_blocks(wrow0, min(wrow0 + 32, n) - 1, wlo, whi);
-  {
-    const int nb = b1 - b0, s = b0;
-    b0 = s + static_cast<int>(static_cast<long long>(nb) * pi / a.nparts);
-    b1 = s + static_cast<int>(static_cast<long long>(nb) * (pi + 1) / a.nparts);
-  }
-  // phi(q) of this wave's rows
-  const size_t xblk = static_cast<size_t>(bh) * a.nblk + min(wrow0 >> 5, a.nblk - 1);
-  uint4 x[KS][2];
-  {
-    const uint4* __restrict__ xp = a.X + xblk * NY * kFragLanes + lane;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int s = 0; s < 2; ++s) x[ks][s] = xp[(ks * 2 + s) * kFragLanes];
-  }
-  const uint32_t zbytes = static_cast<uint32_t>(a.ct_total) * 2 * NSZ * 1024u;  // per key block
-  const int stride = ctab_stride(n);
-  const size_t hb = static_cast<size_t>(bh) * a.nblk;
-  const __amdgpu_buffer_rsrc_t ry = buffer_of(a.Y + hb * NY * kFragLanes, static_cast<size_t>(a.nblk) * NY * 1024);
-  const __amdgpu_buffer_rsrc_t rz =
-      buffer_of(reinterpret_cast<const char*>(a.Z) + hb * zbytes, static_cast<size_t>(a.nblk) * zbytes);
-  const __amdgpu_buffer_rsrc_t rc = buffer_of(a.ctab + static_cast<size_t>(h) * stride, static_cast<size_t>(stride) * 4);
-  const __amdgpu_buffer_rsrc_t rr = buffer_of(a.krec + hb * kRecWords, static_cast<size_t>(a.nblk) * kRecWords * 4);
-  const uint32_t lds0 = lds_address(&tiles_lds[0][0]), str0 = lds_address(&strip[0][0]);
-  const uint32_t zpass = static_cast<uint32_t>(pass * CT * 2 * NSZ) * 1024u;
-  // pieces of block blk into buffer `buf`: wave w stages pieces w, w + NW, ..:
-  // the fragments, the c entries from key 32 blk and row row0 + kRows - 1 on,
-  // the record
-  auto stage = [&](int blk, int buf) {
-    const uint32_t base = lds0 + static_cast<uint32_t>(buf) * (NF * 1024u), v16 = lane * 16u;
-    const uint32_t sb = str0 + static_cast<uint32_t>(buf) * (NC * 64 + kRecWords) * 4u;
-    const uint32_t yo = static_cast<uint32_t>(blk) * (NY * 1024u), zo = static_cast<uint32_t>(blk) * zbytes + zpass;
-    const uint32_t co = static_cast<uint32_t>(32 * blk - row0 - (kRows - 1) + n - 1 + kCPad) * 4u;
-#pragma unroll
-    for (int i = 0; i < (NF + NC + 1 + NW - 1) / NW; ++i) {
-      const int f = NW * i + wave;
-      if (f < NY)
-        stage_lds<16>(ry, base + f * 1024u, v16, yo + f * 1024u);
-      else if (f < NF)
-        stage_lds<16>(rz, base + f * 1024u, v16, zo + (f - NY) * 1024u);
-      else if (f < NF + NC)
-        stage_lds<4>(rc, sb + (f - NF) * 256u, lane * 4u, co + (f - NF) * 256u);
-      else if (f == NF + NC)
-        stage_lds<4>(rr, sb + NC * 256u, lane * 4u, static_cast<uint32_t>(blk) * (kRecWords * 4u));
-    }
-  };
-  double zt[CT][16];
-  double dsum = 0.0;
-#pragma unroll
-  for (int t = 0; t < CT; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) zt[t][e] = 0.0;
-  if (b0 < b1) stage(b0, 0);
-  for (int blk = b0; blk < b1; ++blk) {
-    const int buf = (blk - b0) & 1;
-    // this block's pieces are in LDS, the other buffer is consumed
-    stage_wait();
-    __syncthreads();
-    if (blk + 1 < b1) stage(blk + 1, buf ^ 1);
-    if (blk < wlo || blk >= whi) continue;
-    const uint4* __restrict__ y = &tiles_lds[buf][lane];
-    const uint4* __restrict__ zf = y + NY * kFragLanes;
-    const float* __restrict__ rec = &strip[buf][NC * 64];
-    const float* __restrict__ cs = &strip[buf][kRows - 1 - 32 * wave - lr + 4 * lh];
-    floatx16 s = zero16(), s1 = zero16();
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const uint4 yh = y[(ks * 2 + 0) * kFragLanes], yl = y[(ks * 2 + 1) * kFragLanes];
-      s = mfma_f16(yh, x[ks][0], s);
-      s1 = mfma_f16(yh, x[ks][1], s1);
-      s1 = mfma_f16(yl, x[ks][0], s1);
-    }
-    // P: lane row lr, keys 8 (e / 4) + 4 lh + e % 4
-    float p[16];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 kr = *reinterpret_cast<const float4*>(rec + 8 * g + 4 * lh);
-      const float k4[4] = {kr.x, kr.y, kr.z, kr.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        p[4 * g + j] = fmaf(s1[4 * g + j], kLoInv, s[4 * g + j]) * k4[j] * cs[8 * g + j];
-    }
-    if (32 * blk + 32 > n) {  // uniform: keys past n (phi(k) = 0 there, but c may be infinite)
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (32 * blk + 8 * (e >> 2) + 4 * lh + (e & 3) >= n) p[e] = 0.f;
-    }
-    float ds = 0.f, mx = 0.f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      ds += p[e];
-      mx = fmaxf(mx, fabsf(p[e]));
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    // the row's power in this block: its largest P is brought to [2^14, 2^15)
-    // (zero and NaN maxima: 2^15, any power serves)
-    const int ex = max(__builtin_amdgcn_frexp_expf(mx), -100) - 15;
-    const float sc = __int_as_float((127 - ex) << 23);
-    const int kexp = __float_as_int(rec[kRecE]);
-    const double zs = exp2_int(kexp + __float_as_int(rec[kRecV]) + ex);
-    dsum = fma(static_cast<double>(ds), exp2_int(kexp), dsum);
-    uint4 ph[2], pl[2];
-#pragma unroll
-    for (int k2 = 0; k2 < 2; ++k2) {
-      float v8[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v8[t] = p[8 * k2 + t] * sc;
-      split_f16x8(v8, 1.f, ph[k2], pl[k2]);
-    }
-#pragma unroll
-    for (int t = 0; t < CT; ++t) {
-      floatx16 zc = zero16(), z1 = zero16();
-#pragma unroll
-      for (int k2 = 0; k2 < 2; ++k2) {
-        const uint4 vh = zf[((t * 2 + k2) * NSZ + 0) * kFragLanes];
-        zc = mfma_f16(vh, pl[k2], zc);
-        zc = mfma_f16(vh, ph[k2], zc);
-        if constexpr (NSZ > 1) z1 = mfma_f16(zf[((t * 2 + k2) * NSZ + 1) * kFragLanes], ph[k2], z1);
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float zz = NSZ > 1 ? fmaf(z1[e], kLoInv, zc[e]) : zc[e];
-        zt[t][e] = fma(static_cast<double>(zz), zs, zt[t][e]);
-      }
-    }
-  }
-  if (wrow0 >= n) return;  // uniform per wave; no barrier follows
-  dsum += __shfl_xor(dsum, 32);  // the other half-wave's keys of row lr
-  const int i = wrow0 + lr;
-  // this lane: row i, columns 32 (pass CT + t) + 8 (e / 4) + 4 lh + e % 4
-  constexpr int cw = CT * 32 + 1;
-  const int c0 = pass * CT * 32 + 4 * lh;
-  double* __restrict__ part = a.part + ((static_cast<size_t>(bh * a.passes + pass) * a.tiles + tile) * a.nparts + pi) *
-                                           (kRows * cw) + 32 * wave + lr;  // [column][row]
-  float* __restrict__ zr = a.z + (static_cast<size_t>(bh) * n + i) * a.d;
-  if (a.nparts == 1) {
-    const double inv = 1.0 / dsum;
-    if (i < n) {
-#pragma unroll
-      for (int t = 0; t < CT; ++t)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int c = c0 + 32 * t + 8 * g;
-          float4 o;
-          o.x = static_cast<float>(zt[t][4 * g] * inv);
-          o.y = static_cast<float>(zt[t][4 * g + 1] * inv);
-          o.z = static_cast<float>(zt[t][4 * g + 2] * inv);
-          o.w = static_cast<float>(zt[t][4 * g + 3] * inv);
-          if (a.d % 4 == 0) {  // rows 16-byte aligned
-            if (c < a.d) *reinterpret_cast<float4*>(zr + c) = o;
-          } else {
-            if (c < a.d) zr[c] = o.x;
-            if (c + 1 < a.d) zr[c + 1] = o.y;
-            if (c + 2 < a.d) zr[c + 2] = o.z;
-            if (c + 3 < a.d) zr[c + 3] = o.w;
-          }
-        }
-      if (pass == 0 && lh == 0 && a.den)
-        a.den[static_cast<size_t>(bh) * n + i] = static_cast<float>(dsum * exp2_int(a.rexp[xblk * kBlk + lr]));
-    }
-  } else {
-#pragma unroll
-    for (int t = 0; t < CT; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) part[(32 * t + 8 * (e >> 2) + 4 * lh + (e & 3)) * kRows] = zt[t][e];
-    if (lh == 0) part[CT * 32 * kRows] = dsum;
-  }
-  // Values that are not finite (stored as zero fragments, their blocks
-  // flagged): P v added in fp64, one key at a time; rare.
-  const unsigned* __restrict__ vf = a.vflag + hb;
-  const int f0 = max(b0, wlo), f1 = min(b1, whi);
-  bool odd = false;
-  for (int blk = f0 + lane; blk < f1; blk += 64) odd |= vf[blk] != 0u;
-  if (!__any(odd)) return;
-  __threadfence();  // the rows stored above are read back below, by other lanes
-  const TV* __restrict__ v = static_cast<const TV*>(a.v) + static_cast<size_t>(bh) * n * a.d;
-  const float* __restrict__ ct = a.ctab + static_cast<size_t>(h) * stride + kCPad + n - 1;
-  const int cbeg = pass * CT * 32, cend = min(a.d, cbeg + CT * 32);
-  auto value = [](uint4 hh, uint4 ll, int j) {  // element j of a pair of fragments
-    const uint32_t w[4] = {hh.x, hh.y, hh.z, hh.w}, u[4] = {ll.x, ll.y, ll.z, ll.w};
-    const halfx2 hp = __builtin_bit_cast(halfx2, w[j >> 1]), lp = __builtin_bit_cast(halfx2, u[j >> 1]);
-    return fmaf(static_cast<float>(lp[j & 1]), kLoInv, static_cast<float>(hp[j & 1]));
-  };
-  for (int blk = f0; blk < f1; ++blk) {
-    if (vf[blk] == 0u) continue;
-    const float* __restrict__ rec = a.krec + (hb + blk) * kRecWords;
-    for (int key = 32 * blk; key < min(32 * blk + 32, n); ++key) {
-      bool any = false;
-      for (int c = cbeg + lane; c < cend; c += 64) any |= !isfinite(to_f32(v[static_cast<size_t>(key) * a.d + c]));
-      if (!__any(any)) continue;
-      // S of (row, key): this lane half's slots, then the other half's
-      float s = 0.f;
-      const uint4* __restrict__ yp = a.Y + (hb + blk) * NY * kFragLanes + 32 * lh + (key & 31);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const uint4 yh = yp[(ks * 2 + 0) * kFragLanes], yl = yp[(ks * 2 + 1) * kFragLanes];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) s = fmaf(value(x[ks][0], x[ks][1], j), value(yh, yl, j), s);
-      }
-      s += __shfl_xor(s, 32);
-      if (lh != 0 || i >= n || ct[key - i] == 0.f) continue;  // (a masked key reaches no row)
-      const double p = static_cast<double>(s * rec[key & 31] * ct[key - i]) * exp2_int(__float_as_int(rec[kRecE]));
-      for (int c = cbeg; c < cend; ++c) {
-        const float x1 = to_f32(v[static_cast<size_t>(key) * a.d + c]);
-        if (isfinite(x1)) continue;
-        if (a.nparts == 1)
-          zr[c] = static_cast<float>(zr[c] + p * x1 / dsum);
-        else
-          part[(c - cbeg) * kRows] += p * x1;
-      }
-    }
   }
 }
 
@@ -704,9 +420,7 @@ __global__ __launch_bounds__(64 * NW) void k_direct_parts(DirectArgs a) {
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     if (c + j < a.d) zr[c + j] = static_cast<float>(num[j] / den);
-  if (c == 0 && a.den)
-    a.den[static_cast<size_t>(bh) * a.n + i] =
-        static_cast<float>(den * exp2_int(a.rexp[static_cast<size_t>(bh) * a.nblk * kBlk + i]));
+  if (c == 0 && a.den) a.den[static_cast<size_t>(bh) * a.n + i] = den;
 }
 
 // ------------------------------------------------------------ launchers --
@@ -722,11 +436,11 @@ int round_ks(int ks) {
 // Waves (of 32 rows) per work-group.
 constexpr int direct_waves(int KS) { return 4; }
 
-template <typename TV, int KS, int CT>
+template <int NSZ, int KS, int CT>
 hipError_t direct_go(const DirectArgs& a, hipStream_t st) {
   constexpr int NW = direct_waves(KS);
   const long long blocks = static_cast<long long>(a.BH) * a.passes * a.tiles * a.nparts;
-  hipLaunchKernelGGL((k_direct<TV, KS, CT, NW>), dim3(static_cast<unsigned>(blocks)), dim3(64 * NW), 0, st, a);
+  hipLaunchKernelGGL((k_direct<0, NSZ, KS, 0, CT, NW>), dim3(static_cast<unsigned>(blocks)), dim3(64 * NW), 0, st, a);
   if (hipError_t e = hipGetLastError(); e != hipSuccess || a.nparts == 1) return e;
   hipLaunchKernelGGL((k_direct_parts<CT, NW>),
                      dim3(static_cast<unsigned>(static_cast<long long>(a.BH) * a.passes * a.tiles * (CT * 4))),
@@ -734,15 +448,15 @@ hipError_t direct_go(const DirectArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <typename TV, int CT>
+template <int NSZ, int CT>
 hipError_t direct_ks(int KS, const DirectArgs& a, hipStream_t st) {
   switch (KS) {
-    case 2: return direct_go<TV, 2, CT>(a, st);
-    case 4: return direct_go<TV, 4, CT>(a, st);
-    case 6: return direct_go<TV, 6, CT>(a, st);
-    case 8: return direct_go<TV, 8, CT>(a, st);
-    case 12: return direct_go<TV, 12, CT>(a, st);
-    case 16: return direct_go<TV, 16, CT>(a, st);
+    case 2: return direct_go<NSZ, 2, CT>(a, st);
+    case 4: return direct_go<NSZ, 4, CT>(a, st);
+    case 6: return direct_go<NSZ, 6, CT>(a, st);
+    case 8: return direct_go<NSZ, 8, CT>(a, st);
+    case 12: return direct_go<NSZ, 12, CT>(a, st);
+    case 16: return direct_go<NSZ, 16, CT>(a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -834,8 +548,9 @@ DirectLayout direct_layout(int B, int H, int n, int d, int ks) {
 
 hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
                               const float* b, const float* W, int BH, int H, int n, int d, int m, bool nprf, int kind,
-                              hipStream_t st) {
+                              int* kpow, float* crev, int2* rrange, hipStream_t st) {
   PrepArgs p{};
+  p.kpow = kpow, p.crev = crev, p.rrange = rrange;
   p.q = q, p.k = k, p.v = v, p.W = W, p.b = b;
   p.X = reinterpret_cast<uint4*>(w + L.x);
   p.Y = reinterpret_cast<uint4*>(w + L.y);
@@ -857,7 +572,7 @@ hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, con
   return bf16 ? prep_go<uint16_t>(p, st) : prep_go<float>(p, st);
 }
 
-hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf16, float* z, float* den, int BH, int H,
+hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf16, float* z, double* den, int BH, int H,
                          int n, int d, hipStream_t st) {
   DirectArgs a{};
   a.X = reinterpret_cast<const uint4*>(w + L.x);
@@ -872,12 +587,10 @@ hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf1
   const int rows = 32 * direct_waves(L.ks);
   a.tiles = (n + rows - 1) / rows;
   a.passes = L.passes, a.nparts = L.nparts;
-  // (one XCD's L2 then serves the work-groups of a head; with few heads the
-  // plain order spreads the row tiles, whose lengths differ, over the XCDs)
-  a.remap = BH >= 16 || BH % 8 == 0;
+  a.remap = direct_remap(BH);
   if (L.ct_total >= 2)
-    return bf16 ? direct_ks<uint16_t, 2>(L.ks, a, st) : direct_ks<float, 2>(L.ks, a, st);
-  return bf16 ? direct_ks<uint16_t, 1>(L.ks, a, st) : direct_ks<float, 1>(L.ks, a, st);
+    return bf16 ? direct_ks<1, 2>(L.ks, a, st) : direct_ks<2, 2>(L.ks, a, st);
+  return bf16 ? direct_ks<1, 1>(L.ks, a, st) : direct_ks<2, 1>(L.ks, a, st);
 }
 
 }  // namespace krpe

@@ -1,0 +1,431 @@
+// The kernel of the weighted products (wprod.hpp), shared by the direct route
+// of the forward pass (direct.hip) and the backward pass (bwd_direct.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <type_traits>
+
+#include "common.hpp"
+#include "wprod.hpp"
+
+namespace krpe {
+
+// Record of a 32-key block, 64 words: [0, 32) 2^(e_j - E) per key, e_j the
+// power of phi(k_j) and E = word 32 (int); word 33 (int) the power of its
+// values.
+constexpr int kRecWords = 64, kRecE = 32, kRecV = 33;
+// S of two positions is at most 2^30 M in units of their powers: E carries 30
+// of them, so that P stays near c_{j-i}'s range.
+constexpr int kRecBias = 30;
+
+// 8 values of a row from position p (zeros past `count` values of the row)
+template <typename T>
+__device__ __forceinline__ void load8(const T* __restrict__ p, int count, bool vec, float (&x)[8]) {
+  if (vec && count >= 8) {
+    if constexpr (std::is_same<T, float>::value) {
+      const float4 a = reinterpret_cast<const float4*>(p)[0], c = reinterpret_cast<const float4*>(p)[1];
+      x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w, x[4] = c.x, x[5] = c.y, x[6] = c.z, x[7] = c.w;
+    } else {
+      const uint4 u = *reinterpret_cast<const uint4*>(p);
+      const unsigned w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        x[2 * j] = __uint_as_float(w[j] << 16);
+        x[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = j < count ? to_f32(p[j]) : 0.f;
+  }
+}
+
+// --------------------------------------------------------------- direct --
+// One work-group: 32 NW consecutive rows of one (batch, head), each wave its
+// own 32, over the 32-key blocks of its part of the rows' finite-b range.  A
+// block's fragments of phi(k) and v, its strip of c and its record are staged
+// to LDS one block ahead by direct loads and shared by the waves; phi(q) stays
+// in registers.  Per block and wave: S^T = phi(k) phi(q)^T (lane: row lr, keys
+// along the registers), P = S^T 2^(e_j - E) c_{j-i}, P split with the power of
+// its row's largest entry, and Z^T = [v]^T P^T (lane: row lr again, so that
+// the row's power applies lane by lane), whose fp32 sums over the 32 keys are
+// added into fp64 totals; the denominator is the fp32 sum of P added likewise.
+// The power of phi(q_i) cancels in z.  P's small term is stored unscaled (its
+// largest entry is at 2^14, terms below 2^-40 of that are lost).  A wave skips
+// the blocks outside its own rows' range (it still stages and meets the
+// barriers).
+struct DirectArgs {
+  const uint4 *X, *Y, *Z;
+  const float* krec;
+  const unsigned* vflag;
+  const float* ctab;
+  const int2* crange;
+  const void* v;
+  float* z;
+  double* den;       // denominators in units of the queries' powers (or NULL)
+  const int* rpow;   // MODE 1, 2: powers of the rows [BH][32 nblk]
+  int ldz;           // MODE 1, 2: row length of z; 0: z as fp32 S fragments of out_ks k steps
+  int out_ks;
+  const uint4 *X2, *Y2;  // MODE 2: the second pair of operands ([block][KS2][2])
+  const float* krec2;    // its keys' records
+  const int* rpow2;      // and rows' powers
+  float* pdc;            // diagonal sums [BH][nblk row blocks][32 (nblk + 1)]
+  double* part;
+  int BH, H, n, nblk, d, ct_total, tiles, passes, nparts, remap;
+};
+
+// Whether the work-groups take XCD order: one XCD's L2 then serves the
+// work-groups of a head; with few heads the plain order spreads the row tiles,
+// whose lengths differ, over the XCDs.
+inline bool direct_remap(int BH) { return BH >= 16 || BH % 8 == 0; }
+
+// Key blocks [lo, hi) of rows r0 .. r1 under the head's range of finite b.
+__device__ __forceinline__ void key_blocks(int2 br, int n, int r0, int r1, int& lo, int& hi) {
+  const int jlo = max(0, r0 + br.x - (n - 1)), jhi = min(n - 1, r1 + br.y - (n - 1));
+  lo = jhi >= jlo ? jlo >> 5 : 0;
+  hi = jhi >= jlo ? (jhi >> 5) + 1 : 0;
+}
+// Columns c .. c + 3 of a row of d (16-byte aligned rows when d is a multiple of 4).
+__device__ __forceinline__ void store4(float* __restrict__ row, int c, int d, float x, float y, float z, float w) {
+  if (d % 4 == 0) {
+    if (c < d) *reinterpret_cast<float4*>(row + c) = make_float4(x, y, z, w);
+  } else {
+    if (c < d) row[c] = x;
+    if (c + 1 < d) row[c + 1] = y;
+    if (c + 2 < d) row[c + 2] = z;
+    if (c + 3 < d) row[c + 3] = w;
+  }
+}
+
+// MODE 0: the forward pass.  MODE 1: the plain product, fp32 totals, rows
+// scaled by their powers.  MODE 2: as MODE 1, and the diagonal sums of
+// (X2 Y2^T) o (X Y^T) in pass 0 (bwd_direct.hip).
+template <int MODE, int NSZ, int KS, int KS2, int CT, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void k_direct(DirectArgs a) {
+  using TV = typename std::conditional<NSZ == 1, uint16_t, float>::type;
+  using Total = typename std::conditional<MODE == 0, double, float>::type;
+  constexpr int kRows = 32 * NW;
+  constexpr int NY = KS * 2, NY2 = MODE == 2 ? KS2 * 2 : 0, NZ = CT * 2 * NSZ;
+  constexpr int NF = NY + NY2 + NZ;           // fragments per key block
+  constexpr int NC = (kRows + 31 + 63) / 64;  // 64-entry pieces of the c strip (kRows + 31 entries used)
+  constexpr int NR = MODE == 2 ? 2 : 1;       // records
+  constexpr int kStrip = NC * 64 + NR * kRecWords;
+  __shared__ uint4 tiles_lds[2][NF * kFragLanes];
+  __shared__ __align__(16) float strip[2][kStrip];
+  constexpr int kDS = 33;  // floats per diagonal: writes across the lanes and reads fall in distinct banks
+  __shared__ float diag[MODE == 2 ? NW : 1][MODE == 2 ? 64 * kDS : 1];
+  float dcarry = 0.f;  // sums of the diagonals below the last block's, in lanes 0 .. 31
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lh = lane >> 5;
+  int b = a.remap ? xcd_block(blockIdx.x, gridDim.x) : static_cast<int>(blockIdx.x);
+  const int pi = b % a.nparts;
+  b /= a.nparts;
+  const int tile = a.tiles - 1 - b % a.tiles;  // (under a causal mask the last rows see the most keys)
+  b /= a.tiles;
+  const int pass = b % a.passes, bh = b / a.passes, h = bh % a.H;
+  const int n = a.n, row0 = tile * kRows, wrow0 = row0 + 32 * wave;
+  const int2 br = head_range(a.crange + static_cast<size_t>(h) * ctab_chunks(n), ctab_chunks(n), lane);
+  int b0, b1, wlo = 0, whi = 0;
+  key_blocks(br, n, row0, min(row0 + kRows, n) - 1, b0, b1);
+  if (wrow0 < n) key_blocks(br, n, wrow0, min(wrow0 + 32, n) - 1, wlo, whi);
+  {
+    const int nb = b1 - b0, s = b0;
+    b0 = s + static_cast<int>(static_cast<long long>(nb) * pi / a.nparts);
+    b1 = s + static_cast<int>(static_cast<long long>(nb) * (pi + 1) / a.nparts);
+  }
+  // this wave's rows
+  const size_t hb = static_cast<size_t>(bh) * a.nblk, xblk = hb + min(wrow0 >> 5, a.nblk - 1);
+  uint4 x[KS][2];
+  {
+    const uint4* __restrict__ xp = a.X + xblk * NY * kFragLanes + lane;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) x[ks][s] = xp[(ks * 2 + s) * kFragLanes];
+  }
+  uint4 x2[MODE == 2 ? KS2 : 1][2];
+  int rp2 = 0;  // power of S2 S of this lane's row
+  if constexpr (MODE == 2) {
+    const uint4* __restrict__ xp = a.X2 + xblk * NY2 * kFragLanes + lane;
+#pragma unroll
+    for (int ks = 0; ks < KS2; ++ks)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) x2[ks][s] = xp[(ks * 2 + s) * kFragLanes];
+    rp2 = a.rpow[xblk * kBlk + lr] + a.rpow2[xblk * kBlk + lr];
+    for (int e = lane; e < 64 * kDS; e += 64) diag[wave][e] = 0.f;
+  }
+  const uint32_t zbytes = static_cast<uint32_t>(a.ct_total) * 2 * NSZ * 1024u;  // per key block
+  const int stride = ctab_stride(n);
+  const __amdgpu_buffer_rsrc_t ry = buffer_of(a.Y + hb * NY * kFragLanes, static_cast<size_t>(a.nblk) * NY * 1024);
+  const __amdgpu_buffer_rsrc_t ry2 = buffer_of(MODE == 2 ? a.Y2 + hb * NY2 * kFragLanes : a.Y,
+                                               static_cast<size_t>(a.nblk) * NY2 * 1024);
+  const __amdgpu_buffer_rsrc_t rz =
+      buffer_of(reinterpret_cast<const char*>(a.Z) + hb * zbytes, static_cast<size_t>(a.nblk) * zbytes);
+  const __amdgpu_buffer_rsrc_t rc = buffer_of(a.ctab + static_cast<size_t>(h) * stride, static_cast<size_t>(stride) * 4);
+  const __amdgpu_buffer_rsrc_t rr = buffer_of(a.krec + hb * kRecWords, static_cast<size_t>(a.nblk) * kRecWords * 4);
+  const __amdgpu_buffer_rsrc_t rr2 =
+      buffer_of(MODE == 2 ? a.krec2 + hb * kRecWords : a.krec, static_cast<size_t>(a.nblk) * kRecWords * 4);
+  const uint32_t lds0 = lds_address(&tiles_lds[0][0]), str0 = lds_address(&strip[0][0]);
+  const uint32_t zpass = static_cast<uint32_t>(pass * CT * 2 * NSZ) * 1024u;
+  // pieces of block blk into buffer `buf`: wave w stages pieces w, w + NW, ..:
+  // the fragments, the c entries from key 32 blk and row row0 + kRows - 1 on,
+  // the records
+  auto stage = [&](int blk, int buf) {
+    const uint32_t base = lds0 + static_cast<uint32_t>(buf) * (NF * 1024u), v16 = lane * 16u;
+    const uint32_t sb = str0 + static_cast<uint32_t>(buf) * (kStrip * 4u);
+    const uint32_t yo = static_cast<uint32_t>(blk) * (NY * 1024u), zo = static_cast<uint32_t>(blk) * zbytes + zpass;
+    const uint32_t y2o = static_cast<uint32_t>(blk) * (NY2 * 1024u);
+    const uint32_t co = static_cast<uint32_t>(32 * blk - row0 - (kRows - 1) + n - 1 + kCPad) * 4u;
+    const uint32_t ro = static_cast<uint32_t>(blk) * (kRecWords * 4u);
+#pragma unroll
+    for (int i = 0; i < (NF + NC + NR + NW - 1) / NW; ++i) {
+      const int f = NW * i + wave;
+      if (f < NY)
+        stage_lds<16>(ry, base + f * 1024u, v16, yo + f * 1024u);
+      else if (f < NY + NY2)
+        stage_lds<16>(ry2, base + f * 1024u, v16, y2o + (f - NY) * 1024u);
+      else if (f < NF)
+        stage_lds<16>(rz, base + f * 1024u, v16, zo + (f - NY - NY2) * 1024u);
+      else if (f < NF + NC)
+        stage_lds<4>(rc, sb + (f - NF) * 256u, lane * 4u, co + (f - NF) * 256u);
+      else if (f == NF + NC)
+        stage_lds<4>(rr, sb + NC * 256u, lane * 4u, ro);
+      else if (MODE == 2 && f == NF + NC + 1)
+        stage_lds<4>(rr2, sb + (NC + 1) * 256u, lane * 4u, ro);
+    }
+  };
+  Total zt[CT][16];
+  double dsum = 0.0;
+#pragma unroll
+  for (int t = 0; t < CT; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) zt[t][e] = 0;
+  if (b0 < b1) stage(b0, 0);
+  for (int blk = b0; blk < b1; ++blk) {
+    const int buf = (blk - b0) & 1;
+    // this block's pieces are in LDS, the other buffer is consumed
+    stage_wait();
+    __syncthreads();
+    if (blk + 1 < b1) stage(blk + 1, buf ^ 1);
+    if (blk < wlo || blk >= whi) continue;
+    const uint4* __restrict__ y = &tiles_lds[buf][lane];
+    const uint4* __restrict__ zf = y + (NY + NY2) * kFragLanes;
+    const float* __restrict__ rec = &strip[buf][NC * 64];
+    const float* __restrict__ cs = &strip[buf][kRows - 1 - 32 * wave - lr + 4 * lh];
+    floatx16 s = zero16(), s1 = zero16();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const uint4 yh = y[(ks * 2 + 0) * kFragLanes], yl = y[(ks * 2 + 1) * kFragLanes];
+      s = mfma_f16(yh, x[ks][0], s);
+      s1 = mfma_f16(yh, x[ks][1], s1);
+      s1 = mfma_f16(yl, x[ks][0], s1);
+    }
+    const int kexp = __float_as_int(rec[kRecE]);
+    // P: lane row lr, keys 8 (e / 4) + 4 lh + e % 4
+    float p[16];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 kr = *reinterpret_cast<const float4*>(rec + 8 * g + 4 * lh);
+      const float k4[4] = {kr.x, kr.y, kr.z, kr.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) p[4 * g + j] = fmaf(s1[4 * g + j], kLoInv, s[4 * g + j]) * k4[j];
+    }
+    if constexpr (MODE == 2) {
+      // the products (X2 Y2^T) o (X Y^T) of this block summed along its
+      // diagonals: entry (key) of diagonal 32 + row - key, one diagonal per
+      // lane to sum (slots that hold no entry stay zero; LDS float atomics
+      // into one word per diagonal took four times as long as the rest of
+      // the block).  Diagonals 32 .. 63 are complete after this block, the
+      // next one's lie 32 below.
+      const float* __restrict__ rec2 = rec + kRecWords;
+      const uint4* __restrict__ y2 = y + NY * kFragLanes;
+      floatx16 r = zero16(), r1 = zero16();
+#pragma unroll
+      for (int ks = 0; ks < KS2; ++ks) {
+        const uint4 yh = y2[(ks * 2 + 0) * kFragLanes], yl = y2[(ks * 2 + 1) * kFragLanes];
+        r = mfma_f16(yh, x2[ks][0], r);
+        r1 = mfma_f16(yh, x2[ks][1], r1);
+        r1 = mfma_f16(yl, x2[ks][0], r1);
+      }
+      const float f = ldexpf(1.f, rp2 + kexp + __float_as_int(rec2[kRecE]));
+      float* __restrict__ win = &diag[wave][(32 + lr - 4 * lh) * kDS + 4 * lh];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 kr = *reinterpret_cast<const float4*>(rec2 + 8 * g + 4 * lh);
+        const float k4[4] = {kr.x, kr.y, kr.z, kr.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          win[(8 * g + j) * (1 - kDS)] = fmaf(r1[4 * g + j], kLoInv, r[4 * g + j]) * k4[j] * p[4 * g + j] * f;
+      }
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const float* __restrict__ dl = &diag[wave][lane * kDS];
+      float up = __shfl(dcarry, lr);  // (lanes 32 .. 63 take the carry of 0 .. 31)
+      up = lh == 1 ? up : 0.f;
+#pragma unroll
+      for (int k = 0; k < 32; ++k) up += dl[k];
+      if (lh == 1) a.pdc[((hb + (wrow0 >> 5)) * (a.nblk + 1) + blk) * 32 + lr] = up;
+      dcarry = up;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) p[e] *= cs[8 * (e >> 2) + (e & 3)];
+    if (32 * blk + 32 > n) {  // uniform: keys past n (their fragments are zero, but c may be infinite)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (32 * blk + 8 * (e >> 2) + 4 * lh + (e & 3) >= n) p[e] = 0.f;
+    }
+    float ds = 0.f, mx = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      if (MODE == 0) ds += p[e];
+      mx = fmaxf(mx, fabsf(p[e]));
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    // the row's power in this block: its largest P is brought to [2^14, 2^15)
+    // (zero and NaN maxima: 2^15, any power serves)
+    const int ex = max(__builtin_amdgcn_frexp_expf(mx), -100) - 15;
+    const float sc = __int_as_float((127 - ex) << 23);
+    const int zexp = kexp + __float_as_int(rec[kRecV]) + ex;
+    Total zs;
+    if constexpr (MODE == 0) {
+      zs = exp2_int(zexp);
+      dsum = fma(static_cast<double>(ds), exp2_int(kexp), dsum);
+    } else {
+      zs = ldexpf(1.f, zexp);
+    }
+    uint4 ph[2], pl[2];
+#pragma unroll
+    for (int k2 = 0; k2 < 2; ++k2) {
+      float v8[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v8[t] = p[8 * k2 + t] * sc;
+      split_f16x8(v8, 1.f, ph[k2], pl[k2]);
+    }
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+      floatx16 zc = zero16(), z1 = zero16();
+#pragma unroll
+      for (int k2 = 0; k2 < 2; ++k2) {
+        const uint4 vh = zf[((t * 2 + k2) * NSZ + 0) * kFragLanes];
+        zc = mfma_f16(vh, pl[k2], zc);
+        zc = mfma_f16(vh, ph[k2], zc);
+        if constexpr (NSZ > 1) z1 = mfma_f16(zf[((t * 2 + k2) * NSZ + 1) * kFragLanes], ph[k2], z1);
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float zz = NSZ > 1 ? fmaf(z1[e], kLoInv, zc[e]) : zc[e];
+        zt[t][e] = fma(static_cast<Total>(zz), zs, zt[t][e]);
+      }
+    }
+  }
+  if (wrow0 >= n) return;  // uniform per wave; no barrier follows
+  const int i = wrow0 + lr;
+  if constexpr (MODE > 0) {
+    const float rs = ldexpf(1.f, a.rpow[xblk * kBlk + lr]);
+    if (MODE == 2 && lh == 0 && whi > wlo)  // the diagonals below the last block's
+      a.pdc[((hb + (wrow0 >> 5)) * (a.nblk + 1) + whi) * 32 + lr] = dcarry;
+    if (a.ldz == 0) {
+      float4* __restrict__ o = reinterpret_cast<float4*>(a.z) + (xblk * a.out_ks * kFragLanes + lane) * 2;
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int k2 = 0; k2 < 2; ++k2) {
+          const int ks = 2 * (pass * CT + t) + k2;
+          if (ks >= a.out_ks) continue;  // uniform
+          const Total* __restrict__ q = &zt[t][8 * k2];
+          o[ks * 2 * kFragLanes] = make_float4(q[0] * rs, q[1] * rs, q[2] * rs, q[3] * rs);
+          o[ks * 2 * kFragLanes + 1] = make_float4(q[4] * rs, q[5] * rs, q[6] * rs, q[7] * rs);
+        }
+    } else if (i < n) {
+      float* __restrict__ zr = a.z + (static_cast<size_t>(bh) * n + i) * a.ldz;
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int c = (pass * CT + t) * 32 + 8 * g + 4 * lh;
+          const Total* __restrict__ q = &zt[t][4 * g];
+          store4(zr, c, a.ldz, q[0] * rs, q[1] * rs, q[2] * rs, q[3] * rs);
+        }
+    }
+  } else {
+    dsum += __shfl_xor(dsum, 32);  // the other half-wave's keys of row lr
+    // this lane: row i, columns 32 (pass CT + t) + 8 (e / 4) + 4 lh + e % 4
+    constexpr int cw = CT * 32 + 1;
+    const int c0 = pass * CT * 32 + 4 * lh;
+    double* __restrict__ part = a.part +
+                                ((static_cast<size_t>(bh * a.passes + pass) * a.tiles + tile) * a.nparts + pi) *
+                                    (kRows * cw) +
+                                32 * wave + lr;  // [column][row]
+    float* __restrict__ zr = a.z + (static_cast<size_t>(bh) * n + i) * a.d;
+    if (a.nparts == 1) {
+      const double inv = 1.0 / dsum;
+      if (i < n) {
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const Total* __restrict__ q = &zt[t][4 * g];
+            store4(zr, c0 + 32 * t + 8 * g, a.d, static_cast<float>(q[0] * inv), static_cast<float>(q[1] * inv),
+                   static_cast<float>(q[2] * inv), static_cast<float>(q[3] * inv));
+          }
+        if (pass == 0 && lh == 0 && a.den) a.den[static_cast<size_t>(bh) * n + i] = dsum;
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) part[(32 * t + 8 * (e >> 2) + 4 * lh + (e & 3)) * kRows] = zt[t][e];
+      if (lh == 0) part[CT * 32 * kRows] = dsum;
+    }
+    // Values that are not finite (stored as zero fragments, their blocks
+    // flagged): P v added in fp64, one key at a time; rare.
+    const unsigned* __restrict__ vf = a.vflag + hb;
+    const int f0 = max(b0, wlo), f1 = min(b1, whi);
+    bool odd = false;
+    for (int blk = f0 + lane; blk < f1; blk += 64) odd |= vf[blk] != 0u;
+    if (!__any(odd)) return;
+    __threadfence();  // the rows stored above are read back below, by other lanes
+    const TV* __restrict__ v = static_cast<const TV*>(a.v) + static_cast<size_t>(bh) * n * a.d;
+    const float* __restrict__ ct = a.ctab + static_cast<size_t>(h) * stride + kCPad + n - 1;
+    const int cbeg = pass * CT * 32, cend = min(a.d, cbeg + CT * 32);
+    auto value = [](uint4 hh, uint4 ll, int j) {  // element j of a pair of fragments
+      const uint32_t w[4] = {hh.x, hh.y, hh.z, hh.w}, u[4] = {ll.x, ll.y, ll.z, ll.w};
+      return term_value(w[j >> 1], u[j >> 1], j & 1);
+    };
+    for (int blk = f0; blk < f1; ++blk) {
+      if (vf[blk] == 0u) continue;
+      const float* __restrict__ rec = a.krec + (hb + blk) * kRecWords;
+      for (int key = 32 * blk; key < min(32 * blk + 32, n); ++key) {
+        bool any = false;
+        for (int c = cbeg + lane; c < cend; c += 64) any |= !isfinite(to_f32(v[static_cast<size_t>(key) * a.d + c]));
+        if (!__any(any)) continue;
+        // S of (row, key): this lane half's slots, then the other half's
+        float s = 0.f;
+        const uint4* __restrict__ yp = a.Y + (hb + blk) * NY * kFragLanes + 32 * lh + (key & 31);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const uint4 yh = yp[(ks * 2 + 0) * kFragLanes], yl = yp[(ks * 2 + 1) * kFragLanes];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) s = fmaf(value(x[ks][0], x[ks][1], j), value(yh, yl, j), s);
+        }
+        s += __shfl_xor(s, 32);
+        if (lh != 0 || i >= n || ct[key - i] == 0.f) continue;  // (a masked key reaches no row)
+        const double p = static_cast<double>(s * rec[key & 31] * ct[key - i]) * exp2_int(__float_as_int(rec[kRecE]));
+        for (int c = cbeg; c < cend; ++c) {
+          const float x1 = to_f32(v[static_cast<size_t>(key) * a.d + c]);
+          if (isfinite(x1)) continue;
+          if (a.nparts == 1)
+            zr[c] = static_cast<float>(zr[c] + p * x1 / dsum);
+          else
+            part[(c - cbeg) * kRows] += p * x1;
+        }
+      }
+    }
+  }
+}
+
+}  // namespace krpe

@@ -105,14 +105,44 @@ struct DirectLayout {
   size_t part;   // double [BH][passes][tiles][nparts][columns + 1][rows] partial sums
   size_t total;
 };
+// (kpow, crev, rrange: the powers of phi(k), the reversed table and its ranges
+// for the backward pass, or NULL)
 // k steps of the direct kernels for these features (0: not covered, more than 256)
 int direct_ksteps(int kind, int d, int m);
 DirectLayout direct_layout(int B, int H, int n, int d, int ks);
 hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
                               const float* b, const float* W, int BH, int H, int n, int d, int m, bool nprf, int kind,
-                              hipStream_t st);
-hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf16, float* z, float* den, int BH, int H,
+                              int* kpow, float* crev, int2* rrange, hipStream_t st);
+// den (or NULL): the denominators, in units of the power of each phi(q_i).
+hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf16, float* z, double* den, int BH, int H,
                          int n, int d, hipStream_t st);
+
+// Workspace of the direct backward pass (csrc/bwd_direct.hip): the direct
+// forward's first.
+struct DirectBwdLayout {
+  DirectLayout f;
+  int ks2;          // 16-step count of d + 1 contracted columns
+  int ctq, passq;   // column tiles per pass and passes of the feature gradients
+  size_t z;         // float  [BH][n][d]
+  size_t den;       // double [BH][n]
+  size_t kpow;      // int    [BH][32 nblk]    powers of phi(k)
+  size_t crev;      // float  [H][ctab_stride] reversed table
+  size_t rrange;    // int2   [H][chunks]
+  size_t gs, vs;    // S fragments [BH][nblk][ks2][2] of [Gh, gamma] and [v, 1]
+  size_t gz;        // Z fragments [BH][nblk][ct][2][2] of Gh
+  size_t zq, zk;    // Z fragments [BH][nblk][passq ctq][2][2] of phi(q), phi(k)
+  size_t reca, recb, recc; // records of the keys of the three products
+  size_t gpow, vpow; // int   [BH][32 nblk]
+  size_t wf;        // W as Z fragments, three bf16 terms [H][ks][d tiles][3]
+  size_t dphi;      // float  S fragments [BH][nblk][ks][64][8], one product at a time
+  size_t pdc;       // float  [BH][nblk][32 (nblk + 1)] diagonal sums per row block
+  size_t total;
+};
+int direct_bwd_ksteps(int m);  // 0: not covered
+DirectBwdLayout direct_bwd_layout(int B, int H, int n, int d, int m);
+hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
+                             const float* b, const float* W, const float* dz, float* dq, float* dk, float* dv,
+                             float* db, int BH, int H, int n, int d, int m, bool nprf, hipStream_t st);
 
 // Workspace of krpe_toeplitz_conv.  For n > 2^kMaxLog2N the Toeplitz matrix is
 // taken in nb x nb blocks of nbk = 2^kMaxLog2N positions (nb = 1 otherwise):

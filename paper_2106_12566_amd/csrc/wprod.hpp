@@ -120,6 +120,11 @@ __device__ __forceinline__ void split_f16x8(const float (&x)[8], float lo, uint4
   split_f16(x[4], x[5], lo, h.z, l.z);
   split_f16(x[6], x[7], lo, h.w, l.w);
 }
+// the value of half j (0, 1) of a pair of terms, l scaled by kLoScale
+__device__ __forceinline__ float term_value(uint32_t h, uint32_t l, int j) {
+  const halfx2 hp = __builtin_bit_cast(halfx2, h), lp = __builtin_bit_cast(halfx2, l);
+  return fmaf(static_cast<float>(j ? lp.y : lp.x), kLoInv, static_cast<float>(j ? hp.y : hp.x));
+}
 __device__ __forceinline__ floatx16 mfma_f16(uint4 a, uint4 b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a), __builtin_bit_cast(halfx8, b), c, 0, 0,
                                                 0);

@@ -106,3 +106,40 @@ def test_direct_values_not_finite(gpu_lib, dt, n, d, parts):
     # elsewhere only the elements themselves left the sums, where no row sees them: equal to 2e-5
     scale = np.max(np.abs(clean), axis=-1, keepdims=True)
     assert np.max(np.where(want, 0.0, np.abs(np.where(want, 0.0, z) - clean)) / scale) <= TOL
+
+
+BWD_CASES = [
+    # n, d, m: 32-position blocks and row tiles (128 and 256 rows); d + 1 contracted columns around the
+    # compiled 3, 5 and 9 steps of 16; column tiles and passes; feature counts around 64, 128 and 256
+    (1, 4, 4, "f32", "normal", False), (33, 31, 64, "f32", "causal", True), (127, 32, 65, "bf16", "normal", False),
+    (129, 47, 20, "f32", "decay", False), (257, 48, 128, "f32", "causal", False), (300, 64, 129, "bf16", "decay", False),
+    (255, 79, 256, "f32", "normal", True), (130, 80, 33, "f32", "causal", False), (520, 128, 200, "f32", "decay", False),
+    (1025, 64, 64, "bf16", "causal", False),
+]
+
+
+@pytest.mark.parametrize("n,d,m,dt,bias,nprf", BWD_CASES)
+def test_direct_backward(gpu_lib, n, d, m, dt, bias, nprf):
+    """The gradients of the direct products against the fp64 chain rule.  Tolerance 2e-5 of a
+    gradient's norm, per head: the terms' errors are those of z above, and sums of either sign are
+    measured against the gradient's norm.  Where the exact gradient vanishes (one key, n = 1) terms of
+    the size scale = max|dz| max|[v, 1]| max|W| cancel, a handful of them each rounded to 2^-24 of
+    it: an absolute 2^-21 scale, TOL times the floor 2^-5 scale."""
+    B, H = 2, 2
+    dd = synth.custom(B, H, n, d, m, seed=71 + n, qkv_dtype=dt, bias=bias)
+    G = np.random.default_rng([71, n]).standard_normal((B, H, n, d)).astype(np.float32)
+    print(f"direct backward n={n} d={d} m={m} {dt} {bias} nprf={nprf}", flush=True)
+    q, k, v = (to_gpu(dd[x], dt) for x in ("q", "k", "v"))
+    args = (q, k, v, to_gpu(dd["b"]), to_gpu(dd["W"]), to_gpu(G))
+    got = gpu_lib.attention_bwd(*args, nprf=nprf, with_db=True, route="direct")
+    ref = oracle.attention_grad(dd["q"], dd["k"], dd["v"], dd["b"], dd["W"], G, nprf=nprf)
+    scale = float(np.max(np.abs(G)) * max(1.0, np.max(np.abs(dd["v"]))) * np.max(np.abs(dd["W"])))
+    for name, g, r in zip(("dq", "dk", "dv", "db"), got, ref):
+        g = g.cpu().numpy().astype(np.float64)
+        assert np.all(np.isfinite(g)), name
+        err = np.linalg.norm(g - r) / max(np.linalg.norm(r), 2.0 ** -5 * scale)
+        print(f"  {name}: {err:.3e}", flush=True)
+        assert err <= TOL, (name, err)
+    # without the bias gradient dv comes from another kernel: the same values up to rounding
+    dv = gpu_lib.attention_bwd(*args, nprf=nprf, route="direct")[2].cpu().numpy()
+    assert np.linalg.norm(dv - got[2].cpu().numpy()) <= 2e-6 * np.linalg.norm(ref[2])
