@@ -99,6 +99,63 @@ __device__ __forceinline__ void store4(float* __restrict__ row, int c, int d, fl
   }
 }
 
+// Has the loads of x complete here: a first use inside the loop would wait
+// there, every time, for all outstanding loads, the staged ones too.
+template <int N>
+__device__ __forceinline__ void keep(uint4 (&x)[N][2]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) asm volatile("" : "+v"(x[i][s].x), "+v"(x[i][s].y), "+v"(x[i][s].z), "+v"(x[i][s].w));
+}
+
+// s + s1 / kLoScale = Y X^T over KS k steps: Y's fragments are read from LDS
+// two steps ahead of their products, up to 8 steps (beyond, X leaves no
+// registers for it: at 16 steps it spills, 3.9 -> 5.6 ms at n = 16384).
+constexpr int kAheadSteps = 8;
+template <int KS>
+__device__ __forceinline__ void s_product(const uint4* __restrict__ y, const uint4 (&x)[KS][2], floatx16& s, floatx16& s1) {
+  s = zero16();
+  s1 = zero16();
+  if constexpr (KS > kAheadSteps) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const uint4 yh = y[(ks * 2 + 0) * kFragLanes], yl = y[(ks * 2 + 1) * kFragLanes];
+      s = mfma_f16(yh, x[ks][0], s);
+      s1 = mfma_f16(yh, x[ks][1], s1);
+      s1 = mfma_f16(yl, x[ks][0], s1);
+    }
+    return;
+  }
+  uint4 yb[3][2];
+#pragma unroll
+  for (int ks = 0; ks < 2 && ks < KS; ++ks)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) yb[ks][i] = y[(ks * 2 + i) * kFragLanes];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    if (ks + 2 < KS) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) yb[(ks + 2) % 3][i] = y[((ks + 2) * 2 + i) * kFragLanes];
+    }
+    s = mfma_f16(yb[ks % 3][0], x[ks][0], s);
+    s1 = mfma_f16(yb[ks % 3][0], x[ks][1], s1);
+    s1 = mfma_f16(yb[ks % 3][1], x[ks][0], s1);
+  }
+}
+// The order of s_product's reads and products (one scheduling region): kDs LDS
+// reads, the products of a step, and so on, with room for the reads of later
+// phases.
+constexpr int kSchedMfma = 0x8, kSchedDsRead = 0x100;
+template <int KS>
+__device__ __forceinline__ void s_schedule() {
+  __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 4, 0);
+  constexpr_for<KS>([&](auto) {
+    __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 4, 0);
+    __builtin_amdgcn_sched_group_barrier(kSchedMfma, 3, 0);
+  });
+}
+
 // MODE 0: the forward pass.  MODE 1: the plain product, fp32 totals, rows
 // scaled by their powers.  MODE 2: as MODE 1, and the diagonal sums of
 // (X2 Y2^T) o (X Y^T) in pass 0 (bwd_direct.hip).
@@ -144,6 +201,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
       for (int s = 0; s < 2; ++s) x[ks][s] = xp[(ks * 2 + s) * kFragLanes];
+    keep(x);
   }
   uint4 x2[MODE == 2 ? KS2 : 1][2];
   int rp2 = 0;  // power of S2 S of this lane's row
@@ -153,6 +211,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int ks = 0; ks < KS2; ++ks)
 #pragma unroll
       for (int s = 0; s < 2; ++s) x2[ks][s] = xp[(ks * 2 + s) * kFragLanes];
+    keep(x2);
     rp2 = a.rpow[xblk * kBlk + lr] + a.rpow2[xblk * kBlk + lr];
     for (int e = lane; e < 64 * kDS; e += 64) diag[wave][e] = 0.f;
   }
@@ -179,22 +238,30 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     const uint32_t y2o = static_cast<uint32_t>(blk) * (NY2 * 1024u);
     const uint32_t co = static_cast<uint32_t>(32 * blk - row0 - (kRows - 1) + n - 1 + kCPad) * 4u;
     const uint32_t ro = static_cast<uint32_t>(blk) * (kRecWords * 4u);
-#pragma unroll
-    for (int i = 0; i < (NF + NC + NR + NW - 1) / NW; ++i) {
-      const int f = NW * i + wave;
-      if (f < NY)
+    constexpr_for<(NF + NC + NR + NW - 1) / NW>([&](auto ic) {
+      constexpr int lo = NW * decltype(ic)::value, hi = lo + NW - 1;  // this round's pieces
+      const int f = lo + wave;
+      if constexpr (hi < NY) {
         stage_lds<16>(ry, base + f * 1024u, v16, yo + f * 1024u);
-      else if (f < NY + NY2)
+      } else if constexpr (lo >= NY && hi < NY + NY2) {
         stage_lds<16>(ry2, base + f * 1024u, v16, y2o + (f - NY) * 1024u);
-      else if (f < NF)
+      } else if constexpr (lo >= NY + NY2 && hi < NF) {
         stage_lds<16>(rz, base + f * 1024u, v16, zo + (f - NY - NY2) * 1024u);
-      else if (f < NF + NC)
-        stage_lds<4>(rc, sb + (f - NF) * 256u, lane * 4u, co + (f - NF) * 256u);
-      else if (f == NF + NC)
-        stage_lds<4>(rr, sb + NC * 256u, lane * 4u, ro);
-      else if (MODE == 2 && f == NF + NC + 1)
-        stage_lds<4>(rr2, sb + (NC + 1) * 256u, lane * 4u, ro);
-    }
+      } else {
+        if (f < NY)
+          stage_lds<16>(ry, base + f * 1024u, v16, yo + f * 1024u);
+        else if (f < NY + NY2)
+          stage_lds<16>(ry2, base + f * 1024u, v16, y2o + (f - NY) * 1024u);
+        else if (f < NF)
+          stage_lds<16>(rz, base + f * 1024u, v16, zo + (f - NY - NY2) * 1024u);
+        else if (f < NF + NC)
+          stage_lds<4>(rc, sb + (f - NF) * 256u, lane * 4u, co + (f - NF) * 256u);
+        else if (f == NF + NC)
+          stage_lds<4>(rr, sb + NC * 256u, lane * 4u, ro);
+        else if (MODE == 2 && f == NF + NC + 1)
+          stage_lds<4>(rr2, sb + (NC + 1) * 256u, lane * 4u, ro);
+      }
+    });
   };
   Total zt[CT][16];
   double dsum = 0.0;
@@ -214,23 +281,35 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     const uint4* __restrict__ zf = y + (NY + NY2) * kFragLanes;
     const float* __restrict__ rec = &strip[buf][NC * 64];
     const float* __restrict__ cs = &strip[buf][kRows - 1 - 32 * wave - lr + 4 * lh];
-    floatx16 s = zero16(), s1 = zero16();
+    floatx16 s, s1;
+    s_product<KS>(y, x, s, s1);
+    constexpr bool kAhead = KS <= kAheadSteps;
+    float c16[kAhead ? 16 : 1], k16[kAhead ? 16 : 1];
+    if constexpr (kAhead) {
+      // read with the products: the table's entries and the record
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const uint4 yh = y[(ks * 2 + 0) * kFragLanes], yl = y[(ks * 2 + 1) * kFragLanes];
-      s = mfma_f16(yh, x[ks][0], s);
-      s1 = mfma_f16(yh, x[ks][1], s1);
-      s1 = mfma_f16(yl, x[ks][0], s1);
+      for (int e = 0; e < 16; ++e) c16[e] = cs[8 * (e >> 2) + (e & 3)];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 kr = *reinterpret_cast<const float4*>(rec + 8 * g + 4 * lh);
+        k16[4 * g] = kr.x, k16[4 * g + 1] = kr.y, k16[4 * g + 2] = kr.z, k16[4 * g + 3] = kr.w;
+      }
+      s_schedule<KS>();
     }
     const int kexp = __float_as_int(rec[kRecE]);
     // P: lane row lr, keys 8 (e / 4) + 4 lh + e % 4
     float p[16];
+    if constexpr (kAhead) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 kr = *reinterpret_cast<const float4*>(rec + 8 * g + 4 * lh);
-      const float k4[4] = {kr.x, kr.y, kr.z, kr.w};
+      for (int e = 0; e < 16; ++e) p[e] = fmaf(s1[e], kLoInv, s[e]) * k16[e];
+    } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) p[4 * g + j] = fmaf(s1[4 * g + j], kLoInv, s[4 * g + j]) * k4[j];
+      for (int g = 0; g < 4; ++g) {
+        const float4 kr = *reinterpret_cast<const float4*>(rec + 8 * g + 4 * lh);
+        const float k4[4] = {kr.x, kr.y, kr.z, kr.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[4 * g + j] = fmaf(s1[4 * g + j], kLoInv, s[4 * g + j]) * k4[j];
+      }
     }
     if constexpr (MODE == 2) {
       // the products (X2 Y2^T) o (X Y^T) of this block summed along its
@@ -241,14 +320,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       // next one's lie 32 below.
       const float* __restrict__ rec2 = rec + kRecWords;
       const uint4* __restrict__ y2 = y + NY * kFragLanes;
-      floatx16 r = zero16(), r1 = zero16();
-#pragma unroll
-      for (int ks = 0; ks < KS2; ++ks) {
-        const uint4 yh = y2[(ks * 2 + 0) * kFragLanes], yl = y2[(ks * 2 + 1) * kFragLanes];
-        r = mfma_f16(yh, x2[ks][0], r);
-        r1 = mfma_f16(yh, x2[ks][1], r1);
-        r1 = mfma_f16(yl, x2[ks][0], r1);
-      }
+      floatx16 r, r1;
+      s_product<KS2>(y2, x2, r, r1);
       const float f = ldexpf(1.f, rp2 + kexp + __float_as_int(rec2[kRecE]));
       float* __restrict__ win = &diag[wave][(32 + lr - 4 * lh) * kDS + 4 * lh];
 #pragma unroll
@@ -272,7 +345,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       __builtin_amdgcn_wave_barrier();
     }
 #pragma unroll
-    for (int e = 0; e < 16; ++e) p[e] *= cs[8 * (e >> 2) + (e & 3)];
+    for (int e = 0; e < 16; ++e) p[e] *= kAhead ? c16[kAhead ? e : 0] : cs[8 * (e >> 2) + (e & 3)];
     if (32 * blk + 32 > n) {  // uniform: keys past n (their fragments are zero, but c may be infinite)
 #pragma unroll
       for (int e = 0; e < 16; ++e)
