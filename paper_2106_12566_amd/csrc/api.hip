@@ -625,8 +625,9 @@ krpe_status_t toeplitz_conv(const float* b, const float* a, float* y, int B, int
   const int BHi = static_cast<int>(bh);
   const int N = 1 << L.l2;
   const int splits = conv_splits(L.l2);
-  // The product runs through the attention's convolution kernel with one
-  // feature equal to 1 everywhere: a_c plays the role of the value column c.
+  // Up to n = 8192 the product has a kernel of its own; beyond, it runs through
+  // the attention's convolution kernel with one feature equal to 1 everywhere:
+  // a_c plays the role of the value column c.
   if (L.nb > 1) {
     // Blocks of nbk positions (Eqs. (12)-(13) per block of C): y_I =
     // sum_J C_IJ a_J, block row I as one launch over the nb key blocks J
@@ -663,6 +664,16 @@ krpe_status_t toeplitz_conv(const float* b, const float* a, float* y, int B, int
         return s;
     }
     return KRPE_OK;
+  }
+  if (toeplitz_one_kernel(L.l2, static_cast<long long>(bh) * ((C + 1) / 2))) {
+    // The thread-order tables (2 N entries) lie where the other path keeps its
+    // row of ones (N entries' bytes), the packed channels behind it (at least
+    // N) and its partial sums: workspace sizes, and with them what the static
+    // scratch takes, are the same on both paths.
+    float2* tt = reinterpret_cast<float2*>(w + L.ones);
+    if (krpe_status_t s = hip_check(launch_toeplitz_twiddles(L.l2, tw, tt, st), "twiddle launch")) return s;
+    if (krpe_status_t s = hip_check(launch_spectrum(L.l2, b, tw, Hs, nullptr, H, n, st), "spectrum launch")) return s;
+    return hip_check(launch_toeplitz(L.l2, a, Hs, tw, tt, y, BHi, H, n, C, st), "product launch");
   }
   if (krpe_status_t s = hip_check(launch_twiddles(tw, L.l2, st), "twiddle launch")) return s;
   if (krpe_status_t s = hip_check(launch_spectrum(L.l2, b, tw, Hs, nullptr, H, n, st), "spectrum launch")) return s;

@@ -280,7 +280,11 @@ struct Dft<16, INV> {
 // slower than 8-byte ones where the LDS is the busier pipe.
 // PAD: LDS layout of the hand-overs (see pad); 0 keeps one padding slot per R
 // positions.
-template <int LOG2N_, int LOG2R_, int TWS = 1, bool TWC = false, bool AFF = false, int PAD = 0>
+// TWT: `tw` is not W_M but the passes' twiddles in the order the threads use
+// them, entry p N + (u RP + s) T + tau for output s of butterfly u of thread
+// tau in pass p < P - 1: consecutive lanes read consecutive entries (from W_M they gather entries s 2^(LR p + TWS) apart, a cache line
+// per lane).  For users that run a few transforms per thread.
+template <int LOG2N_, int LOG2R_, int TWS = 1, bool TWC = false, bool AFF = false, int PAD = 0, bool TWT = false>
 struct Fft {
   static constexpr int LOG2N = LOG2N_;
   static constexpr int N = 1 << LOG2N;
@@ -345,9 +349,12 @@ struct Fft {
     return off;
   }
   static constexpr int TABLE = TWC ? twc_offset(P) : M_TAB;
+  // (tt, tau: the table index and thread, of TWT alone)
   template <int p>
-  __device__ __forceinline__ static float2 twiddle(const float2* __restrict__ tw, int ts) {
-    if constexpr (TWC && p > 0) {
+  __device__ __forceinline__ static float2 twiddle(const float2* __restrict__ tw, int ts, int tt = 0, int tau = 0) {
+    if constexpr (TWT) {
+      return tw[p * N + tt * T + tau];
+    } else if constexpr (TWC && p > 0) {
       return tw[twc_offset(p) + ts];
     } else {
       return tw[ts << (LR * p + TWS)];
@@ -424,7 +431,7 @@ struct Fft {
         const int t = (tau + T * u) % SP;
 #pragma unroll
         for (int s = 1; s < RP; ++s) {
-          const float2 w = twiddle<p>(tw, t * s);
+          const float2 w = twiddle<p>(tw, t * s, u * RP + s, tau);
 #pragma unroll
           for (int k = 0; k < K; ++k) x[k][u * RP + s] = cmul(x[k][u * RP + s], w);
         }
@@ -476,7 +483,7 @@ struct Fft {
         const int t = (tau + T * u) % SP;
 #pragma unroll
         for (int s = 1; s < RP; ++s) {
-          const float2 w = twiddle<p>(tw, t * s);
+          const float2 w = twiddle<p>(tw, t * s, u * RP + s, tau);
 #pragma unroll
           for (int k = 0; k < K; ++k) x[k][u * RP + s] = cmulc(x[k][u * RP + s], w);
         }

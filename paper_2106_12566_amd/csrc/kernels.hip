@@ -87,11 +87,12 @@ __global__ void k_twiddles_ext(float2* __restrict__ tw) {
 }
 
 // ------------------------------------------------------------ spectrum --
-// c_{-s} embedded circularly in length 2N (see the header comment).
-__device__ __forceinline__ float circ_kernel(const float* __restrict__ bh, int s, int n, int N) {
-  if (s < n) return expf(bh[n - 1 - s]);
-  if (s > 2 * N - n) return expf(bh[2 * N - s + n - 1]);
-  return 0.f;
+// b_{-s} embedded circularly in length 2N (see the header comment), -inf where
+// the embedding is zero.
+__device__ __forceinline__ float circ_bias(const float* __restrict__ bh, int s, int n, int N) {
+  const bool low = s < n, high = s > 2 * N - n;
+  const float v = bh[low ? n - 1 - s : (high ? 2 * N - s + n - 1 : 0)];
+  return low || high ? v : -INFINITY;
 }
 
 // One transform per (head, residue class r < S): the bins k = S k' + r of the
@@ -120,13 +121,20 @@ __global__ __launch_bounds__(Conf<L2>::THREADS) void k_spectrum(const float* __r
   const float* bh = b + static_cast<size_t>(h) * (2 * n - 1);
   float2 x[F::R];
   float s1 = 0.f, s2 = 0.f;
+  // every entry of h's circular embedding loaded before any is used (as
+  // branches around single loads they were waited on one by one)
+  float hb[F::R][S];
+#pragma unroll
+  for (int i = 0; i < F::R; ++i)
+#pragma unroll
+    for (int p = 0; p < S; ++p) hb[i][p] = circ_bias(bh, tau + F::T * i + p * F::N, n, C::N);
 #pragma unroll
   for (int i = 0; i < F::R; ++i) {
     const int j = tau + F::T * i;
     float2 acc = make_float2(0.f, 0.f);
 #pragma unroll
     for (int p = 0; p < S; ++p) {
-      const float hv = circ_kernel(bh, j + p * F::N, n, C::N);
+      const float hv = expf(hb[i][p]);
       s1 += hv;
       s2 = fmaf(hv, hv, s2);
       acc = cadd(acc, rot_dyn<S, false>(make_float2(hv, 0.f), p * r));

@@ -221,6 +221,21 @@ inline bool direct_rows_path(long long BH, int n, int M) {
 hipError_t launch_direct_rows(const float* phiq, const float* phik, const float* v, const float* b, float* z,
                               float* den_out, int2* brange, float* cexp, int BH, int H, int n, int ld, int d, int m,
                               hipStream_t st);
+// y = C a in one kernel (toeplitz.hip) of BH ceil(C / 2) units: up to N = 4096
+// at every size, at 8192 (512 threads, registers spilled) where the units fill
+// the chip: one unit 62 against 54 us per call through the convolution kernel,
+// 768 units 188 against 202.  At 16384 a pair's values, the sums of its eight
+// classes and the transform do not fit one work-group's registers.
+constexpr int kToeplitzLog2N = 13;
+inline bool toeplitz_one_kernel(int l2, long long units) {
+  return l2 < kToeplitzLog2N || (l2 == kToeplitzLog2N && units >= 512);
+}
+// Its twiddles: W_{2N} (N = 8192: twiddle_slots entries) and, where
+// toeplitz_tables, at most 2 N entries in thread order at tt.
+bool toeplitz_tables(int l2);
+hipError_t launch_toeplitz_twiddles(int l2, float2* tw, float2* tt, hipStream_t st);
+hipError_t launch_toeplitz(int l2, const float* a, const float2* Hs, const float2* tw, const float2* tt, float* y, int BH,
+                           int H, int n, int C, hipStream_t st);
 hipError_t launch_ones(float* ones, int n, int N, hipStream_t st);
 // Long sequences (long_seq.hip): block copies of phi rows, bias windows of a
 // block pair, sums over key blocks, certification weights, row masks, rows.
