@@ -733,6 +733,10 @@ krpe_status_t krpe_feature_map_ex(const void* x, int x_dtype, const float* W, fl
       (needW && overlaps(rphi, {W, static_cast<size_t>(H) * m * d * sizeof(float)})))
     return fail(KRPE_ERR_ALIAS, "phi overlaps x or W");
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (kind != kFeatElu)
+    return hip_check(launch_phi(x_dtype == KRPE_BF16, x, W, phi, static_cast<int>(bh), H, n, d, m,
+                                (flags & KRPE_NPRF) != 0, kind == kFeatTrf, st),
+                     "feature map launch");
   return hip_check(launch_feature_map(x_dtype == KRPE_BF16, x, x, W, phi, phi, 1, false, M, static_cast<int>(bh),
                                       H, n, d, m, nullptr, (flags & KRPE_NPRF) != 0, kind, st),
                    "feature map launch");

@@ -48,31 +48,13 @@ struct PrepArgs {
   int* kpow;        // [BH][32 nblk] powers of phi(k) (NULL: not wanted)
   int BH, H, n, nblk, d, m, KS, ct_total, kind, nprf, tiles, phi_blocks, v_blocks;
   float inv_sqrt_m;
-  float log2_m_hi, log2_m_lo;  // -log2(sqrt(m)) in two floats
+  double log2_m;  // -log2(sqrt(m))
 };
-constexpr float kLn2 = 0.69314718055994531f;
-
-// 2^((s + sl) (r + rl) + (c + cl)) with the exponent in two floats (its rounding
-// at a size of about 10 is the largest error of phi otherwise): t + tl, then
-// 2^rint(t) 2^(t - rint(t)) (1 + tl ln 2).  Zero below 2^-400, infinite
-// arguments included.
-__device__ __forceinline__ float exp2_two(float s, float sl, float r, float rl, float c, float cl) {
-#pragma clang fp contract(off)
-  const float sum = s + sl, sb = sum - s;
-  sl = (s - (sum - sb)) + (sl - sb);
-  s = sum;
-  const float p = s * r, pl = fmaf(s, rl, fmaf(sl, r, fmaf(s, r, -p)));
-  const float t = p + c, b = t - p, tl = (((p - (t - b)) + (c - b)) + pl) + cl;
-  const float ti = rintf(t), y = __builtin_amdgcn_exp2f(t - ti);
-  const float f = ldexpf(fmaf(y, tl * kLn2, y), static_cast<int>(fminf(fmaxf(ti, -300.f), 300.f)));
-  return t < -400.f ? 0.f : f;
-}
-
 // DK: k steps of the head dimension, d <= 16 DK.  NT: 32-feature tiles of
 // projections held in registers until the position's largest feature is known.
 template <typename TX, int DK, int NT>
 __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __restrict__ smem) {
-  constexpr int XS = 16 * DK + 4;  // floats per staged row (16 lanes' 16-byte reads fall in distinct banks)
+  constexpr int XS = x_stride(DK);
   constexpr int NSX = sizeof(TX) == 2 ? 1 : 3;
   constexpr int GT = DK <= 4 ? 4 : 2;  // tiles of W staged at a time
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -81,47 +63,22 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
   const int h = bh % a.H, n = a.n, d = a.d;
   const TX* __restrict__ x = static_cast<const TX*>(src == 0 ? a.q : a.k) + static_cast<size_t>(bh) * n * d;
   const int p0 = pt * 128, rows = min(128, n - p0);
-  // x rows to LDS (zeros past n and past d); rows of 8-element multiples are
-  // 16-byte aligned (the base is)
-  const bool vec = d % 8 == 0;
-  for (int e = tid; e < 128 * 2 * DK; e += 256) {
-    const int r = e / (2 * DK), c8 = 8 * (e % (2 * DK));
-    float v8[8];
-    load8(x + static_cast<size_t>(p0 + min(r, rows - 1)) * d + c8, r < rows ? d - c8 : 0, vec, v8);
-    *reinterpret_cast<float4*>(smem + r * XS + c8) = make_float4(v8[0], v8[1], v8[2], v8[3]);
-    *reinterpret_cast<float4*>(smem + r * XS + c8 + 4) = make_float4(v8[4], v8[5], v8[6], v8[7]);
-  }
+  stage_x<TX, DK>(x, p0, rows, d, smem);
   __syncthreads();
-  // this lane's position: dimensions 16 ks + 8 lh + t as B operands; its
-  // squared norm in fp64 (it is the same for every feature: an error of it
-  // weighs on the whole position)
+  // this lane's position: its operand and squared norm
   uint4 xf[DK][NSX];
-  double sqd = 0.0;
   const float* __restrict__ row = smem + (32 * wave + lr) * XS;
-#pragma unroll
-  for (int ks = 0; ks < DK; ++ks) {
-    const float4 u = *reinterpret_cast<const float4*>(row + 16 * ks + 8 * lh);
-    const float4 w = *reinterpret_cast<const float4*>(row + 16 * ks + 8 * lh + 4);
-    const float v8[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int t = 0; t < 8; ++t) sqd = fma(static_cast<double>(v8[t]), static_cast<double>(v8[t]), sqd);
-    uint4 t3[3];
-    split_bf16x8(v8, t3);
-#pragma unroll
-    for (int s = 0; s < NSX; ++s) xf[ks][s] = t3[s];
-  }
-  sqd += __shfl_xor(sqd, 32);  // ||x||^2
+  const double sqd = x_operand<DK, NSX>(row, lh, xf);
   // phi of x / ||x|| when normalising (Algorithm 1, first step): the
   // projections scale by 1 / ||x|| and ||x||^2 / 2 becomes 1/2 (a zero row
   // stays zero).
   const bool nz = sqd > 0.0;
   const double half_sq = a.nprf ? (nz ? 0.5 : 0.0) : 0.5 * sqd;
   const float row_scale = a.nprf ? (nz ? static_cast<float>(1.0 / sqrt(sqd)) : 0.f) : 1.f;
-  // PRF: phi = 2^(s rs + e0), rs and e0 in two floats each
-  const double rsd = (a.nprf ? (nz ? 1.0 / sqrt(sqd) : 0.0) : 1.0) * 1.4426950408889634;
-  const double e0d = -half_sq * 1.4426950408889634 + (static_cast<double>(a.log2_m_hi) + static_cast<double>(a.log2_m_lo));
-  const float rs = static_cast<float>(rsd), rs_lo = static_cast<float>(rsd - static_cast<double>(rs));
-  const float e0 = static_cast<float>(e0d), e0_lo = static_cast<float>(e0d - static_cast<double>(e0));
+  // PRF: phi_prf's factors
+  const float rs = static_cast<float>((a.nprf ? (nz ? 1.0 / sqrt(sqd) : 0.0) : 1.0) * kLog2e);
+  const double e0d = a.log2_m - half_sq * kLog2e;
+  const float e0 = static_cast<float>(e0d), ef = rounding_factor(e0d, e0);
   const bool pos_ok = p0 + 32 * wave + lr < n;
   const int blk = 4 * pt + wave;
   const bool store = blk < a.nblk;  // uniform
@@ -130,40 +87,11 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
   const int ksp = a.kind == kFeatTrf ? a.KS / 2 : a.KS;  // k steps of projections (of x for elu + 1)
   const int ftiles = (ksp + 1) / 2;
   const float* __restrict__ Wh = a.W + static_cast<size_t>(h) * a.m * d;
-  uint4* __restrict__ wf = reinterpret_cast<uint4*>(smem);  // [tile][ks][term][64]
-  // rows 32 t0 .. of W (up to GT tiles) split into LDS
-  auto stage_w = [&](int t0) {
+  uint4* __restrict__ wf = reinterpret_cast<uint4*>(smem);
+  auto stage_tiles = [&](int t0) {
     __syncthreads();  // x rows / the previous features consumed
-    const int gt = min(GT, ftiles - t0);
-    for (int e = tid; e < gt * 32 * 2 * DK; e += 256) {
-      const int fl = e / (2 * DK), c = e % (2 * DK), f = 32 * t0 + fl;
-      float v8[8];
-      load8(Wh + static_cast<size_t>(min(f, a.m - 1)) * d + 8 * c, f < a.m ? d - 8 * c : 0, d % 4 == 0, v8);
-      uint4 t3[3];
-      split_bf16x8(v8, t3);
-      uint4* __restrict__ o = wf + ((fl >> 5) * DK + (c >> 1)) * 3 * kFragLanes + (c & 1) * 32 + (fl & 31);
-#pragma unroll
-      for (int s = 0; s < 3; ++s) o[s * kFragLanes] = t3[s];
-    }
+    stage_w<DK>(Wh, 32 * t0, min(GT, ftiles - t0), a.m, d, wf);
     __syncthreads();
-  };
-  // projections of staged tile tt: the products of the largest terms, and the
-  // small ones, apart
-  auto project = [&](int tt, floatx16& acc, floatx16& lo) {
-    acc = zero16();
-    lo = zero16();
-#pragma unroll
-    for (int ks = 0; ks < DK; ++ks) {
-      uint4 w3[3];
-#pragma unroll
-      for (int s = 0; s < 3; ++s) w3[s] = wf[((tt * DK + ks) * 3 + s) * kFragLanes + lane];
-#pragma unroll
-      for (int s = 2; s >= 1; --s)
-#pragma unroll
-        for (int i = 0; i <= s; ++i)
-          if (s - i < NSX) lo = mfma_bf16(w3[i], xf[ks][s - i], lo);
-      acc = mfma_bf16(w3[0], xf[ks][0], acc);
-    }
   };
   auto emit = [&](int ks, const float (&v8)[8]) {
     uint4 hh, ll;
@@ -180,10 +108,10 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
     const float as = ldexpf(amp, -ex);
     any_phi = amp > 0.f;
     for (int t0 = 0; t0 < ftiles; t0 += GT) {
-      stage_w(t0);
+      stage_tiles(t0);
       for (int tt = 0; tt < min(GT, ftiles - t0) && store; ++tt) {
         floatx16 acc, lo;
-        project(tt, acc, lo);
+        project<DK, NSX, false>(wf + tt * DK * 3 * kFragLanes, xf, acc, lo);
         float s16[16], c16[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
@@ -223,12 +151,12 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
       constexpr_for<NT>([&](auto tc) {
         constexpr int ti = decltype(tc)::value, t0 = ti / GT * GT;
         if (ti >= ftiles) return;  // uniform
-        if constexpr (ti == t0) stage_w(t0);
+        if constexpr (ti == t0) stage_tiles(t0);
         floatx16 acc, lo;
-        project(ti - t0, acc, lo);
+        project<DK, NSX, false>(wf + (ti - t0) * DK * 3 * kFragLanes, xf, acc, lo);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          val[ti][e] = pos_ok ? exp2_two(acc[e], lo[e], rs, rs_lo, e0, e0_lo) : 0.f;
+          val[ti][e] = pos_ok ? phi_prf(acc[e], lo[e], rs, e0, ef) : 0.f;
         }
         if (32 * ti + 32 > a.m) {  // uniform: unused slots are zero
 #pragma unroll
@@ -380,7 +308,7 @@ __device__ __forceinline__ void prep_c(const PrepArgs& a, int bid) {
 
 template <typename TX, int DK, int NT>
 __global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
-  constexpr int kX = 128 * (16 * DK + 4), kW = (DK <= 4 ? 4 : 2) * DK * 3 * 256;
+  constexpr int kX = 128 * x_stride(DK), kW = (DK <= 4 ? 4 : 2) * DK * 3 * 256;
   __shared__ __align__(16) float smem[kX > kW ? kX : kW];
   const int bid = blockIdx.x;
   if (bid < a.phi_blocks) {
@@ -566,9 +494,7 @@ hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, con
   p.phi_blocks = 2 * BH * p.tiles;
   p.v_blocks = BH * p.tiles;
   p.inv_sqrt_m = static_cast<float>(1.0 / std::sqrt(static_cast<double>(m)));
-  const double lm = -0.5 * std::log2(static_cast<double>(m));
-  p.log2_m_hi = static_cast<float>(lm);
-  p.log2_m_lo = static_cast<float>(lm - static_cast<double>(p.log2_m_hi));
+  p.log2_m = -0.5 * std::log2(static_cast<double>(m));
   return bf16 ? prep_go<uint16_t>(p, st) : prep_go<float>(p, st);
 }
 

@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "features.hpp"
 #include "wprod.hpp"
 
 namespace krpe {
@@ -19,28 +20,6 @@ constexpr int kRecWords = 64, kRecE = 32, kRecV = 33;
 // S of two positions is at most 2^30 M in units of their powers: E carries 30
 // of them, so that P stays near c_{j-i}'s range.
 constexpr int kRecBias = 30;
-
-// 8 values of a row from position p (zeros past `count` values of the row)
-template <typename T>
-__device__ __forceinline__ void load8(const T* __restrict__ p, int count, bool vec, float (&x)[8]) {
-  if (vec && count >= 8) {
-    if constexpr (std::is_same<T, float>::value) {
-      const float4 a = reinterpret_cast<const float4*>(p)[0], c = reinterpret_cast<const float4*>(p)[1];
-      x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w, x[4] = c.x, x[5] = c.y, x[6] = c.z, x[7] = c.w;
-    } else {
-      const uint4 u = *reinterpret_cast<const uint4*>(p);
-      const unsigned w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        x[2 * j] = __uint_as_float(w[j] << 16);
-        x[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = j < count ? to_f32(p[j]) : 0.f;
-  }
-}
 
 // --------------------------------------------------------------- direct --
 // One work-group: 32 NW consecutive rows of one (batch, head), each wave its
