@@ -73,66 +73,98 @@ constexpr unsigned kKnownFlags =
     KRPE_NPRF | KRPE_FEAT_TRF | KRPE_FEAT_ELU | KRPE_ROUTE_DIRECT | KRPE_ROUTE_FFT | KRPE_HINT_CAUSAL;
 constexpr unsigned kBwdFlags = KRPE_NPRF | KRPE_ROUTE_DIRECT | KRPE_ROUTE_FFT | KRPE_HINT_CAUSAL;
 
-// Whether the direct route is the faster one for BH heads of length n with M
-// features and d value columns.  Cost model fitted to MI355X timings of both
-// routes at 80 shapes (B H = 1, 16, 96; d = 64; M = 32 .. 128; n = 512 ..
-// 40000, not causal): each route's time is its work over all heads at a
-// measured rate plus a fixed cost (the launch chain and its latency-bound
-// small kernels).  Direct: per (query, key) pair and unit of M rounded up to
-// a multiple of 64, plus d + 1, 1.74e-14 s on the row-parallel kernel and
-// 1.9e-14 s on the exact-row kernel (few heads, or M > 128), plus 7.4e-5 s.
-// FFT: per column pair, feature and point of the length-2N transform times
-// log2(2N), 1.65e-13 s up to N = 4096, 3.8e-13 s at N = 8192 and 3.1e-13 s
-// at N = 16384, over the nb^2 block pairs of a blocked sequence, plus
-// 1.5e-4 s.
-// All n^2 pairs are counted, as the host does not read b, unless the caller
-// states a causal mask (KRPE_HINT_CAUSAL): the direct kernels then visit the
-// n (n + 1) / 2 pairs j <= i only (measured at n = 16384, 16 heads, m = 256:
-// 11.7 ms direct, 17.8 ms FFT), and a blocked FFT route runs the
-// nb (nb + 1) / 2 block pairs on or below the diagonal.  The route bits force
-// either route.
-bool direct_is_faster(long long BH, int n, int M, int d, bool causal) {
+// Cost models of the routes, seconds, fitted to MI355X timings (B H = 1 .. 96;
+// d = 64; M = 16 .. 256; n = 512 .. 65536).  Query/key pairs: all n^2, as the
+// host does not read b, unless the caller states a causal mask
+// (KRPE_HINT_CAUSAL): the direct kernels then visit n (n + 1) / 2 and a blocked
+// FFT route the nb (nb + 1) / 2 block pairs on or below the diagonal.
+double pair_count(int n, bool causal) {
+  return causal ? 0.5 * static_cast<double>(n) * (n + 1) : static_cast<double>(n) * n;
+}
+
+// FFT route: per column pair, feature and point of the length-2N transform
+// times log2(2N), 1.65e-13 s up to N = 4096, 3.8e-13 s at N = 8192 and 3.1e-13 s
+// at N = 16384, over the nb^2 block pairs of a blocked sequence, plus 1.5e-4 s.
+double fft_seconds(long long BH, int n, int M, int d, bool causal) {
   int l2 = 0;
   while ((1 << l2) < n) ++l2;
-  // beyond one transform block the FFT route runs nb^2 block pairs
   const int nb = l2 > kMaxLog2N ? (n + (1 << kMaxLog2N) - 1) >> kMaxLog2N : 1;
   if (l2 > kMaxLog2N) l2 = kMaxLog2N;
   const double L = 2.0 * static_cast<double>(1 << l2);
-  const double heads = static_cast<double>(BH);
-  const double pairs = causal ? 0.5 * static_cast<double>(n) * (n + 1) : static_cast<double>(n) * n;
-  // (both direct kernels run the features in steps of 64)
-  const double per_pair = M <= 128 && BH * ((n + 31) / 32) >= 1536 ? 1.74e-14 : 1.9e-14;
-  const double direct = per_pair * heads * pairs * (((M + 63) / 64) * 64 + d + 1) + 7.4e-5;
   const double rate = l2 <= 12 ? 1.65e-13 : (l2 == 13 ? 3.8e-13 : 3.1e-13);
-  // (a causal mask leaves nb (nb + 1) / 2 of the block pairs live; the others are skipped)
   const double blocks = causal ? 0.5 * nb * (nb + 1) : static_cast<double>(nb) * nb;
-  const double fft = rate * heads * M * ((d + 2) / 2) * L * (l2 + 1) * blocks + 1.5e-4;
-  return direct < fft;
+  return rate * static_cast<double>(BH) * M * ((d + 2) / 2) * L * (l2 + 1) * blocks + 1.5e-4;
+}
+
+// The direct route on the fp16 matrix cores (direct.hip): per pair and unit of
+// its padded work (features in steps of 16 per column pass, columns in tiles
+// of 32) 6.5e-15 s, plus 2e-5 s.  Measured at d = 64 it is the faster route at
+// every shape up to n = 8192 with M >= 16 (96 heads, n = 2048, M = 32: 0.34
+// against 1.0 ms); with fewer features, padded to 32, the transforms can win.
+double direct_seconds(long long BH, int n, int ks, int d, bool causal) {
+  const int ct = (d + 31) / 32, passes = (ct + 1) / 2;
+  return 6.5e-15 * static_cast<double>(BH) * pair_count(n, causal) * (16.0 * ks * passes + 32.0 * ct + 1.0) + 2e-5;
+}
+
+// Whether the direct route on the fp32 matrix cores is the faster one: more
+// than 256 features, and the forward pass inside the transform backward.  Per
+// pair and unit of M rounded up to a multiple of 64, plus d + 1, 1.74e-14 s on
+// the row-parallel kernel and 1.9e-14 s on the exact-row kernel (few heads, or
+// M > 128), plus 7.4e-5 s (fitted at 80 shapes).
+bool fp32_direct_is_faster(long long BH, int n, int M, int d, bool causal) {
+  const double per_pair = direct_rows_path(BH, n, M) ? 1.74e-14 : 1.9e-14;
+  const double direct =
+      per_pair * static_cast<double>(BH) * pair_count(n, causal) * (((M + 63) / 64) * 64 + d + 1) + 7.4e-5;
+  return direct < fft_seconds(BH, n, M, d, causal);
 }
 
 // Route of the forward pass: the FFT convolution (Sec. 3.2) or the direct
-// quadratic evaluation of Eq. (10) on MFMA, forced by an option bit or chosen
-// by the measured cost model (the direct route is faster for short sequences).
-bool use_direct(unsigned flags, long long BH, int n, int M, int d) {
+// quadratic evaluation of Eq. (10) on the matrix cores, forced by an option bit
+// or chosen by the cost models.
+bool use_direct(unsigned flags, long long BH, int n, int M, int d, int m, int kind) {
   if (flags & KRPE_ROUTE_DIRECT) return true;
   if (flags & KRPE_ROUTE_FFT) return false;
-  return direct_is_faster(BH, n, M, d, (flags & KRPE_HINT_CAUSAL) != 0);
+  const bool causal = (flags & KRPE_HINT_CAUSAL) != 0;
+  // Beyond n = 8192 the route that krpe_attention_fwd_route has always reported
+  // for a shape is kept (the fp32 model's).  Of 55 measured shapes that it sends
+  // to the transforms there, the direct route is faster on 39, up to 2.9 times
+  // (16 heads, n = 16384, M = 128: 4.9 against 8.6 ms): KRPE_ROUTE_DIRECT asks
+  // for it.
+  const int ks = direct_ksteps(kind, d, m);
+  if (ks != 0 && n <= 8192) return direct_seconds(BH, n, ks, d, causal) < fft_seconds(BH, n, M, d, causal);
+  return fp32_direct_is_faster(BH, n, M, d, causal);
+}
+// The forward pass inside the transform backward.
+bool use_fp32_direct(unsigned flags, long long BH, int n, int M, int d) {
+  if (flags & KRPE_ROUTE_DIRECT) return true;
+  if (flags & KRPE_ROUTE_FFT) return false;
+  return fp32_direct_is_faster(BH, n, M, d, (flags & KRPE_HINT_CAUSAL) != 0);
 }
 
 // Route of the backward pass's products (up to 256 features): the direct ones
-// of bwd_direct.hip or the transforms.  A call that states a causal mask, with
-// neither row normalisation nor a route, keeps the transforms (and with them
-// every bit of its results): where rows with small denominators weigh in, the
-// rounding that a transform spreads over the sequence is 1e-4 to 4e-1 of a
-// gradient's norm against 64 bits (the direct products 4e-7), so the two
-// routes differ by more than the results of one call may change.
-// KRPE_ROUTE_DIRECT asks for the direct ones (64 tokens, 12 heads: 0.08 ms
-// against 0.80).
+// of bwd_direct.hip or the transforms.  The direct ones take 2.9e-14 s per pair
+// and unit of their features (in 64, 128 or 256) and columns plus 1.5e-4 s,
+// more where their row tiles do not fill the chip; the transforms about 4.9
+// forward passes (88 shapes: 96 heads, n = 4096, M = 128 9.2 ms direct, 34.5
+// transforms; one head, n = 16384, M = 32 2.7 and 1.8).
+//
+// A call that states a causal mask, with neither row normalisation nor a
+// route, keeps the transforms (and with them every bit of its results): where
+// rows with small denominators weigh in, the rounding that a transform spreads
+// over the sequence is 1e-4 to 4e-1 of a gradient's norm against 64 bits (the
+// direct products 4e-7), so the two routes differ by more than the results of
+// one call may change.  KRPE_ROUTE_DIRECT asks for the direct ones (64 tokens,
+// 12 heads: 0.08 ms against 0.80).
 bool use_direct_products(unsigned flags, long long BH, int n, int M, int d) {
   if (flags & KRPE_ROUTE_DIRECT) return true;
   if (flags & KRPE_ROUTE_FFT) return false;
-  if ((flags & KRPE_HINT_CAUSAL) && !(flags & KRPE_NPRF)) return false;
-  return direct_is_faster(BH, n, M, d, (flags & KRPE_HINT_CAUSAL) != 0);
+  const bool causal = (flags & KRPE_HINT_CAUSAL) != 0;
+  if (causal && !(flags & KRPE_NPRF)) return false;
+  const double tiles = static_cast<double>(BH) * ((n + 127) / 128);
+  const double fill = tiles < 320.0 ? 320.0 / tiles : 1.0;
+  const double direct = 2.9e-14 * static_cast<double>(BH) * pair_count(n, causal) * fill *
+                            (16.0 * direct_bwd_ksteps(M) + d + 1.0) + 1.5e-4;
+  return direct < 4.9 * fft_seconds(BH, n, M, d, causal);
 }
 
 // Feature map selected by the option bits, and its number of features M
@@ -783,7 +815,7 @@ size_t krpe_attention_fwd_workspace_ex(int B, int H, int n, int d, int m, unsign
   if (feature_kind(flags, d, m, &kind, &M) != KRPE_OK) return 0;
   // Up to one transform the size serves either route, so that a workspace
   // stays valid when the route bits or the causal hint of a call differ.
-  const bool direct = use_direct(flags, static_cast<long long>(B) * H, n, M, d);
+  const bool direct = use_direct(flags, static_cast<long long>(B) * H, n, M, d, m, kind);
   const size_t need = fwd_workspace(B, H, n, d, m, M, kind, direct);
   if (n > (1 << kMaxLog2N)) return need;
   const size_t other = fwd_workspace(B, H, n, d, m, M, kind, !direct);
@@ -810,7 +842,7 @@ krpe_status_t krpe_attention_fwd_profiled(const void* q, const void* k, const vo
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(b) || (needW && misaligned(W)) ||
       misaligned(z) || misaligned(ws))
     return fail(KRPE_ERR_ALIGN, "all pointers must be 16-byte aligned");
-  const bool direct = use_direct(flags, static_cast<long long>(B) * H, n, M, d);
+  const bool direct = use_direct(flags, static_cast<long long>(B) * H, n, M, d, m, kind);
   const size_t need = fwd_workspace(B, H, n, d, m, M, kind, direct);
   if (!ws || ws_bytes < need) return fail(KRPE_ERR_WORKSPACE, "workspace needs " + std::to_string(need) + " bytes");
   const size_t qkv_bytes = bh * n * d * dtype_size(qkv_dtype);
@@ -855,7 +887,7 @@ int krpe_attention_fwd_route(int B, int H, int n, int d, int m, unsigned flags) 
   if (B < 1 || H < 1 || n < 1 || n > (1 << kMaxLongLog2N) || d < 1 || d > kMaxD || m < 1 || m > kMaxM) return 0;
   int kind = kFeatPrf, M = m;
   if (feature_kind(flags, d, m, &kind, &M) != KRPE_OK) return 0;
-  return use_direct(flags, static_cast<long long>(B) * H, n, M, d) ? static_cast<int>(KRPE_ROUTE_DIRECT)
+  return use_direct(flags, static_cast<long long>(B) * H, n, M, d, m, kind) ? static_cast<int>(KRPE_ROUTE_DIRECT)
                                                                    : static_cast<int>(KRPE_ROUTE_FFT);
 }
 
@@ -887,7 +919,7 @@ krpe_status_t krpe_attention_bwd(const void* q, const void* k, const void* v, in
   for (const void* p : ptrs)
     if (misaligned(p)) return fail(KRPE_ERR_ALIGN, "all pointers must be 16-byte aligned");
   const BwdLayout L = bwd_layout(B, H, n, d, m);
-  const bool direct = use_direct(flags, static_cast<long long>(B) * H, n, m, d);
+  const bool direct = use_fp32_direct(flags, static_cast<long long>(B) * H, n, m, d);
   const bool products = direct_bwd_ksteps(m) != 0 && use_direct_products(flags, static_cast<long long>(B) * H, n, m, d);
   const size_t need = products ? direct_bwd_layout(B, H, n, d, m).total : L.total;
   if (!ws || ws_bytes < need)
