@@ -145,7 +145,7 @@ bool use_fp32_direct(unsigned flags, long long BH, int n, int M, int d) {
 // of bwd_direct.hip or the transforms.  The direct ones take 2.9e-14 s per pair
 // and unit of their features (in 64, 128 or 256) and columns plus 1.5e-4 s,
 // more where their row tiles do not fill the chip; the transforms about 4.9
-// forward passes (88 shapes: 96 heads, n = 4096, M = 128 9.2 ms direct, 34.5
+// forward passes (79 shapes: 96 heads, n = 4096, M = 128 9.2 ms direct, 34.5
 // transforms; one head, n = 16384, M = 32 2.7 and 1.8).
 //
 // A call that states a causal mask, with neither row normalisation nor a

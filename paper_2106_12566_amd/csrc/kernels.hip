@@ -167,11 +167,10 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // cos(s_l) / sqrt(m) (2m signed features).  Up to two sources (q and k) in
 // one launch.  Tile: 64 positions x 64 projections per work-group, four waves
 // of 32 x 32 v_mfma_f32_32x32x2f32 tiles; K (= d) staged through LDS in chunks
-// of 32.  FEATURE_MAJOR writes phi[bh][l][i] for i < ld (zeros for
-// n <= i < ld; lanes run along positions), otherwise phi[bh][i][l] (lanes run
-// along features): stores stay coalesced either way because the operand
-// roles are swapped.  M = m (PRF) or 2m (TRF) is the row length of phi.
-template <typename TX, bool FEATURE_MAJOR>
+// of 32.  Writes phi[bh][l][i] for i < ld (zeros for n <= i < ld; lanes run
+// along positions, so the stores are coalesced).  M = m (PRF) or 2m (TRF) is
+// the number of rows of phi.
+template <typename TX>
 __global__ __launch_bounds__(256) void k_feature_map(const TX* __restrict__ x0, const TX* __restrict__ x1,
                                                      const float* __restrict__ W, float* __restrict__ phi0,
                                                      float* __restrict__ phi1, int H, int n, int ld, int d,
@@ -222,10 +221,7 @@ __global__ __launch_bounds__(256) void k_feature_map(const TX* __restrict__ x0, 
       const int kq = kk + (lane >> 5);
       const float xa = xs[wi + (lane & 31)][kq];
       const float wb = wsm[wl + (lane & 31)][kq];
-      if constexpr (FEATURE_MAJOR)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wb, xa, acc, 0, 0, 0);
-      else
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa, wb, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wb, xa, acc, 0, 0, 0);
     }
     __syncthreads();
   }
@@ -239,17 +235,16 @@ __global__ __launch_bounds__(256) void k_feature_map(const TX* __restrict__ x0, 
     trf_amp[threadIdx.x] = expf(half_sq[threadIdx.x]) * inv_sqrt_m;
   }
   __syncthreads();
-  const int n_store = FEATURE_MAJOR ? ld : n;
   const int M = trf ? 2 * m : m;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     // 32x32 MFMA result layout: lane holds column lane%32, rows 8(v/4) + 4(lane/32) + v%4
     const int row = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     const int col = lane & 31;
-    const int li = FEATURE_MAJOR ? wl + row : wl + col;  // feature within tile
-    const int ii = FEATURE_MAJOR ? wi + col : wi + row;  // position within tile
+    const int li = wl + row;  // feature within tile
+    const int ii = wi + col;  // position within tile
     const int l = l0 + li, i = i0 + ii;
-    if (i < n_store && l < m) {
+    if (i < ld && l < m) {
       if (trf) {
         float sv = 0.f, cv = 0.f;
         if (i < n) {
@@ -257,19 +252,11 @@ __global__ __launch_bounds__(256) void k_feature_map(const TX* __restrict__ x0, 
           sv *= trf_amp[ii];
           cv *= trf_amp[ii];
         }
-        if constexpr (FEATURE_MAJOR) {
-          phi[(static_cast<size_t>(bh) * M + l) * ld + i] = sv;
-          phi[(static_cast<size_t>(bh) * M + m + l) * ld + i] = cv;
-        } else {
-          phi[(static_cast<size_t>(bh) * n + i) * M + l] = sv;
-          phi[(static_cast<size_t>(bh) * n + i) * M + m + l] = cv;
-        }
+        phi[(static_cast<size_t>(bh) * M + l) * ld + i] = sv;
+        phi[(static_cast<size_t>(bh) * M + m + l) * ld + i] = cv;
       } else {
         const float val = i < n ? expf(fmaf(acc[v], row_scale[ii], -half_sq[ii])) * inv_sqrt_m : 0.f;
-        if constexpr (FEATURE_MAJOR)
-          phi[(static_cast<size_t>(bh) * M + l) * ld + i] = val;
-        else
-          phi[(static_cast<size_t>(bh) * n + i) * M + l] = val;
+        phi[(static_cast<size_t>(bh) * M + l) * ld + i] = val;
       }
     }
   }
@@ -327,8 +314,8 @@ __device__ __forceinline__ void lds_half_row64(const float* __restrict__ rows, i
   }
 }
 
-template <typename TX, bool FEATURE_MAJOR>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(FEATURE_MAJOR ? 4 : 1))) void k_feature_map64(const TX* __restrict__ x0, const TX* __restrict__ x1,
+template <typename TX>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_feature_map64(const TX* __restrict__ x0, const TX* __restrict__ x1,
                                                        const float* __restrict__ W, float* __restrict__ phi0,
                                                        float* __restrict__ phi1, int H, int n, int ld, int m,
                                                        float inv_sqrt_m, int tiles_n, int BH,
@@ -360,7 +347,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(FEATURE_MAJ
 #pragma unroll
   for (int s2 = 0; s2 < 32; ++s2) sq = fmaf(xr[s2], xr[s2], sq);
   sq += __shfl_xor(sq, 32);  // ||x||^2 of position i0 + c
-  const int n_store = FEATURE_MAJOR ? ld : n;
   const int M = trf ? 2 * m : m;
   // Whole tiles of the PRF map in the feature-major layout: position i0 + c
   // of this lane; phi = 2^(a s log2(e) + e0) with e0 = -h log2(e) - log2(sqrt(m))
@@ -374,7 +360,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(FEATURE_MAJ
   const float e0_l = fmaf(-hs_l, kLog2e, __log2f(inv_sqrt_m));
   const bool pos_ok = i0 + c < n;  // positions n .. ld - 1 are zeros
   const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      phi + static_cast<size_t>(bh) * M * ld, 0, FEATURE_MAJOR ? M * ld * 4 : 0, 0x00020000);
+      phi + static_cast<size_t>(bh) * M * ld, 0, M * ld * 4, 0x00020000);
   const uint32_t out_voff = static_cast<uint32_t>(4 * half * ld + i0 + c) * 4u;
   for (int l0 = 0; l0 < m; l0 += 64) {
     if (l0 % 128 == 0) {
@@ -390,14 +376,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(FEATURE_MAJ
       float wr[32];
       lds_half_row64(ws, (l0 % 128) + 32 * t + c, half, wr);
 #pragma unroll
-      for (int s2 = 0; s2 < 32; ++s2) {
-        if constexpr (FEATURE_MAJOR)
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[s2], xr[s2], acc[t], 0, 0, 0);
-        else
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(xr[s2], wr[s2], acc[t], 0, 0, 0);
-      }
+      for (int s2 = 0; s2 < 32; ++s2)
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[s2], xr[s2], acc[t], 0, 0, 0);
     }
-    if (FEATURE_MAJOR && !trf && i0 + 32 <= n_store && l0 + 64 <= m) {  // uniform
+    if (!trf && i0 + 32 <= ld && l0 + 64 <= m) {  // uniform
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -415,18 +397,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(FEATURE_MAJ
       for (int v = 0; v < 16; ++v) {
         // 32x32 MFMA result layout: lane holds column lane%32, rows 8(v/4) + 4(lane/32) + v%4
         const int row = 8 * (v >> 2) + 4 * half + (v & 3);
-        const int li = FEATURE_MAJOR ? row : c;  // feature within the 32-feature tile t
-        const int ii = FEATURE_MAJOR ? c : row;  // position within the wave's 32
-        // ||x||^2 of position i0 + ii lives in lanes ii and ii + 32
-        const float sqi = FEATURE_MAJOR ? sq : __shfl(sq, ii);
-        const bool nz = sqi > 0.f;
+        const int li = row;  // feature within the 32-feature tile t
+        const int ii = c;  // position within the wave's 32
+        const bool nz = sq > 0.f;
         // phi of x / ||x|| when normalising (Algorithm 1, first step): the
         // projections scale by 1 / ||x|| and ||x||^2 / 2 becomes 1/2 (a zero
         // row stays zero)
-        const float half_sq = nprf ? (nz ? 0.5f : 0.f) : 0.5f * sqi;
-        const float row_scale = nprf ? (nz ? rsqrtf(sqi) : 0.f) : 1.f;
+        const float half_sq = nprf ? (nz ? 0.5f : 0.f) : 0.5f * sq;
+        const float row_scale = nprf ? (nz ? rsqrtf(sq) : 0.f) : 1.f;
         const int l = l0 + 32 * t + li, i = i0 + ii;
-        if (i < n_store && l < m) {
+        if (i < ld && l < m) {
           if (trf) {
             float sv = 0.f, cv = 0.f;
             if (i < n) {
@@ -435,19 +415,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(FEATURE_MAJ
               sv *= amp;
               cv *= amp;
             }
-            if constexpr (FEATURE_MAJOR) {
-              phi[(static_cast<size_t>(bh) * M + l) * ld + i] = sv;
-              phi[(static_cast<size_t>(bh) * M + m + l) * ld + i] = cv;
-            } else {
-              phi[(static_cast<size_t>(bh) * n + i) * M + l] = sv;
-              phi[(static_cast<size_t>(bh) * n + i) * M + m + l] = cv;
-            }
+            phi[(static_cast<size_t>(bh) * M + l) * ld + i] = sv;
+            phi[(static_cast<size_t>(bh) * M + m + l) * ld + i] = cv;
           } else {
             const float val = i < n ? expf(fmaf(acc[t][v], row_scale, -half_sq)) * inv_sqrt_m : 0.f;
-            if constexpr (FEATURE_MAJOR)
-              phi[(static_cast<size_t>(bh) * M + l) * ld + i] = val;
-            else
-              phi[(static_cast<size_t>(bh) * n + i) * M + l] = val;
+            phi[(static_cast<size_t>(bh) * M + l) * ld + i] = val;
           }
         }
       }
@@ -458,7 +430,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(FEATURE_MAJ
 // phi_l(x) = x_l + 1 for x_l > 0, exp(x_l) otherwise, d features, no
 // projections (of x / ||x|| when normalising; a zero row stays zero before
 // the map).  Block: 64 positions of one (source, batch-head), x staged through
-// LDS; same output layouts and queue-counter duty as k_feature_map.
+// LDS; same queue-counter duty as k_feature_map.  FEATURE_MAJOR writes its
+// layout, otherwise phi[bh][i][l] (lanes run along features).
 template <typename TX, bool FEATURE_MAJOR>
 __global__ __launch_bounds__(256) void k_feature_elu(const TX* __restrict__ x0, const TX* __restrict__ x1,
                                                      float* __restrict__ phi0, float* __restrict__ phi1, int n,
@@ -2141,42 +2114,26 @@ hipError_t launch_feature_map(bool bf16, const void* x0, const void* x1, const f
     if (bf16) {
       const uint16_t* a = static_cast<const uint16_t*>(x0);
       const uint16_t* c = static_cast<const uint16_t*>(x1);
-      if (feature_major)
-        hipLaunchKernelGGL((k_feature_map64<uint16_t, true>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, m,
-                           inv_sqrt_m, tiles_n, BH, fix_counts, np, trf);
-      else
-        hipLaunchKernelGGL((k_feature_map64<uint16_t, false>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, m,
-                           inv_sqrt_m, tiles_n, BH, fix_counts, np, trf);
+      hipLaunchKernelGGL((k_feature_map64<uint16_t>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, m,
+                         inv_sqrt_m, tiles_n, BH, fix_counts, np, trf);
     } else {
       const float* a = static_cast<const float*>(x0);
       const float* c = static_cast<const float*>(x1);
-      if (feature_major)
-        hipLaunchKernelGGL((k_feature_map64<float, true>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, m,
-                           inv_sqrt_m, tiles_n, BH, fix_counts, np, trf);
-      else
-        hipLaunchKernelGGL((k_feature_map64<float, false>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, m,
-                           inv_sqrt_m, tiles_n, BH, fix_counts, np, trf);
+      hipLaunchKernelGGL((k_feature_map64<float>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, m,
+                         inv_sqrt_m, tiles_n, BH, fix_counts, np, trf);
     }
     return hipGetLastError();
   }
   if (bf16) {
     const uint16_t* a = static_cast<const uint16_t*>(x0);
     const uint16_t* c = static_cast<const uint16_t*>(x1);
-    if (feature_major)
-      hipLaunchKernelGGL((k_feature_map<uint16_t, true>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, d, m,
-                         inv_sqrt_m, tiles_n, tiles_m, BH, fix_counts, np, trf);
-    else
-      hipLaunchKernelGGL((k_feature_map<uint16_t, false>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, d,
-                         m, inv_sqrt_m, tiles_n, tiles_m, BH, fix_counts, np, trf);
+    hipLaunchKernelGGL((k_feature_map<uint16_t>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, d, m,
+                       inv_sqrt_m, tiles_n, tiles_m, BH, fix_counts, np, trf);
   } else {
     const float* a = static_cast<const float*>(x0);
     const float* c = static_cast<const float*>(x1);
-    if (feature_major)
-      hipLaunchKernelGGL((k_feature_map<float, true>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, d, m,
-                         inv_sqrt_m, tiles_n, tiles_m, BH, fix_counts, np, trf);
-    else
-      hipLaunchKernelGGL((k_feature_map<float, false>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, d, m,
-                         inv_sqrt_m, tiles_n, tiles_m, BH, fix_counts, np, trf);
+    hipLaunchKernelGGL((k_feature_map<float>), grid, block, 0, st, a, c, W, phi0, phi1, H, n, ld, d, m,
+                       inv_sqrt_m, tiles_n, tiles_m, BH, fix_counts, np, trf);
   }
   return hipGetLastError();
 }

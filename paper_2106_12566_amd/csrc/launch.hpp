@@ -166,8 +166,8 @@ hipError_t launch_twiddles(float2* tw, int l2, hipStream_t st);
 hipError_t launch_spectrum(int l2, const float* b, const float2* tw, float2* Hs, float2* hnorm, int H, int n,
                            hipStream_t st);
 // nsrc sources (1 or 2) x0/x1 -> phi0/phi1.  feature_major: phi[bh][l][ld] for
-// positions < ld (zero beyond n); otherwise phi[bh][i][m].  fix_counts, if not
-// NULL, gets its BH + 1 entries cleared.  nprf: rows of x are divided by their
+// positions < ld (zero beyond n); otherwise phi[bh][i][d] (elu + 1 only: the
+// other maps of one source go through launch_phi).  fix_counts, if not NULL, gets its BH + 1 entries cleared.  nprf: rows of x are divided by their
 // l2 norm first.
 hipError_t launch_feature_map(bool bf16, const void* x0, const void* x1, const float* W, float* phi0,
                               float* phi1, int nsrc, bool feature_major, int ld, int BH, int H, int n, int d,
