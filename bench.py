@@ -28,6 +28,13 @@ sys.path.insert(0, ROOT)
 METRIC = "tokens/sec and ms/layer for RPE kernelized attn fwd; % HBM/MFMA roofline"
 PEAK_FP32_VECTOR_TFLOPS = 157.3   # MI355X published fp32 vector peak
 PEAK_HBM_GBS = 8000.0
+PEAK_FP16_MATRIX_TFLOPS = 2500.0  # dense
+
+
+def direct_peak_tflops(M: int) -> float:
+    """Peak of the direct route's flops: up to 256 features each takes three on the fp16 matrix
+    cores (operands in two terms), beyond that one on the fp32 ones (the vector peak)."""
+    return PEAK_FP16_MATRIX_TFLOPS / 3.0 if M <= 256 else PEAK_FP32_VECTOR_TFLOPS
 
 
 def direct_flops(B: int, H: int, n: int, d: int, m: int, b: np.ndarray) -> float:
@@ -290,7 +297,7 @@ def time_config(wid: int, steps: int, warmup: int, route: str, rows: int = 16) -
     else:
         tf = direct_flops(B, H, n, dd, m, d["b"]) / (stage[3] * 1e-3) / 1e12
         res.update({"exact_kernel_ms": stage[3], "exact_kernel_tflops": tf,
-                    "exact_kernel_frac": tf / PEAK_FP32_VECTOR_TFLOPS})
+                    "exact_kernel_frac": tf / direct_peak_tflops(m)})
     rng = np.random.default_rng([2106, 12566, 97, wid])
     sel = [(0, 0, 0), (B - 1, H - 1, n - 1)] + [(int(rng.integers(B)), int(rng.integers(H)), int(rng.integers(n)))
                                                 for _ in range(rows)]
@@ -439,11 +446,13 @@ def main() -> int:
         conv_ms = stages["conv_contract"]
         conv_gbs = conv_stage_bytes(B, H, n, dd, M, s_in) / (conv_ms * 1e-3) / 1e9
         roof = {"bound": "alu", "kernel": "k_conv_contract"}
+        peak = PEAK_FP32_VECTOR_TFLOPS
     else:
         flops = direct_flops(B, H, n, dd, M, d["b"])
-        conv_ms = stages["combine"]       # the exact-row kernel evaluates every row
+        conv_ms = stages["combine"]       # the direct kernel evaluates every row
         conv_gbs = None
-        roof = {"bound": "mfma", "kernel": "k_fixup"}
+        roof = {"bound": "mfma", "kernel": "k_direct" if M <= 256 else "k_fixup"}
+        peak = direct_peak_tflops(M)
     achieved_tflops = flops / (conv_ms * 1e-3) / 1e12
     print(f"bench: {ms_per_step:.3f} ms/step, stages {stages}", file=sys.stderr, flush=True)
 
@@ -470,8 +479,8 @@ def main() -> int:
                                               if route_used == "fft" and n <= BLOCK and fm == "prf" else None),
                    "exact_rows": krpe.attention_fwd_fixed_rows(ws, B, H, n, dd, m)},
         "roofline": {**roof, "achieved": achieved_tflops,
-                     "peak": PEAK_FP32_VECTOR_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved_tflops / PEAK_FP32_VECTOR_TFLOPS,
+                     "peak": peak, "unit": "TFLOP/s",
+                     "frac": achieved_tflops / peak,
                      "traffic": (measured_traffic("k_conv_contract", wl.name)
                                  if fm == "prf" and route_used == "fft" else None)},
     }

@@ -108,9 +108,11 @@ typedef enum {
  * count).  KRPE_ROUTE_FFT: the O(n log n) FFT
  * convolution of Section 3.2 (rows it cannot certify evaluated directly).
  * KRPE_ROUTE_DIRECT: every row evaluated directly from Eq. (10) as
- * (phi(Q) phi(K)^T o C) [v, 1] on fp32 MFMA tiles with fp64 totals, O(n^2);
- * faster than the FFT route for short sequences and many heads.  Same results to the
- * tolerance of the FFT route (the direct route is the more accurate).
+ * (phi(Q) phi(K)^T o C) [v, 1] on the matrix cores at fp32 accuracy (operands
+ * in two scaled fp16 terms up to 256 features, fp32 beyond) with fp64 totals,
+ * O(n^2); faster than the FFT route up to n = 8192 and often beyond.  Same
+ * results to the tolerance of the FFT route (the direct route is the more
+ * accurate).
  */
 #define KRPE_ROUTE_DIRECT 8u
 #define KRPE_ROUTE_FFT 16u
@@ -140,7 +142,8 @@ const char* krpe_last_error(void);
  *                             - 0.5 sum_a x[beta, h, i, a]^2 ) / sqrt(m)
  * x   : [B, H, n, d] in x_dtype        W : [H, m, d] fp32 (rows w_l)
  * phi : [B, H, n, m] fp32 (output)
- * Runs as an fp32 MFMA contraction with the exponential fused into its epilogue.
+ * Runs as a contraction on the matrix cores at fp32 accuracy (W and x in three
+ * bf16 terms) with the exponential fused into its epilogue.
  */
 krpe_status_t krpe_feature_map(const void* x, int x_dtype, const float* W, float* phi,
                                int B, int H, int n, int d, int m, void* stream);
@@ -270,8 +273,8 @@ size_t krpe_attention_bwd_workspace(int B, int H, int n, int d, int m, unsigned 
  * transposed Toeplitz matrix (the reversed b) where C^T appears, or, on the
  * direct route (m <= 256), a weighted product on the matrix cores like the
  * direct forward; the forward pass is recomputed inside (its exact-row
- * evaluation included).  Without a route bit the route follows the forward's
- * cost model, except that a stated causal mask without KRPE_NPRF keeps the
+ * evaluation included).  Without a route bit the faster one by a cost
+ * model of their own runs, except that a stated causal mask without KRPE_NPRF keeps the
  * FFT products: their rounding, spread over the sequence, reaches 1e-4 to
  * 4e-1 of a gradient's norm there (rows with small denominators), that of
  * KRPE_ROUTE_DIRECT's 1e-6.
