@@ -112,11 +112,9 @@ typedef enum {
  * in two scaled fp16 terms up to 256 features, fp32 beyond) with fp64 totals,
  * O(n^2); faster than the FFT route up to n = 8192 and often beyond.  Same
  * results to the tolerance of the FFT route (the direct route is the more
- * accurate).  Within one position the two fp16 terms span 2^50: where every key
- * opposes every query and their norms are well above d^(1/4) (w . x of a
- * position spread over more than 30), the products that remain are below that
- * span and up to 256 features lose digits; KRPE_ROUTE_FFT (or KRPE_NPRF, whose
- * positions have norm 1) does not.
+ * accurate).  Rows that two fp16 terms do not hold (keys that oppose their
+ * query, at norms well above d^(1/4)) are found by a bound on what they may
+ * have lost and evaluated in fp32, at several times the cost.
  */
 #define KRPE_ROUTE_DIRECT 8u
 #define KRPE_ROUTE_FFT 16u

@@ -350,7 +350,8 @@ krpe_status_t run_direct(const DirectLayout& L, char* w, const void* q, const vo
     return s;
   for (int e = 2; e < 4; ++e)
     if (krpe_status_t s = record(events, e, st)) return s;
-  if (krpe_status_t s = hip_check(launch_direct(L, w, v, bf16, z, nullptr, BHi, H, n, d, st), "direct launch"))
+  if (krpe_status_t s = hip_check(launch_direct(L, w, q, k, v, bf16, W, z, nullptr, BHi, H, n, d, m, nprf, kind, st),
+                                  "direct launch"))
     return s;
   return record(events, 4, st);
 }

@@ -459,7 +459,9 @@ hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, c
                                         Fl(L.crev), rrange, st);
       e != hipSuccess)
     return e;
-  if (hipError_t e = launch_direct(F, w, v, bf16, Fl(L.z), den, BH, H, n, d, st); e != hipSuccess) return e;
+  if (hipError_t e = launch_direct(F, w, q, k, v, bf16, W, Fl(L.z), den, BH, H, n, d, m, nprf, kFeatPrf, st);
+      e != hipSuccess)
+    return e;
 
   OpsArgs o{};
   o.v = v, o.dz = dz, o.z = Fl(L.z), o.den = den, o.kpow = I(L.kpow);

@@ -45,7 +45,8 @@ struct PrepArgs {
   float* crev;      // the table and ranges of c_{-t} (NULL: not wanted)
   int2* rrange;
   unsigned* fix;    // fix[BH] = rows evaluated exactly (all of them)
-  int* kpow;        // [BH][32 nblk] powers of phi(k) (NULL: not wanted)
+  int *qpow, *kpow; // [BH][32 nblk] powers of phi(q), phi(k) (kpow NULL: not wanted)
+  unsigned* flag;   // [BH + 1] cleared
   int BH, H, n, nblk, d, m, KS, ct_total, kind, nprf, tiles, phi_blocks, v_blocks;
   float inv_sqrt_m;
   double log2_m;  // -log2(sqrt(m))
@@ -185,8 +186,11 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
       emit(ks, v8);
     });
   }
+  if (src == 0 && pt == 0 && tid == 0) a.flag[bh] = 0u;
   if (!store) return;
-  if (src == 1) {
+  if (src == 0) {
+    if (lh == 0) a.qpow[block * kBlk + lr] = ex;
+  } else {
     if (a.kpow && lh == 0) a.kpow[block * kBlk + lr] = ex;
     // (positions without features have no power of their own)
     int E = any_phi ? ex : -400;
@@ -302,7 +306,10 @@ __device__ __forceinline__ void prep_c(const PrepArgs& a, int bid) {
     hi = max(max(wr[0].y, wr[1].y), max(wr[2].y, wr[3].y));
     a.crange[static_cast<size_t>(h) * chunks + ch] = make_int2(lo, hi);
     if (a.crev) a.rrange[static_cast<size_t>(h) * chunks + ch] = hi < 0 ? make_int2(lo, hi) : make_int2(len - 1 - hi, len - 1 - lo);
-    if (bid == 0) a.fix[a.BH] = static_cast<unsigned>(a.BH) * static_cast<unsigned>(a.n);
+    if (bid == 0) {
+      a.fix[a.BH] = static_cast<unsigned>(a.BH) * static_cast<unsigned>(a.n);
+      a.flag[a.BH] = 0u;
+    }
   }
 }
 
@@ -353,6 +360,9 @@ __global__ __launch_bounds__(64 * NW) void k_direct_parts(DirectArgs a) {
 
 // ------------------------------------------------------------ launchers --
 namespace {
+
+float inv_sqrt(int m) { return static_cast<float>(1.0 / std::sqrt(static_cast<double>(m))); }
+double log2_scale(int m) { return -0.5 * std::log2(static_cast<double>(m)); }  // -log2(sqrt(m))
 
 // k steps the kernels are compiled for
 int round_ks(int ks) {
@@ -467,6 +477,8 @@ DirectLayout direct_layout(int B, int H, int n, int d, int ks) {
   L.vflag = take(bh * L.nblk * sizeof(unsigned));
   L.ctab = take(static_cast<size_t>(H) * ctab_stride(n) * sizeof(float));
   L.crange = take(static_cast<size_t>(H) * ctab_chunks(n) * sizeof(int2));
+  L.qpow = take(bh * L.nblk * kBlk * sizeof(int));
+  L.flag = take((bh + 1) * sizeof(unsigned));
   const size_t rows = 32 * direct_waves(ks), tiles = (static_cast<size_t>(n) + rows - 1) / rows;
   const size_t cw = (L.ct_total >= 2 ? 64 : 32) + 1;
   L.part = take(L.nparts > 1 ? bh * L.passes * tiles * L.nparts * rows * cw * sizeof(double) : 0);
@@ -490,16 +502,19 @@ hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, con
   p.BH = BH, p.H = H, p.n = n, p.nblk = L.nblk, p.d = d, p.m = m, p.KS = L.ks, p.ct_total = L.ct_total;
   p.kind = kind, p.nprf = nprf ? 1 : 0;
   p.krec = reinterpret_cast<float*>(w + L.krec);
+  p.qpow = reinterpret_cast<int*>(w + L.qpow);
+  p.flag = reinterpret_cast<unsigned*>(w + L.flag);
   p.tiles = (n + 127) / 128;
   p.phi_blocks = 2 * BH * p.tiles;
   p.v_blocks = BH * p.tiles;
-  p.inv_sqrt_m = static_cast<float>(1.0 / std::sqrt(static_cast<double>(m)));
-  p.log2_m = -0.5 * std::log2(static_cast<double>(m));
+  p.inv_sqrt_m = inv_sqrt(m);
+  p.log2_m = log2_scale(m);
   return bf16 ? prep_go<uint16_t>(p, st) : prep_go<float>(p, st);
 }
 
-hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf16, float* z, double* den, int BH, int H,
-                         int n, int d, hipStream_t st) {
+hipError_t launch_direct(const DirectLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
+                         const float* W, float* z, double* den, int BH, int H, int n, int d, int m, bool nprf, int kind,
+                         hipStream_t st) {
   DirectArgs a{};
   a.X = reinterpret_cast<const uint4*>(w + L.x);
   a.Y = reinterpret_cast<const uint4*>(w + L.y);
@@ -514,6 +529,10 @@ hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf1
   a.tiles = (n + rows - 1) / rows;
   a.passes = L.passes, a.nparts = L.nparts;
   a.remap = direct_remap(BH);
+  a.q = q, a.k = k, a.W = W, a.m = m, a.kind = kind, a.nprf = nprf ? 1 : 0;
+  a.qpow = reinterpret_cast<const int*>(w + L.qpow);
+  a.flag = reinterpret_cast<unsigned*>(w + L.flag);
+  a.inv_sqrt_m = inv_sqrt(m), a.log2_m = log2_scale(m);
   if (L.ct_total >= 2)
     return bf16 ? direct_ks<1, 2>(L.ks, a, st) : direct_ks<2, 2>(L.ks, a, st);
   return bf16 ? direct_ks<1, 1>(L.ks, a, st) : direct_ks<2, 1>(L.ks, a, st);

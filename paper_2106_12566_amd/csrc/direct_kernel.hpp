@@ -8,18 +8,12 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "direct_args.hpp"
+#include "direct_exact.hpp"
 #include "features.hpp"
 #include "wprod.hpp"
 
 namespace krpe {
-
-// Record of a 32-key block, 64 words: [0, 32) 2^(e_j - E) per key, e_j the
-// power of phi(k_j) and E = word 32 (int); word 33 (int) the power of its
-// values.
-constexpr int kRecWords = 64, kRecE = 32, kRecV = 33;
-// S of two positions is at most 2^30 M in units of their powers: E carries 30
-// of them, so that P stays near c_{j-i}'s range.
-constexpr int kRecBias = 30;
 
 // --------------------------------------------------------------- direct --
 // One work-group: 32 NW consecutive rows of one (batch, head), each wave its
@@ -34,49 +28,15 @@ constexpr int kRecBias = 30;
 // The power of phi(q_i) cancels in z.  P's small term is stored unscaled (its
 // largest entry is at 2^14, terms below 2^-40 of that are lost).  A wave skips
 // the blocks outside its own rows' range (it still stages and meets the
-// barriers).
-struct DirectArgs {
-  const uint4 *X, *Y, *Z;
-  const float* krec;
-  const unsigned* vflag;
-  const float* ctab;
-  const int2* crange;
-  const void* v;
-  float* z;
-  double* den;       // denominators in units of the queries' powers (or NULL)
-  const int* rpow;   // MODE 1, 2: powers of the rows [BH][32 nblk]
-  int ldz;           // MODE 1, 2: row length of z; 0: z as fp32 S fragments of out_ks k steps
-  int out_ks;
-  const uint4 *X2, *Y2;  // MODE 2: the second pair of operands ([block][KS2][2])
-  const float* krec2;    // its keys' records
-  const int* rpow2;      // and rows' powers
-  float* pdc;            // diagonal sums [BH][nblk row blocks][32 (nblk + 1)]
-  double* part;
-  int BH, H, n, nblk, d, ct_total, tiles, passes, nparts, remap;
-};
+// barriers).  The forward pass sums the weights of S too (kRowTau's test, 1.5 to 2 %
+// of a long call: 1.98 -> 2.01 ms at 96 heads, n = 4096, m = 128); a branch on
+// each block's least S instead costs 2.5 to 4 %, and so does holding anything for
+// the rows that fail through the loop.
 
 // Whether the work-groups take XCD order: one XCD's L2 then serves the
 // work-groups of a head; with few heads the plain order spreads the row tiles,
 // whose lengths differ, over the XCDs.
 inline bool direct_remap(int BH) { return BH >= 16 || BH % 8 == 0; }
-
-// Key blocks [lo, hi) of rows r0 .. r1 under the head's range of finite b.
-__device__ __forceinline__ void key_blocks(int2 br, int n, int r0, int r1, int& lo, int& hi) {
-  const int jlo = max(0, r0 + br.x - (n - 1)), jhi = min(n - 1, r1 + br.y - (n - 1));
-  lo = jhi >= jlo ? jlo >> 5 : 0;
-  hi = jhi >= jlo ? (jhi >> 5) + 1 : 0;
-}
-// Columns c .. c + 3 of a row of d (16-byte aligned rows when d is a multiple of 4).
-__device__ __forceinline__ void store4(float* __restrict__ row, int c, int d, float x, float y, float z, float w) {
-  if (d % 4 == 0) {
-    if (c < d) *reinterpret_cast<float4*>(row + c) = make_float4(x, y, z, w);
-  } else {
-    if (c < d) row[c] = x;
-    if (c + 1 < d) row[c + 1] = y;
-    if (c + 2 < d) row[c + 2] = z;
-    if (c + 3 < d) row[c + 3] = w;
-  }
-}
 
 // Has the loads of x complete here: a first use inside the loop would wait
 // there, every time, for all outstanding loads, the staged ones too.
@@ -138,8 +98,12 @@ __device__ __forceinline__ void s_schedule() {
 // MODE 0: the forward pass.  MODE 1: the plain product, fp32 totals, rows
 // scaled by their powers.  MODE 2: as MODE 1, and the diagonal sums of
 // (X2 Y2^T) o (X Y^T) in pass 0 (bwd_direct.hip).
+// Waves per SIMD: what the main loop's registers allow (exact_rows would take
+// more of them for its loads).
+template <int MODE, int KS, int CT>
+constexpr int kDirectWaves = MODE == 0 && CT == 1 && KS <= 2 ? 4 : MODE == 0 && KS * CT <= 4 ? 3 : 2;
 template <int MODE, int NSZ, int KS, int KS2, int CT, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void k_direct(DirectArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirectWaves<MODE, KS, CT>))) void k_direct(DirectArgs a) {
   using TV = typename std::conditional<NSZ == 1, uint16_t, float>::type;
   using Total = typename std::conditional<MODE == 0, double, float>::type;
   constexpr int kRows = 32 * NW;
@@ -152,6 +116,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   __shared__ __align__(16) float strip[2][kStrip];
   constexpr int kDS = 33;  // floats per diagonal: writes across the lanes and reads fall in distinct banks
   __shared__ float diag[MODE == 2 ? NW : 1][MODE == 2 ? 64 * kDS : 1];
+  __shared__ unsigned redo;  // MODE 0: waves whose rows are evaluated again,
+  __shared__ double den[MODE == 0 ? 32 : 1];  // and one's denominators
   float dcarry = 0.f;  // sums of the diagonals below the last block's, in lanes 0 .. 31
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lh = lane >> 5;
@@ -242,8 +208,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       }
     });
   };
+  if (MODE == 0 && tid == 0) redo = 0u;
   Total zt[CT][16];
-  double dsum = 0.0;
+  double dsum = 0.0, wsum = 0.0;
+  int vmost = -1000;  // largest power of the values
 #pragma unroll
   for (int t = 0; t < CT; ++t)
 #pragma unroll
@@ -275,19 +243,27 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       }
       s_schedule<KS>();
     }
-    const int kexp = __float_as_int(rec[kRecE]);
+    const int kexp = __builtin_amdgcn_readfirstlane(__float_as_int(rec[kRecE]));
+    const int vexp = __builtin_amdgcn_readfirstlane(__float_as_int(rec[kRecV]));
     // P: lane row lr, keys 8 (e / 4) + 4 lh + e % 4
     float p[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) p[e] = fmaf(s1[e], kLoInv, s[e]);
+    // w4: sums of the weights of S in P (they wait for no product)
+    float w4[4] = {0.f, 0.f, 0.f, 0.f};
     if constexpr (kAhead) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) p[e] = fmaf(s1[e], kLoInv, s[e]) * k16[e];
+      for (int e = 0; e < 16; ++e) {
+        if (MODE == 0) w4[e & 3] = fmaf(k16[e], c16[e], w4[e & 3]);
+        p[e] *= k16[e];
+      }
     } else {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const float4 kr = *reinterpret_cast<const float4*>(rec + 8 * g + 4 * lh);
         const float k4[4] = {kr.x, kr.y, kr.z, kr.w};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) p[4 * g + j] = fmaf(s1[4 * g + j], kLoInv, s[4 * g + j]) * k4[j];
+        for (int j = 0; j < 4; ++j) p[4 * g + j] *= k4[j];
       }
     }
     if constexpr (MODE == 2) {
@@ -325,7 +301,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
 #pragma unroll
     for (int e = 0; e < 16; ++e) p[e] *= kAhead ? c16[kAhead ? e : 0] : cs[8 * (e >> 2) + (e & 3)];
-    if (32 * blk + 32 > n) {  // uniform: keys past n (their fragments are zero, but c may be infinite)
+    if (32 * blk + 32 > n) {  // uniform: keys past n (of no weight, but c may be infinite)
 #pragma unroll
       for (int e = 0; e < 16; ++e)
         if (32 * blk + 8 * (e >> 2) + 4 * lh + (e & 3) >= n) p[e] = 0.f;
@@ -341,11 +317,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     // (zero and NaN maxima: 2^15, any power serves)
     const int ex = max(__builtin_amdgcn_frexp_expf(mx), -100) - 15;
     const float sc = __int_as_float((127 - ex) << 23);
-    const int zexp = kexp + __float_as_int(rec[kRecV]) + ex;
+    const int zexp = kexp + vexp + ex;
     Total zs;
     if constexpr (MODE == 0) {
       zs = exp2_int(zexp);
       dsum = fma(static_cast<double>(ds), exp2_int(kexp), dsum);
+      if constexpr (!kAhead) {
+        // (apart from P, whose registers it would take: it spills)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float4 kr = *reinterpret_cast<const float4*>(rec + 8 * g + 4 * lh);
+          const float k4[4] = {kr.x, kr.y, kr.z, kr.w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) w4[0] = fmaf(k4[j], cs[8 * g + j], w4[0]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const double ws = static_cast<double>((w4[0] + w4[1]) + (w4[2] + w4[3])) * exp2_int(kexp);
+      wsum += ws;
+      vmost = max(vmost, vexp);
     } else {
       zs = ldexpf(1.f, zexp);
     }
@@ -374,8 +365,48 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       }
     }
   }
-  if (wrow0 >= n) return;  // uniform per wave; no barrier follows
   const int i = wrow0 + lr;
+  if constexpr (MODE == 0) {
+    // a lane's sums cover this half-wave's keys, its columns those of its half
+    dsum += __shfl_xor(dsum, 32);
+    wsum += __shfl_xor(wsum, 32);
+    // The test with every S taken as doubtful and a few columns (trigonometric
+    // features are as large as their position's amplitude allows and S cancels:
+    // its size does not say that a term was not held) ...
+    const double off = kDoubtErr<KS> * wsum, offn = off * exp2_int(vmost + 15);
+    double num = fmax(fmax(fabs(zt[0][0]), fabs(zt[0][1])), fmax(fabs(zt[0][2]), fabs(zt[0][3])));
+    bool again = false;
+    if (__builtin_expect(a.kind != kFeatTrf && __any(i < n && !(off <= kRowTau * dsum && offn <= kRowTau * num)), 0)) {
+      // ... and in full, where that does not pass
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) num = fmax(num, fabs(zt[t][e]));
+      num = fmax(num, __shfl_xor(num, 32));
+      again = !rows_held<KS>(a, bh, wrow0, max(b0, wlo), min(b1, whi), dsum, num);
+    }
+    if (__builtin_expect(again, 0)) {
+      if (lane == 0) atomicOr(&redo, 1u << wave);
+    } else if (wrow0 < n) {
+      store_rows<CT, NW>(a, bh, pass, tile, pi, wave, zt, dsum);
+    }
+    __syncthreads();
+    if (__builtin_expect(redo != 0u, 0)) {
+      // (the arguments are read anew: none is held through the loop above for this)
+      const DirectArgs* ap = (const DirectArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+s"(ap));
+      if (ap->flag && tid == 0) ap->flag[bh] = ap->flag[ap->BH] = 1u;
+      const unsigned mask = __builtin_amdgcn_readfirstlane(redo);
+#pragma unroll 1
+      for (int w = 0; w < NW; ++w) {
+        if ((mask >> w & 1u) == 0u) continue;
+        exact_rows<TV, KS, CT, NW>(*ap, reinterpret_cast<float4*>(&tiles_lds[0][0]), den, bh, pass, tile, pi, w, b0,
+                                   b1);
+        if (wave == w) dsum = den[lr];
+      }
+    }
+  }
+  if (wrow0 >= n) return;  // uniform per wave; no barrier follows
   if constexpr (MODE > 0) {
     const float rs = ldexpf(1.f, a.rpow[xblk * kBlk + lr]);
     if (MODE == 2 && lh == 0 && whi > wlo)  // the diagonals below the last block's
@@ -404,35 +435,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
     }
   } else {
-    dsum += __shfl_xor(dsum, 32);  // the other half-wave's keys of row lr
-    // this lane: row i, columns 32 (pass CT + t) + 8 (e / 4) + 4 lh + e % 4
-    constexpr int cw = CT * 32 + 1;
-    const int c0 = pass * CT * 32 + 4 * lh;
-    double* __restrict__ part = a.part +
-                                ((static_cast<size_t>(bh * a.passes + pass) * a.tiles + tile) * a.nparts + pi) *
-                                    (kRows * cw) +
-                                32 * wave + lr;  // [column][row]
+    double* __restrict__ part = part_of<CT, NW>(a, bh, pass, tile, pi) + 32 * wave + lr;  // [column][row]
     float* __restrict__ zr = a.z + (static_cast<size_t>(bh) * n + i) * a.d;
-    if (a.nparts == 1) {
-      const double inv = 1.0 / dsum;
-      if (i < n) {
-#pragma unroll
-        for (int t = 0; t < CT; ++t)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const Total* __restrict__ q = &zt[t][4 * g];
-            store4(zr, c0 + 32 * t + 8 * g, a.d, static_cast<float>(q[0] * inv), static_cast<float>(q[1] * inv),
-                   static_cast<float>(q[2] * inv), static_cast<float>(q[3] * inv));
-          }
-        if (pass == 0 && lh == 0 && a.den) a.den[static_cast<size_t>(bh) * n + i] = dsum;
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < CT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) part[(32 * t + 8 * (e >> 2) + 4 * lh + (e & 3)) * kRows] = zt[t][e];
-      if (lh == 0) part[CT * 32 * kRows] = dsum;
-    }
     // Values that are not finite (stored as zero fragments, their blocks
     // flagged): P v added in fp64, one key at a time; rare.
     const unsigned* __restrict__ vf = a.vflag + hb;
@@ -458,11 +462,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         // S of (row, key): this lane half's slots, then the other half's
         float s = 0.f;
         const uint4* __restrict__ yp = a.Y + (hb + blk) * NY * kFragLanes + 32 * lh + (key & 31);
-#pragma unroll
+        const uint4* __restrict__ xp = a.X + xblk * NY * kFragLanes + lane;
         for (int ks = 0; ks < KS; ++ks) {
+          const uint4 xh = xp[(ks * 2 + 0) * kFragLanes], xl = xp[(ks * 2 + 1) * kFragLanes];
           const uint4 yh = yp[(ks * 2 + 0) * kFragLanes], yl = yp[(ks * 2 + 1) * kFragLanes];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) s = fmaf(value(x[ks][0], x[ks][1], j), value(yh, yl, j), s);
+          for (int j = 0; j < 8; ++j) s = fmaf(value(xh, xl, j), value(yh, yl, j), s);
         }
         s += __shfl_xor(s, 32);
         if (lh != 0 || i >= n || ct[key - i] == 0.f) continue;  // (a masked key reaches no row)

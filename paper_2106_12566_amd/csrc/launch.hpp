@@ -102,6 +102,8 @@ struct DirectLayout {
   size_t vflag;  // uint  [BH][nblk]  blocks with values that are not finite
   size_t ctab;   // float [H][ctab_stride(n)]  c = exp(b), zero-padded
   size_t crange; // int2  [H][ctab_chunks(n)]  range of finite b per table chunk
+  size_t qpow;   // int   [BH][32 nblk]  powers of two of phi(q)
+  size_t flag;   // uint  [BH + 1]  heads with rows evaluated in fp32; any such head
   size_t part;   // double [BH][passes][tiles][nparts][columns + 1][rows] partial sums
   size_t total;
 };
@@ -114,8 +116,9 @@ hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, con
                               const float* b, const float* W, int BH, int H, int n, int d, int m, bool nprf, int kind,
                               int* kpow, float* crev, int2* rrange, hipStream_t st);
 // den (or NULL): the denominators, in units of the power of each phi(q_i).
-hipError_t launch_direct(const DirectLayout& L, char* w, const void* v, bool bf16, float* z, double* den, int BH, int H,
-                         int n, int d, hipStream_t st);
+hipError_t launch_direct(const DirectLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
+                         const float* W, float* z, double* den, int BH, int H, int n, int d, int m, bool nprf, int kind,
+                         hipStream_t st);
 
 // Workspace of the direct backward pass (csrc/bwd_direct.hip): the direct
 // forward's first.

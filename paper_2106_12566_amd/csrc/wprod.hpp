@@ -11,16 +11,13 @@
 //
 // e from the largest |a| that shares the power (the features of one position;
 // the block of 32 positions for Z), which is brought to [2^14, 2^15).  The two
-// terms represent 2^-e a to 2^-24 of itself down to 2^-13, 28 binades below
+// terms represent 2^-e a to 2^-23 of itself down to 2^-13, 28 binades below
 // that largest element, and to an absolute 2^-36 below.  So an S whose terms
-// all pair one position's largest features with the other's smallest loses
-// accuracy: below about 2^4 M in units of the two powers (2^30 M at most) it is
-// no longer good to fp32's last bits.  Inputs scaled by d^(-1/4) keep clear of that,
-// also where all keys oppose all queries (z 1.3e-7 of its norm off); queries
-// and keys of N(0, 0.6^2) elements at d = 64 that are nearly all alike and
-// opposite give 5.8e-6, of N(0, 1) 5e-2 (fp32 operands 1.0e-6 and 2.4e-6).
-// Random ones of N(0, 1) elements stay at 6e-7.  A product takes the
-// three terms h h, h l and l h (l l is below 2^-23 of it): three fp16 MFMAs of
+// all pair one position's largest features with the other's smallest (keys that
+// oppose the query, norms well above d^(1/4)) is not held; the forward pass
+// bounds what each row may have lost that way and evaluates the rows that do not
+// pass in fp32 from q, k and W (direct_args.hpp, direct_exact.hpp).  A product takes the
+// three terms h h, h l and l h (l l is below 2^-22 of it): three fp16 MFMAs of
 // 16 contraction steps, 32 cycles each, against eight fp32 MFMAs of two, 64
 // cycles each, 5.3 times the fp32 matrix rate.  Products are exact and sums
 // are fp32 in the MFMA; h h and the two small products run in accumulators of

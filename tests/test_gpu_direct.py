@@ -108,6 +108,60 @@ def test_direct_values_not_finite(gpu_lib, dt, n, d, parts):
     assert np.max(np.where(want, 0.0, np.abs(np.where(want, 0.0, z) - clean)) / scale) <= TOL
 
 
+def _opposed(d, scale, kind, mask, n=200, m=128, dt="f32"):
+    """Queries and keys for which every product phi_l(q) phi_l(k) a row sums pairs a large feature with
+    one far below its position's largest: k = -q, a common direction with `kind`'s share of noise, or
+    independent draws (where a mask leaves a row few keys, some rows see only such ones)."""
+    dd = synth.custom(1, 2, n, d, m, seed=d + int(100 * scale) + n, qkv_dtype=dt)
+    rng = np.random.default_rng([n, d, int(100 * scale)])
+    draw = lambda *shape: (scale * rng.standard_normal(shape)).astype(np.float32)
+    q = draw(1, 2, n, d)
+    if kind == "opposite":
+        k = -q
+    elif kind == "aligned":
+        u = draw(1, 2, 1, d)
+        q, k = u + 0.1 * q, -u + 0.1 * draw(1, 2, n, d)
+    else:
+        k = draw(1, 2, n, d)
+    if dt == "bf16":
+        q, k = (torch.from_numpy(x).to(torch.bfloat16).float().numpy() for x in (q, k))
+    dd["q"], dd["k"] = np.ascontiguousarray(q), np.ascontiguousarray(k)
+    t = np.arange(-(n - 1), n)
+    if mask == "causal":
+        dd["b"][:, t > 0] = -np.inf
+    elif mask == "window":
+        dd["b"][:, np.abs(t) > 2] = -np.inf
+    return dd
+
+
+OPPOSED = [
+    (64, 0.8, "aligned", "none", 200, 128, "f32"), (64, 1.0, "aligned", "none", 130, 128, "f32"),
+    (64, 1.0, "aligned", "causal", 200, 64, "bf16"), (64, 1.0, "aligned", "window", 97, 200, "f32"),
+    (128, 0.6, "aligned", "none", 200, 128, "f32"), (128, 0.6, "aligned", "causal", 33, 256, "bf16"),
+    (64, 0.8, "opposite", "window", 200, 128, "f32"), (64, 1.0, "opposite", "causal", 160, 16, "f32"),
+    (64, 1.2, "random", "causal", 300, 128, "f32"), (64, 1.2, "random", "window", 300, 128, "bf16"),
+    (31, 1.0, "aligned", "none", 129, 40, "f32"), (64, 1.0, "aligned", "none", 2050, 128, "f32"),  # (row tiles in parts)
+]
+
+
+@pytest.mark.parametrize("d,scale,kind,mask,n,m,dt", OPPOSED)
+def test_direct_opposed(gpu_lib, d, scale, kind, mask, n, m, dt):
+    """Rows whose S is below what two fp16 terms hold: they keep the accuracy of the others, on the
+    default route too.  Exponents of phi are up to 2^6 to 2^7 here (norms up to d^(1/2) and more), up to
+    twice those that TOL is derived from; the rows are the exact features' (fp32 sums over d), so
+    the bound is 2 TOL."""
+    dd = _opposed(d, scale, kind, mask, n, m, dt)
+    print(f"opposed d={d} scale={scale} {kind} {mask} n={n} m={m} {dt}", flush=True)
+    q, k, v, b, W = (to_gpu(dd[x], dt) if x in "qkv" else to_gpu(dd[x]) for x in ("q", "k", "v", "b", "W"))
+    ref, _ = oracle.attention(dd["q"], dd["k"], dd["v"], dd["b"], dd["W"])
+    for route in ("auto", "direct"):
+        z = gpu_lib.attention_fwd(q, k, v, b, W, route=route, causal=mask == "causal").cpu().numpy()
+        assert np.all(np.isfinite(z))
+        err = rownorm_err(z, ref)
+        print(f"  {route}: {err:.3e}", flush=True)
+        assert err <= 2 * TOL, err
+
+
 BWD_CASES = [
     # n, d, m: 32-position blocks and row tiles (128 and 256 rows); d + 1 contracted columns around the
     # compiled 3, 5 and 9 steps of 16; column tiles and passes; feature counts around 64, 128 and 256
