@@ -30,7 +30,9 @@ namespace krpe {
 //       see their order; unused slots are zero, as are positions >= n).
 //  v    128 positions of one batch-head as Z fragments.  An element that is
 //       not finite is stored as zero and its block flagged: k_direct adds
-//       its contribution separately (a split of it would give inf - inf).
+//       its contribution separately (a split of it would give inf - inf),
+//       as it does elements 2^31 (bf16: 2^32) and more below their
+//       block's largest, whose power they share.
 //  c    2048 entries of one head's table and the range of its finite ones.
 // The features are written once and read once per 128 rows; at 96 heads, n =
 // 4096, m = 128 the kernel is bound by its 0.5 GB of stores.
@@ -213,7 +215,7 @@ __device__ __forceinline__ void prep_v(const PrepArgs& a, int bid) {
   const TX* __restrict__ v = static_cast<const TX*>(a.v) + static_cast<size_t>(bh) * n * d;
   const size_t block = static_cast<size_t>(bh) * a.nblk + blk;
   uint4* __restrict__ out = a.Z + block * a.ct_total * 2 * NSZ * kFragLanes + lane;
-  bool odd = false;
+  bool odd = false, lost = false;
   float x[kMaxD / 32][16];
   float mx = 0.f;
 #pragma unroll
@@ -248,16 +250,21 @@ __device__ __forceinline__ void prep_v(const PrepArgs& a, int bid) {
     for (int k2 = 0; k2 < 2; ++k2) {
       float v8[8];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) v8[t] = ldexpf(x[ct][8 * k2 + t], -ex);
+      for (int t = 0; t < 8; ++t) {
+        v8[t] = ldexpf(x[ct][8 * k2 + t], -ex);
+        const float small = apart<NSZ>(v8[t]);
+        lost |= small != 0.f;
+        v8[t] -= small;
+      }
       uint4 hh, ll;
       split_f16x8(v8, kLoScale, hh, ll);
       out[((ct * 2 + k2) * NSZ + 0) * kFragLanes] = hh;
       if (NSZ > 1) out[((ct * 2 + k2) * NSZ + NSZ - 1) * kFragLanes] = ll;
     }
   }
-  const bool any = __any(odd);
+  const unsigned any = (__any(odd) ? 1u : 0u) | (__any(lost) ? 2u : 0u);
   if (lane == 0) {
-    a.vflag[block] = any ? 1u : 0u;
+    a.vflag[block] = any;
     a.krec[block * kRecWords + kRecV] = __int_as_float(ex);
   }
 }

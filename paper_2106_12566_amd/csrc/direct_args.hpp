@@ -16,8 +16,9 @@ constexpr int kRecWords = 64, kRecE = 32, kRecV = 33;
 constexpr int kRecBias = 30;
 // Rows of the forward pass that two fp16 terms do not hold (wprod.hpp).  A term is
 // off by at most 2^-36 of its position's unit where it does not hold its feature
-// to 2^-23, so an S by at most kDoubtErr = 16 KS 2^-20 for features up to 2^15; an S
-// below kDoubt, 22 bits above that, is doubtful.  A row is held if what its
+// to 2^-23, and the product l l of such a term by 2^-37 of that unit times the
+// other's, so an S by less than kDoubtErr = 32 KS 2^-20 for features up to 2^15; an S
+// below kDoubt, 21 bits above that, is doubtful.  A row is held if what its
 // doubtful entries may be off by, weighted as in the sums, is at most kRowTau of
 // its denominator and, with their values, of its largest numerator.  k_direct
 // tests this with every entry taken as doubtful (inputs scaled by d^(-1/4) pass by
@@ -27,7 +28,7 @@ constexpr double kRowTau = 0x1p-20;
 template <int KS>
 constexpr float kDoubt = 64.f * KS;
 template <int KS>
-constexpr double kDoubtErr = 16.0 * KS * 0x1p-20;
+constexpr double kDoubtErr = 32.0 * KS * 0x1p-20;
 
 struct DirectArgs {
   const uint4 *X, *Y, *Z;

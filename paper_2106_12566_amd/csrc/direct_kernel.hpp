@@ -437,12 +437,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
   } else {
     double* __restrict__ part = part_of<CT, NW>(a, bh, pass, tile, pi) + 32 * wave + lr;  // [column][row]
     float* __restrict__ zr = a.z + (static_cast<size_t>(bh) * n + i) * a.d;
-    // Values that are not finite (stored as zero fragments, their blocks
-    // flagged): P v added in fp64, one key at a time; rare.
+    // Values that are not finite and those too small for their block's power
+    // (rows evaluated again have these), stored as zeros, their blocks flagged:
+    // P v added in fp64, one key at a time; rare.
     const unsigned* __restrict__ vf = a.vflag + hb;
     const int f0 = max(b0, wlo), f1 = min(b1, whi);
+    const unsigned kinds = (redo >> wave & 1u) != 0u ? 1u : 3u;
     bool odd = false;
-    for (int blk = f0 + lane; blk < f1; blk += 64) odd |= vf[blk] != 0u;
+    for (int blk = f0 + lane; blk < f1; blk += 64) odd |= (vf[blk] & kinds) != 0u;
     if (!__any(odd)) return;
     __threadfence();  // the rows stored above are read back below, by other lanes
     const TV* __restrict__ v = static_cast<const TV*>(a.v) + static_cast<size_t>(bh) * n * a.d;
@@ -453,16 +455,23 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
       return term_value(w[j >> 1], u[j >> 1], j & 1);
     };
     for (int blk = f0; blk < f1; ++blk) {
-      if (vf[blk] == 0u) continue;
+      if ((vf[blk] & kinds) == 0u) continue;
       const float* __restrict__ rec = a.krec + (hb + blk) * kRecWords;
+      const int vexp = __float_as_int(rec[kRecV]);
+      auto missing = [&](int key, int c) {  // what the sums lack of v[key][c]
+        const float x1 = to_f32(v[static_cast<size_t>(key) * a.d + c]);
+        if (!isfinite(x1)) return x1;
+        return kinds == 1u ? 0.f : ldexpf(apart<NSZ>(ldexpf(x1, -vexp)), vexp);
+      };
       for (int key = 32 * blk; key < min(32 * blk + 32, n); ++key) {
         bool any = false;
-        for (int c = cbeg + lane; c < cend; c += 64) any |= !isfinite(to_f32(v[static_cast<size_t>(key) * a.d + c]));
+        for (int c = cbeg + lane; c < cend; c += 64) any |= missing(key, c) != 0.f;
         if (!__any(any)) continue;
         // S of (row, key): this lane half's slots, then the other half's
         float s = 0.f;
         const uint4* __restrict__ yp = a.Y + (hb + blk) * NY * kFragLanes + 32 * lh + (key & 31);
         const uint4* __restrict__ xp = a.X + xblk * NY * kFragLanes + lane;
+#pragma unroll 2
         for (int ks = 0; ks < KS; ++ks) {
           const uint4 xh = xp[(ks * 2 + 0) * kFragLanes], xl = xp[(ks * 2 + 1) * kFragLanes];
           const uint4 yh = yp[(ks * 2 + 0) * kFragLanes], yl = yp[(ks * 2 + 1) * kFragLanes];
@@ -473,8 +482,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
         if (lh != 0 || i >= n || ct[key - i] == 0.f) continue;  // (a masked key reaches no row)
         const double p = static_cast<double>(s * rec[key & 31] * ct[key - i]) * exp2_int(__float_as_int(rec[kRecE]));
         for (int c = cbeg; c < cend; ++c) {
-          const float x1 = to_f32(v[static_cast<size_t>(key) * a.d + c]);
-          if (isfinite(x1)) continue;
+          const float x1 = missing(key, c);
+          if (x1 == 0.f) continue;
           if (a.nparts == 1)
             zr[c] = static_cast<float>(zr[c] + p * x1 / dsum);
           else

@@ -99,7 +99,7 @@ struct DirectLayout {
   size_t x, y;   // phi(q), phi(k): S fragments [BH][nblk][ks][2]
   size_t z;      // v: Z fragments [BH][nblk][ct_total][2][2 or 1]
   size_t krec;   // float [BH][nblk][64]  powers of two of the keys and values of each block
-  size_t vflag;  // uint  [BH][nblk]  blocks with values that are not finite
+  size_t vflag;  // uint  [BH][nblk]  blocks with values that are not finite (1), too small for their block's power (2)
   size_t ctab;   // float [H][ctab_stride(n)]  c = exp(b), zero-padded
   size_t crange; // int2  [H][ctab_chunks(n)]  range of finite b per table chunk
   size_t qpow;   // int   [BH][32 nblk]  powers of two of phi(q)

@@ -124,6 +124,14 @@ __device__ __forceinline__ void split_f16x8(const float (&x)[8], float lo, uint4
   split_f16(x[4], x[5], lo, h.z, l.z);
   split_f16(x[6], x[7], lo, h.w, l.w);
 }
+// An element of Z too small for its power's terms (the power's largest is 2^31 or
+// more above it) is not split but added apart, else zero.  TERMS = 2: above 2^-16
+// the terms hold it, and the product l l that is dropped, to 2^-20 of it; 1 (bf16
+// values): above 2^-17 it is an fp16 number.
+template <int TERMS>
+__device__ __forceinline__ float apart(float a) {
+  return fabsf(a) < (TERMS == 2 ? 0x1p-16f : 0x1p-17f) ? a : 0.f;
+}
 // the value of half j (0, 1) of a pair of terms, l scaled by kLoScale
 __device__ __forceinline__ float term_value(uint32_t h, uint32_t l, int j) {
   const halfx2 hp = __builtin_bit_cast(halfx2, h), lp = __builtin_bit_cast(halfx2, l);

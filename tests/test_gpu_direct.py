@@ -87,6 +87,41 @@ def test_direct_powers_far_apart(gpu_lib):
     assert err <= 8 * TOL, err
 
 
+@pytest.mark.parametrize("dt,n,d,features,nprf,bias", [
+    ("bf16", 100, 64, "prf", False, "causal"), ("f32", 100, 64, "prf", False, "causal"),
+    ("bf16", 70, 33, "trf", True, "decay"), ("f32", 200, 128, "elu", False, "causal"),
+    ("bf16", 2100, 24, "prf", True, "causal"),  # row tiles in parts
+])
+def test_direct_values_far_apart(gpu_lib, dt, n, d, features, nprf, bias):
+    """Values within one 32-key block whose sizes differ by more than fp16 terms with one power hold, by
+    key and by column: each is in the results of the rows that see it.  Weights and values are
+    positive (TRF under NPRF: nearly), so every element of z is a sum without cancellation and TOL,
+    a bound on the relative error of each weight and value, holds element by element."""
+    m = d if features == "elu" else 32
+    dd = synth.custom(1, 2, n, d, m, seed=n + d, qkv_dtype=dt, bias=bias, bias_sigma=0.3)
+    rng = np.random.default_rng([n, d])
+    v = 1.0 + rng.random((1, 2, n, d))
+    v[..., ::3] *= 2.0 ** -36  # whole columns
+    for j, e in ((5, 40), (17, -33), (37, 44), (50, 30), (n - 2, 35)):
+        v[:, :, j] *= 2.0 ** e
+    v = v.astype(np.float32)
+    if dt == "bf16":
+        v = torch.from_numpy(v).to(torch.bfloat16).float().numpy()
+    dd["v"] = v
+    q, k, vv, b = to_gpu(dd["q"], dt), to_gpu(dd["k"], dt), to_gpu(v, dt), to_gpu(dd["b"])
+    W = None if features == "elu" else to_gpu(dd["W"])
+    print(f"values far apart {dt} n={n} d={d} {features}", flush=True)
+    z = gpu_lib.attention_fwd(q, k, vv, b, W, nprf=nprf, features=features, route="direct",
+                              causal=bias == "causal").cpu().numpy()
+    ref, _ = oracle.attention(dd["q"], dd["k"], v, dd["b"], None if W is None else dd["W"], nprf=nprf, kind=features)
+    if bias == "causal":  # row 0 is v_0, row 4 does not see the large values behind it
+        np.testing.assert_allclose(z[:, :, 0], v[:, :, 0], rtol=TOL)
+    rel = np.abs(z - ref) / np.abs(ref)
+    err = float(np.max(rel))
+    print(f"  elementwise {err:.3e} at {np.unravel_index(np.argmax(rel), rel.shape)}", flush=True)
+    assert err <= TOL, err
+
+
 @pytest.mark.parametrize("dt,n,d,parts", [("f32", 100, 64, False), ("bf16", 160, 40, False), ("f32", 2100, 24, True)])
 def test_direct_values_not_finite(gpu_lib, dt, n, d, parts):
     """An infinite or NaN value reaches its column of the rows that see it and nothing else."""
