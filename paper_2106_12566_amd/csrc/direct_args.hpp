@@ -20,15 +20,20 @@ constexpr int kRecBias = 30;
 // other's, so an S by less than kDoubtErr = 32 KS 2^-20 for features up to 2^15; an S
 // below kDoubt, 21 bits above that, is doubtful.  A row is held if what its
 // doubtful entries may be off by, weighted as in the sums, is at most kRowTau of
-// its denominator and, with their values, of its largest numerator.  k_direct
-// tests this with every entry taken as doubtful (inputs scaled by d^(-1/4) pass by
-// 2^9 and more), rows_held in full, and exact_rows evaluates the rows of a wave
-// that fails.
+// its denominator and, with their values, of its largest numerator.
+// Two more losses count: kUnderflow, in units of the block's power, for each entry
+// whose weight may have left fp32's range (b near the range's end, a key far below
+// one of its block that the row does not see), and kSplitFloor of the block's
+// largest entry, below which P's terms lose its others, with its largest value.
+// k_direct tests this with every entry taken as doubtful (inputs scaled by d^(-1/4)
+// pass by 2^9 and more), rows_held in full, and exact_rows evaluates the rows of a
+// wave that fails.
 constexpr double kRowTau = 0x1p-20;
 template <int KS>
 constexpr float kDoubt = 64.f * KS;
 template <int KS>
 constexpr double kDoubtErr = 32.0 * KS * 0x1p-20;
+constexpr double kUnderflow = 0x1p-111, kSplitFloor = 0x1p-36;
 
 struct DirectArgs {
   const uint4 *X, *Y, *Z;

@@ -120,15 +120,22 @@ __device__ __forceinline__ bool rows_held(const DirectArgs& a, int bh, int wrow0
     }
     const float* __restrict__ rec = a.krec + (hb + blk) * kRecWords;
     const int kexp = __float_as_int(rec[kRecE]), vexp = __float_as_int(rec[kRecV]);
-    double w = 0.0;
+    double w = 0.0, most = 0.0;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
+      if (e % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // (few registers)
       const int key = 8 * (e >> 2) + 4 * lh + (e & 3), j = 32 * blk + key;
-      if (j < n && fmaf(s1[e], kLoInv, s[e]) < kDoubt<KS>)
-        w += static_cast<double>(rec[key]) * at_bytes(ct, static_cast<uint32_t>(j - i + kCPad + n - 1) * 4u);
+      const double c = j < n ? at_bytes(ct, static_cast<uint32_t>(j - i + kCPad + n - 1) * 4u) : 0.f;
+      const double r = rec[key];
+      const float se = fmaf(s1[e], kLoInv, s[e]);
+      if (se < kDoubt<KS>) w = fma(kDoubtErr<KS>, r * c, w);
+      // (a key of a power so far below its block's that its record is zero: at
+      // most 2^38 2^-149)
+      w += (r == 0.0 ? c : c > 0.0 ? 1.0 : 0.0) * kUnderflow;
+      most = fmax(most, se * r * c);
     }
-    dd = fma(w * kDoubtErr<KS>, exp2_int(kexp), dd);
-    dn = fma(w * kDoubtErr<KS>, exp2_int(kexp + vexp + 15), dn);
+    dd = fma(w, exp2_int(kexp), dd);
+    dn = fma(w + most * kSplitFloor, exp2_int(kexp + vexp + 15), dn);
   }
   dd += __shfl_xor(dd, 32);
   dn += __shfl_xor(dn, 32);
@@ -202,10 +209,10 @@ __device__ __forceinline__ void exact_rows(const DirectArgs& a, float4* __restri
   }
   const int lo = max(b0, wlo), hi = min(b1, whi);
   float f[16];
-  const int pw = a.qpow[(hb + (wrow0 >> 5)) * kBlk + lr];
+  const int qp = a.qpow[(hb + (wrow0 >> 5)) * kBlk + lr];
   __syncthreads();  // xs and den are free
   for (int ti = wave; ti < kTiles; ti += NW) {
-    exact_features(a, q + static_cast<size_t>(min(i, n - 1)) * d, i < n, Wh, ti, pw, f);
+    exact_features(a, q + static_cast<size_t>(min(i, n - 1)) * d, i < n, Wh, ti, qp, f);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       float4* __restrict__ o = xs + ((2 * ti + j) * kFragLanes + lane) * 2;
@@ -222,12 +229,13 @@ __device__ __forceinline__ void exact_rows(const DirectArgs& a, float4* __restri
 #pragma unroll 1
   for (int blk = lo + wave; blk < hi; blk += NW) {
     const float* __restrict__ rec = a.krec + (hb + blk) * kRecWords;
-    const int kexp = __float_as_int(rec[kRecE]), vexp = __float_as_int(rec[kRecV]);
+    // (S is at most 2^68: keys down to 2^-140 of the block's largest stand beside it)
+    const int pw = __float_as_int(rec[kRecE]) - 2 * kRecBias, vexp = __float_as_int(rec[kRecV]);
     const int key = 32 * blk + lr;
     floatx16 s = zero16();
 #pragma unroll 1
     for (int ti = 0; ti < kTiles; ++ti) {
-      exact_features(a, k + static_cast<size_t>(min(key, n - 1)) * d, key < n, Wh, ti, kexp, f);
+      exact_features(a, k + static_cast<size_t>(min(key, n - 1)) * d, key < n, Wh, ti, pw, f);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const float4* __restrict__ o = xs + ((2 * ti + j) * kFragLanes + lane) * 2;
@@ -238,21 +246,34 @@ __device__ __forceinline__ void exact_rows(const DirectArgs& a, float4* __restri
       }
     }
     // lane: row i, keys 8 (e / 4) + 4 lh + e % 4 (groups of four: few loads in
-    // flight, few registers)
-    float ds = 0.f;
+    // flight, few registers); P over the power of its row's largest, as S c may
+    // leave fp32's range
     const int j0 = 32 * blk + 4 * lh;
+    auto c_of = [&](int e) {
+      const int j = j0 + 8 * (e >> 2) + (e & 3);
+      return j < n ? at_bytes(ct, static_cast<uint32_t>(j - i + ct0) * 4u) : 0.f;
+    };
+    int ex = -1000;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int j = j0 + 8 * g + t, e = 4 * g + t;
-        s[e] = j < n ? s[e] * at_bytes(ct, static_cast<uint32_t>(j - i + ct0) * 4u) : 0.f;
-        ds += s[e];
-      }
-      __builtin_amdgcn_sched_barrier(0);
+    for (int e = 0; e < 16; ++e) {
+      const float c = c_of(e);
+      if (s[e] > 0.f && c > 0.f)
+        ex = max(ex, __builtin_amdgcn_frexp_expf(s[e]) + __builtin_amdgcn_frexp_expf(c));
+      if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
-    dsum = fma(static_cast<double>(ds), exp2_int(kexp), dsum);
-    const double zs = exp2_int(kexp + vexp);
+    ex = max(ex, __shfl_xor(ex, 32));
+    if (ex == -1000) ex = 0;
+    asm volatile("" ::: "memory");  // (c is read again, not held)
+    float ds = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const float c = c_of(e), mant = __builtin_amdgcn_frexp_mantf(s[e]) * __builtin_amdgcn_frexp_mantf(c);
+      s[e] = ldexpf(mant, __builtin_amdgcn_frexp_expf(s[e]) + __builtin_amdgcn_frexp_expf(c) - ex);
+      ds += s[e];
+      if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    dsum = fma(static_cast<double>(ds), exp2_int(pw + ex), dsum);
+    const double zs = exp2_int(pw + vexp + ex);
 #pragma unroll
     for (int t = 0; t < CT; ++t) {
       const int col = (pass * CT + t) * 32 + lr;

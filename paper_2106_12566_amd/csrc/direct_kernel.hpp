@@ -211,7 +211,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
   if (MODE == 0 && tid == 0) redo = 0u;
   Total zt[CT][16];
   double dsum = 0.0, wsum = 0.0;
-  int vmost = -1000;  // largest power of the values
+  int kmost = -1000, vmost = -1000;  // largest powers of the keys and of the values
 #pragma unroll
   for (int t = 0; t < CT; ++t)
 #pragma unroll
@@ -336,6 +336,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
       }
       const double ws = static_cast<double>((w4[0] + w4[1]) + (w4[2] + w4[3])) * exp2_int(kexp);
       wsum += ws;
+      kmost = max(kmost, kexp);
       vmost = max(vmost, vexp);
     } else {
       zs = ldexpf(1.f, zexp);
@@ -373,7 +374,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
     // The test with every S taken as doubtful and a few columns (trigonometric
     // features are as large as their position's amplitude allows and S cancels:
     // its size does not say that a term was not held) ...
-    const double off = kDoubtErr<KS> * wsum, offn = off * exp2_int(vmost + 15);
+    const double off = fma(kDoubtErr<KS>, wsum, kUnderflow * exp2_int(kmost + 11));  // (2^11 blocks at most)
+    const double offn = fma(kSplitFloor, fabs(dsum), off) * exp2_int(vmost + 15);
     double num = fmax(fmax(fabs(zt[0][0]), fabs(zt[0][1])), fmax(fabs(zt[0][2]), fabs(zt[0][3])));
     bool again = false;
     if (__builtin_expect(a.kind != kFeatTrf && __any(i < n && !(off <= kRowTau * dsum && offn <= kRowTau * num)), 0)) {

@@ -87,6 +87,73 @@ def test_direct_powers_far_apart(gpu_lib):
     assert err <= 8 * TOL, err
 
 
+@pytest.mark.parametrize("n,d,m,offset", [(100, 64, 64, -85.5), (70, 20, 16, -86.0), (1300, 40, 128, -85.5)])
+def test_direct_weights_small(gpu_lib, n, d, m, offset):
+    """A bias near the end of fp32's range (c = exp(b) of 2^-123): z does not depend on the scale of c."""
+    dd = synth.custom(1, 2, n, d, m, seed=n, bias="normal", bias_sigma=0.2)
+    dd["b"] = (dd["b"] + np.float32(offset)).astype(np.float32)
+    print(f"weights small n={n} d={d} m={m}", flush=True)
+    z = gpu_lib.attention_fwd(*(to_gpu(dd[x]) for x in ("q", "k", "v", "b", "W")), route="direct").cpu().numpy()
+    ref, _ = oracle.attention(dd["q"], dd["k"], dd["v"], dd["b"], dd["W"])
+    err = rownorm_err(z, ref)
+    print(f"  {err:.3e}", flush=True)
+    # (c itself is an fp32 number of 2^-123 and up, normal: rounded to 2^-24)
+    assert err <= TOL, err
+
+
+@pytest.mark.parametrize("mask", ["causal", "window"])
+def test_direct_keys_hidden(gpu_lib, mask):
+    """Keys whose features are 2^-117 beside one, in their block but hidden from the first rows, that is
+    2^11: the rows that see only the small ones keep them."""
+    n, d, m = 80, 16, 32
+    dd = synth.custom(1, 1, n, d, m, seed=17, bias="normal", bias_sigma=0.3, qk_scale=0.3)
+    t = np.arange(-(n - 1), n)
+    dd["b"][:, t > 0] = -np.inf
+    if mask == "window":
+        dd["b"][:, t < -3] = -np.inf
+    W = dd["W"][0].astype(np.float64)
+    u = np.zeros(d)
+    u[0] = 1.0
+    for j in range(5):
+        # |k|^2 / 2 - max_l w_l.k = 81 (e^-81 is 2^-117)
+        g = float(np.max(W @ u))
+        dd["k"][0, 0, j] = ((g + np.sqrt(g * g + 2 * 81.0)) * u).astype(np.float32)
+        dd["k"][0, 0, j, 1:] += 0.01 * (j + 1)
+    dd["k"][0, 0, 5] = (W[3] * (np.sqrt(2 * 8.5) / np.linalg.norm(W[3]))).astype(np.float32)
+    ref, _ = oracle.attention(dd["q"], dd["k"], dd["v"], dd["b"], dd["W"])
+    z = gpu_lib.attention_fwd(*(to_gpu(dd[x]) for x in ("q", "k", "v", "b", "W")), route="direct",
+                              causal=True).cpu().numpy()
+    assert np.all(np.isfinite(z))
+    err = rownorm_err(z, ref)
+    print(f"keys hidden {mask}: {err:.3e}", flush=True)
+    # (exponents of phi near 2^7, as in test_direct_powers_far_apart)
+    assert err <= 8 * TOL, err
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_direct_weights_far_apart(gpu_lib, dt):
+    """Rows in which a small weight meets a large value: entries of P 2^24 to 2^40 below the row's largest
+    in the block, with values as much larger, count as much in z as the others.  Positive weights and
+    values: element by element."""
+    n, d, m = 96, 64, 64
+    dd = synth.custom(1, 2, n, d, m, seed=23, qkv_dtype=dt, bias="normal", bias_sigma=0.2)
+    v = 1.0 + np.random.default_rng(23).random((1, 2, n, d))
+    t = np.arange(-(n - 1), n)
+    dd["b"] = dd["b"].copy()
+    # row i weighs key j by 2^(e_{j - i}); values grow with j as the weights fall
+    dd["b"] += (-t * np.log(2.0) * 1.25).astype(np.float32)
+    v = (v * 2.0 ** (1.25 * np.arange(n))[:, None]).astype(np.float32)
+    if dt == "bf16":
+        v = torch.from_numpy(v).to(torch.bfloat16).float().numpy()
+    dd["v"] = v
+    ref, _ = oracle.attention(dd["q"], dd["k"], v, dd["b"], dd["W"])
+    z = gpu_lib.attention_fwd(to_gpu(dd["q"], dt), to_gpu(dd["k"], dt), to_gpu(v, dt), to_gpu(dd["b"]), to_gpu(dd["W"]),
+                              route="direct").cpu().numpy()
+    err = float(np.max(np.abs(z - ref) / np.abs(ref)))
+    print(f"weights far apart {dt}: {err:.3e}", flush=True)
+    assert err <= TOL, err
+
+
 @pytest.mark.parametrize("dt,n,d,features,nprf,bias", [
     ("bf16", 100, 64, "prf", False, "causal"), ("f32", 100, 64, "prf", False, "causal"),
     ("bf16", 70, 33, "trf", True, "decay"), ("f32", 200, 128, "elu", False, "causal"),
