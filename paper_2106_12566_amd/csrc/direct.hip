@@ -48,6 +48,7 @@ struct PrepArgs {
   int2* rrange;
   unsigned* fix;    // fix[BH] = rows evaluated exactly (all of them)
   int *qpow, *kpow; // [BH][32 nblk] powers of phi(q), phi(k) (kpow NULL: not wanted)
+  float* qsum;      // [BH][32 nblk] sums of phi(q) in units of its power
   unsigned* flag;   // [BH + 1] cleared
   int BH, H, n, nblk, d, m, KS, ct_total, kind, nprf, tiles, phi_blocks, v_blocks;
   float inv_sqrt_m;
@@ -104,6 +105,7 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
   };
   int ex;  // the position's power: its largest feature is brought to [2^14, 2^15)
   bool any_phi;
+  float sum = 0.f;
   if (a.kind == kFeatTrf) {
     // every feature is at most the amplitude: no need to see them first
     const float amp = pos_ok ? static_cast<float>(exp(half_sq)) * a.inv_sqrt_m : 0.f;
@@ -173,10 +175,14 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
       constexpr int ti = decltype(tc)::value;
       if (ti < ftiles) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, val[ti][e]);
+        for (int e = 0; e < 16; ++e) {
+          mx = fmaxf(mx, val[ti][e]);
+          sum += val[ti][e];
+        }
       }
     });
     mx = fmaxf(mx, __shfl_xor(mx, 32));
+    sum += __shfl_xor(sum, 32);
     ex = __builtin_amdgcn_frexp_expf(mx) - 15;  // (-15 for zero, infinite and NaN maxima)
     any_phi = mx > 0.f;
     constexpr_for<2 * NT>([&](auto kc) {
@@ -190,17 +196,27 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
   }
   if (src == 0 && pt == 0 && tid == 0) a.flag[bh] = 0u;
   if (!store) return;
+  sum = ldexpf(sum, -ex);
   if (src == 0) {
-    if (lh == 0) a.qpow[block * kBlk + lr] = ex;
+    if (lh == 0) {
+      a.qpow[block * kBlk + lr] = ex;
+      a.qsum[block * kBlk + lr] = sum;
+    }
   } else {
     if (a.kpow && lh == 0) a.kpow[block * kBlk + lr] = ex;
     // (positions without features have no power of their own)
     int E = any_phi ? ex : -400;
 #pragma unroll
-    for (int off = 16; off > 0; off >>= 1) E = max(E, __shfl_xor(E, off));
+    for (int off = 16; off > 0; off >>= 1) {
+      E = max(E, __shfl_xor(E, off));
+      sum = fmaxf(sum, __shfl_xor(sum, off));
+    }
     float* __restrict__ rec = a.krec + block * kRecWords;
     if (lh == 0) rec[lr] = any_phi ? ldexpf(1.f, ex - E - kRecBias) : 0.f;
-    if (lane == 0) rec[kRecE] = __int_as_float(E + kRecBias);
+    if (lane == 0) {
+      rec[kRecE] = __int_as_float(E + kRecBias);
+      rec[kRecSum] = sum;
+    }
   }
 }
 
@@ -485,6 +501,7 @@ DirectLayout direct_layout(int B, int H, int n, int d, int ks) {
   L.ctab = take(static_cast<size_t>(H) * ctab_stride(n) * sizeof(float));
   L.crange = take(static_cast<size_t>(H) * ctab_chunks(n) * sizeof(int2));
   L.qpow = take(bh * L.nblk * kBlk * sizeof(int));
+  L.qsum = take(bh * L.nblk * kBlk * sizeof(float));
   L.flag = take((bh + 1) * sizeof(unsigned));
   const size_t rows = 32 * direct_waves(ks), tiles = (static_cast<size_t>(n) + rows - 1) / rows;
   const size_t cw = (L.ct_total >= 2 ? 64 : 32) + 1;
@@ -510,6 +527,7 @@ hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, con
   p.kind = kind, p.nprf = nprf ? 1 : 0;
   p.krec = reinterpret_cast<float*>(w + L.krec);
   p.qpow = reinterpret_cast<int*>(w + L.qpow);
+  p.qsum = reinterpret_cast<float*>(w + L.qsum);
   p.flag = reinterpret_cast<unsigned*>(w + L.flag);
   p.tiles = (n + 127) / 128;
   p.phi_blocks = 2 * BH * p.tiles;
@@ -538,6 +556,7 @@ hipError_t launch_direct(const DirectLayout& L, char* w, const void* q, const vo
   a.remap = direct_remap(BH);
   a.q = q, a.k = k, a.W = W, a.m = m, a.kind = kind, a.nprf = nprf ? 1 : 0;
   a.qpow = reinterpret_cast<const int*>(w + L.qpow);
+  a.qsum = reinterpret_cast<const float*>(w + L.qsum);
   a.flag = reinterpret_cast<unsigned*>(w + L.flag);
   a.inv_sqrt_m = inv_sqrt(m), a.log2_m = log2_scale(m);
   if (L.ct_total >= 2)

@@ -97,15 +97,26 @@ __device__ __forceinline__ void store4(float* __restrict__ row, int c, int d, fl
 
 
 // Whether every one of the 32 rows from wrow0 on passes kRowTau's test over the key
-// blocks [lo, hi), given its denominator and its largest numerator (each lane
-// its row's; S formed again from memory).
+// blocks [lo, hi), given its denominator, its largest numerator, the sum of its
+// weights and what it may have lost beside them (each lane its row's), first by
+// the sums of the features, then in full (S formed again from memory).
 template <int KS>
 __device__ __forceinline__ bool rows_held(const DirectArgs& a, int bh, int wrow0, int lo, int hi, double dsum,
-                                          double num) {
+                                          double num, double wsum, double beside, int vmost) {
   const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5, n = a.n, i = wrow0 + lr;
   const size_t hb = static_cast<size_t>(bh) * a.nblk;
   const uint4* __restrict__ xp = a.X + (hb + (wrow0 >> 5)) * KS * 2 * kFragLanes + lane;
   const float* __restrict__ ct = a.ctab + static_cast<size_t>(bh % a.H) * ctab_stride(n);
+  const double xs = a.qsum[(hb + (wrow0 >> 5)) * kBlk + lr];
+  {
+    float ys = 0.f;
+    for (int blk = lo + lane; blk < hi; blk += 64) ys = fmaxf(ys, a.krec[(hb + blk) * kRecWords + kRecSum]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) ys = fmaxf(ys, __shfl_xor(ys, off));
+    const double off = fma(kTermErr * (xs + ys), wsum, beside);
+    const bool held = off <= kRowTau * dsum && fma(kSplitFloor, dsum, off) * exp2_int(vmost + 15) <= kRowTau * num;
+    if (!__any(i < n && !held)) return true;
+  }
   double dd = 0.0, dn = 0.0;
 #pragma unroll 1
   for (int blk = lo; blk < hi; ++blk) {
@@ -120,6 +131,8 @@ __device__ __forceinline__ bool rows_held(const DirectArgs& a, int bh, int wrow0
     }
     const float* __restrict__ rec = a.krec + (hb + blk) * kRecWords;
     const int kexp = __float_as_int(rec[kRecE]), vexp = __float_as_int(rec[kRecV]);
+    const double err = kTermErr * (xs + rec[kRecSum]);
+    const float doubt = static_cast<float>(kDoubt * err);
     double w = 0.0, most = 0.0;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -128,7 +141,7 @@ __device__ __forceinline__ bool rows_held(const DirectArgs& a, int bh, int wrow0
       const double c = j < n ? at_bytes(ct, static_cast<uint32_t>(j - i + kCPad + n - 1) * 4u) : 0.f;
       const double r = rec[key];
       const float se = fmaf(s1[e], kLoInv, s[e]);
-      if (se < kDoubt<KS>) w = fma(kDoubtErr<KS>, r * c, w);
+      if (se < doubt) w = fma(err, r * c, w);
       // (a key of a power so far below its block's that its record is zero: at
       // most 2^38 2^-149)
       w += (r == 0.0 ? c : c > 0.0 ? 1.0 : 0.0) * kUnderflow;

@@ -374,7 +374,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
     // The test with every S taken as doubtful and a few columns (trigonometric
     // features are as large as their position's amplitude allows and S cancels:
     // its size does not say that a term was not held) ...
-    const double off = fma(kDoubtErr<KS>, wsum, kUnderflow * exp2_int(kmost + 11));  // (2^11 blocks at most)
+    const double beside = kUnderflow * exp2_int(kmost + 11);  // (2^11 blocks at most)
+    const double off = fma(kDoubtErr<KS>, wsum, beside);
     const double offn = fma(kSplitFloor, fabs(dsum), off) * exp2_int(vmost + 15);
     double num = fmax(fmax(fabs(zt[0][0]), fabs(zt[0][1])), fmax(fabs(zt[0][2]), fabs(zt[0][3])));
     bool again = false;
@@ -385,7 +386,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
 #pragma unroll
         for (int e = 0; e < 16; ++e) num = fmax(num, fabs(zt[t][e]));
       num = fmax(num, __shfl_xor(num, 32));
-      again = !rows_held<KS>(a, bh, wrow0, max(b0, wlo), min(b1, whi), dsum, num);
+      again = !rows_held<KS>(a, bh, wrow0, max(b0, wlo), min(b1, whi), dsum, num, wsum, beside, vmost);
     }
     if (__builtin_expect(again, 0)) {
       if (lane == 0) atomicOr(&redo, 1u << wave);

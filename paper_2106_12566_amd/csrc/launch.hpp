@@ -103,6 +103,7 @@ struct DirectLayout {
   size_t ctab;   // float [H][ctab_stride(n)]  c = exp(b), zero-padded
   size_t crange; // int2  [H][ctab_chunks(n)]  range of finite b per table chunk
   size_t qpow;   // int   [BH][32 nblk]  powers of two of phi(q)
+  size_t qsum;   // float [BH][32 nblk]  sums of phi(q) in units of these
   size_t flag;   // uint  [BH + 1]  heads with rows evaluated in fp32; any such head
   size_t part;   // double [BH][passes][tiles][nparts][columns + 1][rows] partial sums
   size_t total;
