@@ -124,8 +124,8 @@ typedef enum {
  * relative-position view).  Read by the route choice alone: the direct route
  * visits only the keys inside each row's finite-b range, so with the hint
  * its cost model counts n (n + 1) / 2 query/key pairs instead of n^2.
- * Results do not depend on it (both routes evaluate Eq. (10) for the b
- * given), and a wrong hint only costs time.
+ * Both routes evaluate Eq. (10) for the b given, so that results depend on
+ * it only as they do on the route, and a wrong hint only costs time.
  */
 #define KRPE_HINT_CAUSAL 32u
 
@@ -276,10 +276,10 @@ size_t krpe_attention_bwd_workspace(int B, int H, int n, int d, int m, unsigned 
  * direct route (m <= 256), a weighted product on the matrix cores like the
  * direct forward; the forward pass is recomputed inside (its exact-row
  * evaluation included).  Without a route bit the faster one by a cost
- * model of their own runs, except that a stated causal mask without KRPE_NPRF keeps the
- * FFT products: their rounding, spread over the sequence, reaches 1e-4 to
- * 4e-1 of a gradient's norm there (rows with small denominators), that of
- * KRPE_ROUTE_DIRECT's 1e-6.
+ * model of their own runs.  The direct products are good to 1e-6 of a
+ * gradient's norm; the FFT products spread their rounding over the sequence,
+ * which reaches 1e-4 and more of it where rows with small denominators weigh
+ * in (few keys under a mask, no row normalisation).
  * q, k, v : [B, H, n, d] in qkv_dtype    b : [H, 2n-1]    W : [H, m, d]
  * dz      : [B, H, n, d] fp32             dq, dk, dv : [B, H, n, d] fp32 (outputs)
  * db      : [H, 2n-1] fp32 (output, summed over the batch), or NULL to skip it:

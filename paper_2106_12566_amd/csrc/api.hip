@@ -147,19 +147,10 @@ bool use_fp32_direct(unsigned flags, long long BH, int n, int M, int d) {
 // more where their row tiles do not fill the chip; the transforms about 4.9
 // forward passes (79 shapes: 96 heads, n = 4096, M = 128 9.2 ms direct, 34.5
 // transforms; one head, n = 16384, M = 32 2.7 and 1.8).
-//
-// A call that states a causal mask, with neither row normalisation nor a
-// route, keeps the transforms (and with them every bit of its results): where
-// rows with small denominators weigh in, the rounding that a transform spreads
-// over the sequence is 1e-4 to 4e-1 of a gradient's norm against 64 bits (the
-// direct products 4e-7), so the two routes differ by more than the results of
-// one call may change.  KRPE_ROUTE_DIRECT asks for the direct ones (64 tokens,
-// 12 heads: 0.08 ms against 0.80).
 bool use_direct_products(unsigned flags, long long BH, int n, int M, int d) {
   if (flags & KRPE_ROUTE_DIRECT) return true;
   if (flags & KRPE_ROUTE_FFT) return false;
   const bool causal = (flags & KRPE_HINT_CAUSAL) != 0;
-  if (causal && !(flags & KRPE_NPRF)) return false;
   const double tiles = static_cast<double>(BH) * ((n + 127) / 128);
   const double fill = tiles < 320.0 ? 320.0 / tiles : 1.0;
   const double direct = 2.9e-14 * static_cast<double>(BH) * pair_count(n, causal) * fill *

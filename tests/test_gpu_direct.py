@@ -264,6 +264,24 @@ def test_direct_opposed(gpu_lib, d, scale, kind, mask, n, m, dt):
         assert err <= 2 * TOL, err
 
 
+@pytest.mark.parametrize("B,H,n,d,m,dt", [(1, 12, 64, 64, 64, "f32"), (2, 4, 300, 64, 128, "f32"), (1, 3, 17, 16, 7, "f32"),
+                                          (1, 8, 777, 40, 50, "bf16"), (1, 16, 1500, 64, 64, "f32")])
+def test_backward_causal_hint(gpu_lib, B, H, n, d, m, dt):
+    """Under a causal mask, on the default route, the hint that states it changes no gradient: both calls
+    within the direct products' bound (test_direct_backward) of 64 bits."""
+    dd = synth.custom(B, H, n, d, m, seed=31 + n, qkv_dtype=dt, bias="causal")
+    G = np.random.default_rng([31, n]).standard_normal((B, H, n, d)).astype(np.float32)
+    args = (*(to_gpu(dd[x], dt) for x in ("q", "k", "v")), to_gpu(dd["b"]), to_gpu(dd["W"]), to_gpu(G))
+    print(f"backward causal B={B} H={H} n={n} d={d} m={m} {dt}", flush=True)
+    ref = oracle.attention_grad(dd["q"], dd["k"], dd["v"], dd["b"], dd["W"], G)
+    for hint in (True, False):
+        got = gpu_lib.attention_bwd(*args, with_db=True, causal=hint)
+        for name, g, r in zip(("dq", "dk", "dv", "db"), got, ref):
+            err = np.linalg.norm(g.cpu().numpy() - r) / np.linalg.norm(r)
+            print(f"  hint={hint} {name}: {err:.3e}", flush=True)
+            assert err <= TOL, (hint, name, err)
+
+
 BWD_CASES = [
     # n, d, m: 32-position blocks and row tiles (128 and 256 rows); d + 1 contracted columns around the
     # compiled 3, 5 and 9 steps of 16; column tiles and passes; feature counts around 64, 128 and 256
