@@ -33,14 +33,16 @@ struct OpsArgs {
   const double* den;
   const int* kpow;
   uint4 *gs, *vs, *gz;
-  float *reca, *recb, *recc;
+  float *reca, *recb, *recc, *recd;
   int *gpow, *vpow;
   int BH, n, nblk, d, ks2, ct_total, tiles;
 };
 
 // 64 positions of one (batch, head), wave w its 32-position block; source 0:
 // Gh and gamma (S and Z fragments, records of dv's and dphi(k)'s keys), source
-// 1: [v, 1] (S fragments, records of dphi(q)'s keys).
+// 1: [v, 1] (S fragments, records of dphi(q)'s keys).  Gh as dv's Z operand is taken
+// times the power of D_i and dv's records over it: P_ij / D_i is a share of row i,
+// while P_ij alone differs between the rows of a block by all that D does.
 template <typename TV>
 __global__ __launch_bounds__(128) void k_bwd_ops(OpsArgs a) {
   constexpr int XS = kMaxD + 16 + 4;
@@ -54,6 +56,7 @@ __global__ __launch_bounds__(128) void k_bwd_ops(OpsArgs a) {
   if (blk >= a.nblk) return;  // uniform per wave; waves share nothing here
   const size_t block = static_cast<size_t>(bh) * a.nblk + blk;
   float(*__restrict__ row)[XS] = rows[wave];
+  int dp = 0;  // power of D_i
   // rows of dz or v to LDS (zeros past n and past d)
   const size_t at = (static_cast<size_t>(bh) * n + 32 * blk) * d;
   const int live = min(32, n - 32 * blk);
@@ -76,7 +79,8 @@ __global__ __launch_bounds__(128) void k_bwd_ops(OpsArgs a) {
   if (src == 0) {
     // lane half lh takes the groups of 4 columns 2 g + lh of its row
     const size_t i = static_cast<size_t>(bh) * n + 32 * blk + min(lr, live - 1);
-    const double inv = ok ? 1.0 / a.den[i] : 0.0;
+    const double den = a.den[i], inv = ok ? 1.0 / den : 0.0;
+    if (ok && isfinite(den) && den != 0.0) dp = ilogb(den) + 1;
     const float* __restrict__ zr = a.z + i * d;
     double dot = 0.0;
     for (int c = 4 * lh; c < d; c += 8) {
@@ -139,12 +143,16 @@ __global__ __launch_bounds__(128) void k_bwd_ops(OpsArgs a) {
     rec[kRecV] = __int_as_float(0);
   }
   if (src == 1) return;
-  // Gh as Z fragments with the block's power
+  // Gh over the power of 1 / D_i as Z fragments with the block's power
   float gm = 0.f;
   for (int ct = 0; ct < a.ct_total; ++ct) {
     const int c = 32 * ct + lr;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) gm = fmaxf(gm, c < d ? fabsf(row[8 * (e >> 2) + 4 * lh + (e & 3)][min(c, d)]) : 0.f);
+    for (int e = 0; e < 16; ++e) {
+      const int r = 8 * (e >> 2) + 4 * lh + (e & 3);
+      const float g = ldexpf(row[r][min(c, d)], __shfl(dp, r));
+      gm = fmaxf(gm, c < d ? fabsf(g) : 0.f);
+    }
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) gm = fmaxf(gm, __shfl_xor(gm, off));
@@ -157,8 +165,9 @@ __global__ __launch_bounds__(128) void k_bwd_ops(OpsArgs a) {
       float v8[8];
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
-        const float g = row[16 * k2 + 8 * (t >> 2) + 4 * lh + (t & 3)][min(c, d)];
-        v8[t] = c < d ? ldexpf(g, -gx) : 0.f;
+        const int r = 16 * k2 + 8 * (t >> 2) + 4 * lh + (t & 3);
+        const float g = ldexpf(row[r][min(c, d)], __shfl(dp, r) - gx);
+        v8[t] = c < d ? g : 0.f;
       }
       uint4 hh, ll;
       split_f16x8(v8, kLoScale, hh, ll);
@@ -166,13 +175,19 @@ __global__ __launch_bounds__(128) void k_bwd_ops(OpsArgs a) {
       zo[((ct * 2 + k2) * 2 + 1) * kFragLanes] = ll;
     }
   }
-  // dv's keys: phi(q) without its power
-  float* __restrict__ ra = a.reca + block * kRecWords;
-  if (lh == 0) ra[lr] = 32 * blk + lr < n ? ldexpf(1.f, -kRecBias) : 0.f;
-  if (lane == 0) {
-    ra[kRecE] = __int_as_float(kRecBias);
-    ra[kRecV] = __int_as_float(gx);
-  }
+  // dv's keys: phi(q) without its power, over D_i's; the diagonal sums' with it
+  auto record = [&](float* __restrict__ r, int p, bool has, int v) {
+    int e = has ? p : -800;
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) e = max(e, __shfl_xor(e, off));
+    if (lh == 0) r[lr] = has ? ldexpf(1.f, p - e - kRecBias) : 0.f;
+    if (lane == 0) {
+      r[kRecE] = __int_as_float(e + kRecBias);
+      r[kRecV] = __int_as_float(v);
+    }
+  };
+  record(a.reca + block * kRecWords, -dp, ok, gx);
+  record(a.recd + block * kRecWords, ex + dp, any, 0);
 }
 
 // S fragments of phi turned into Z fragments (the same values; powers are the
@@ -436,6 +451,7 @@ DirectBwdLayout direct_bwd_layout(int B, int H, int n, int d, int m) {
   L.reca = take(bh * nb * kRecWords * sizeof(float));
   L.recb = take(bh * nb * kRecWords * sizeof(float));
   L.recc = take(bh * nb * kRecWords * sizeof(float));
+  L.recd = take(bh * nb * kRecWords * sizeof(float));
   L.gpow = take(bh * nb * kBlk * sizeof(int));
   L.vpow = take(bh * nb * kBlk * sizeof(int));
   L.wf = take(static_cast<size_t>(H) * ks * d_tiles(d) * 3 * kFrag);
@@ -466,7 +482,7 @@ hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, c
   OpsArgs o{};
   o.v = v, o.dz = dz, o.z = Fl(L.z), o.den = den, o.kpow = I(L.kpow);
   o.gs = U(L.gs), o.vs = U(L.vs), o.gz = U(L.gz);
-  o.reca = Fl(L.reca), o.recb = Fl(L.recb), o.recc = Fl(L.recc), o.gpow = I(L.gpow), o.vpow = I(L.vpow);
+  o.reca = Fl(L.reca), o.recb = Fl(L.recb), o.recc = Fl(L.recc), o.recd = Fl(L.recd), o.gpow = I(L.gpow), o.vpow = I(L.vpow);
   o.BH = BH, o.n = n, o.nblk = nblk, o.d = d, o.ks2 = L.ks2, o.ct_total = F.ct_total, o.tiles = (nblk + 1) / 2;
   const dim3 ogrid(static_cast<unsigned>(static_cast<long long>(2) * BH * o.tiles));
   if (bf16)
@@ -488,7 +504,7 @@ hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, c
   // diagonal sums of (v_j.Gh_i + gamma_i) (phi(k_j).phi(q_i))
   a.X = U(F.y), a.Y = U(F.x), a.Z = U(L.gz), a.krec = Fl(L.reca), a.rpow = I(L.kpow);
   a.ctab = Fl(L.crev), a.crange = rrange, a.ct_total = F.ct_total, a.passes = F.passes, a.z = dv, a.ldz = d;
-  a.X2 = U(L.vs), a.Y2 = U(L.gs), a.krec2 = Fl(L.recc), a.rpow2 = I(L.vpow), a.pdc = Fl(L.pdc);
+  a.X2 = U(L.vs), a.Y2 = U(L.gs), a.krec2 = Fl(L.recd), a.rpow2 = I(L.vpow), a.pdc = Fl(L.pdc);
   hipError_t e = F.ks == 4   ? go_dv<4>(a, L.ks2, db != nullptr, st)
                  : F.ks == 8 ? go_dv<8>(a, L.ks2, db != nullptr, st)
                              : go_dv<16>(a, L.ks2, db != nullptr, st);

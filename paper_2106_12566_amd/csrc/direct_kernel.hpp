@@ -25,8 +25,11 @@ namespace krpe {
 // its row's largest entry, and Z^T = [v]^T P^T (lane: row lr again, so that
 // the row's power applies lane by lane), whose fp32 sums over the 32 keys are
 // added into fp64 totals; the denominator is the fp32 sum of P added likewise.
-// The power of phi(q_i) cancels in z.  P's small term is stored unscaled (its
-// largest entry is at 2^14, terms below 2^-40 of that are lost).  A wave skips
+// The power of phi(q_i) cancels in z.  The forward pass stores P's small term
+// unscaled (its largest entry is at 2^14, terms below 2^-40 of that are lost: the
+// row test counts it); the backward's products, whose weights R_ij = (..) / D_i
+// differ within a block by all that D does, scale it (2^-51), 16 multiplications
+// a block.  A wave skips
 // the blocks outside its own rows' range (it still stages and meets the
 // barriers).  The forward pass sums the weights of S too (kRowTau's test, 1.5 to 2 %
 // of a long call: 1.98 -> 2.01 ms at 96 heads, n = 4096, m = 128); a branch on
@@ -114,6 +117,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
   constexpr int kStrip = NC * 64 + NR * kRecWords;
   __shared__ uint4 tiles_lds[2][NF * kFragLanes];
   __shared__ __align__(16) float strip[2][kStrip];
+  constexpr float kPLow = MODE > 0 ? kLoScale : 1.f;  // scale of P's small term
   constexpr int kDS = 33;  // floats per diagonal: writes across the lanes and reads fall in distinct banks
   __shared__ float diag[MODE == 2 ? NW : 1][MODE == 2 ? 64 * kDS : 1];
   __shared__ unsigned redo;  // MODE 0: waves whose rows are evaluated again,
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
       float v8[8];
 #pragma unroll
       for (int t = 0; t < 8; ++t) v8[t] = p[8 * k2 + t] * sc;
-      split_f16x8(v8, 1.f, ph[k2], pl[k2]);
+      split_f16x8(v8, kPLow, ph[k2], pl[k2]);
     }
 #pragma unroll
     for (int t = 0; t < CT; ++t) {
@@ -355,7 +359,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
 #pragma unroll
       for (int k2 = 0; k2 < 2; ++k2) {
         const uint4 vh = zf[((t * 2 + k2) * NSZ + 0) * kFragLanes];
-        zc = mfma_f16(vh, pl[k2], zc);
+        if constexpr (MODE > 0)
+          z1 = mfma_f16(vh, pl[k2], z1);
+        else
+          zc = mfma_f16(vh, pl[k2], zc);
         zc = mfma_f16(vh, ph[k2], zc);
         if constexpr (NSZ > 1) z1 = mfma_f16(zf[((t * 2 + k2) * NSZ + 1) * kFragLanes], ph[k2], z1);
       }

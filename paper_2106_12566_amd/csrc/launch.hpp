@@ -135,7 +135,7 @@ struct DirectBwdLayout {
   size_t gs, vs;    // S fragments [BH][nblk][ks2][2] of [Gh, gamma] and [v, 1]
   size_t gz;        // Z fragments [BH][nblk][ct][2][2] of Gh
   size_t zq, zk;    // Z fragments [BH][nblk][passq ctq][2][2] of phi(q), phi(k)
-  size_t reca, recb, recc; // records of the keys of the three products
+  size_t reca, recb, recc, recd;  // records of the keys of the three products and of the diagonal sums
   size_t gpow, vpow; // int   [BH][32 nblk]
   size_t wf;        // W as Z fragments, three bf16 terms [H][ks][d tiles][3]
   size_t dphi;      // float  S fragments [BH][nblk][ks][64][8], one product at a time

@@ -292,6 +292,35 @@ BWD_CASES = [
 ]
 
 
+def _bwd_check(lib, dd, dt, G, what, tol=TOL, **kw):
+    print(what, flush=True)
+    args = (*(to_gpu(dd[x], dt) for x in ("q", "k", "v")), to_gpu(dd["b"]), to_gpu(dd["W"]), to_gpu(G))
+    got = lib.attention_bwd(*args, with_db=True, **kw)
+    ref = oracle.attention_grad(dd["q"], dd["k"], dd["v"], dd["b"], dd["W"], G, nprf=kw.get("nprf", False))
+    errs = {}
+    for name, g, r in zip(("dq", "dk", "dv", "db"), got, ref):
+        g = g.cpu().numpy().astype(np.float64)
+        assert np.all(np.isfinite(g)), name
+        errs[name] = np.linalg.norm(g - r) / np.linalg.norm(r)
+    print("  " + " ".join(f"{k} {e:.3e}" for k, e in errs.items()), flush=True)
+    assert max(errs.values()) <= tol, errs
+
+
+@pytest.mark.parametrize("d,n,m,bias", [(64, 200, 64, "normal"), (64, 130, 128, "causal"), (30, 100, 200, "normal")])
+def test_direct_backward_denominators_far_apart(gpu_lib, d, n, m, bias):
+    """Rows of one block whose denominators (in units of their queries) differ by 2^20 and more: every
+    third query opposes the keys, which share a direction."""
+    dd = synth.custom(1, 2, n, d, m, seed=5, bias=bias, qk_scale=0.1)
+    rng = np.random.default_rng([5, n])
+    u = rng.standard_normal((1, 2, 1, d)).astype(np.float32)
+    u *= 3.6 / np.linalg.norm(u, axis=-1, keepdims=True)
+    dd["k"] = (dd["k"] + u).astype(np.float32)
+    sign = np.where(np.arange(n) % 3 == 1, -1.0, 1.0)[:, None]
+    dd["q"] = (dd["q"] + sign * u).astype(np.float32)
+    G = rng.standard_normal((1, 2, n, d)).astype(np.float32)
+    _bwd_check(gpu_lib, dd, "f32", G, f"denominators far apart d={d} n={n} m={m} {bias}", route="direct")
+
+
 @pytest.mark.parametrize("n,d,m,dt,bias,nprf", BWD_CASES)
 def test_direct_backward(gpu_lib, n, d, m, dt, bias, nprf):
     """The gradients of the direct products against the fp64 chain rule.  Tolerance 2e-5 of a
