@@ -32,6 +32,7 @@ struct OpsArgs {
   const float *dz, *z;
   const double* den;
   const int* kpow;
+  const float* krec;  // the forward's records (powers of v)
   uint4 *gs, *vs, *gz;
   float *reca, *recb, *recc, *recd;
   int *gpow, *vpow;
@@ -40,7 +41,9 @@ struct OpsArgs {
 
 // 64 positions of one (batch, head), wave w its 32-position block; source 0:
 // Gh and gamma (S and Z fragments, records of dv's and dphi(k)'s keys), source
-// 1: [v, 1] (S fragments, records of dphi(q)'s keys).  Gh as dv's Z operand is taken
+// 1: [v, 1] (S fragments, records of dphi(q)'s keys).  The 1 is stored as 2^sv, the
+// power of the head's largest value, and gamma over it, so that neither column
+// is far from the others whatever the values' scale.  Gh as dv's Z operand is taken
 // times the power of D_i and dv's records over it: P_ij / D_i is a share of row i,
 // while P_ij alone differs between the rows of a block by all that D does.
 template <typename TV>
@@ -56,6 +59,11 @@ __global__ __launch_bounds__(128) void k_bwd_ops(OpsArgs a) {
   if (blk >= a.nblk) return;  // uniform per wave; waves share nothing here
   const size_t block = static_cast<size_t>(bh) * a.nblk + blk;
   float(*__restrict__ row)[XS] = rows[wave];
+  int sv = -400;
+  for (int j = lane; j < a.nblk; j += 64)
+    sv = max(sv, __float_as_int(a.krec[(static_cast<size_t>(bh) * a.nblk + j) * kRecWords + kRecV]) + 15);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sv = max(sv, __shfl_xor(sv, off));
   int dp = 0;  // power of D_i
   // rows of dz or v to LDS (zeros past n and past d)
   const size_t at = (static_cast<size_t>(bh) * n + 32 * blk) * d;
@@ -104,9 +112,9 @@ __global__ __launch_bounds__(128) void k_bwd_ops(OpsArgs a) {
     dot += __shfl_xor(dot, 32);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();  // (the group of 4 that holds column d is rewritten above when d % 4 != 0)
-    if (lh == 0) row[lr][d] = ok ? static_cast<float>(-dot * inv) : 0.f;
+    if (lh == 0) row[lr][d] = ok ? static_cast<float>(-dot * inv * exp2_int(-sv)) : 0.f;
   } else if (lh == 0) {
-    row[lr][d] = ok ? 1.f : 0.f;
+    row[lr][d] = ok ? ldexpf(1.f, sv) : 0.f;
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -480,7 +488,7 @@ hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, c
     return e;
 
   OpsArgs o{};
-  o.v = v, o.dz = dz, o.z = Fl(L.z), o.den = den, o.kpow = I(L.kpow);
+  o.v = v, o.dz = dz, o.z = Fl(L.z), o.den = den, o.kpow = I(L.kpow), o.krec = Fl(F.krec);
   o.gs = U(L.gs), o.vs = U(L.vs), o.gz = U(L.gz);
   o.reca = Fl(L.reca), o.recb = Fl(L.recb), o.recc = Fl(L.recc), o.recd = Fl(L.recd), o.gpow = I(L.gpow), o.vpow = I(L.vpow);
   o.BH = BH, o.n = n, o.nblk = nblk, o.d = d, o.ks2 = L.ks2, o.ct_total = F.ct_total, o.tiles = (nblk + 1) / 2;

@@ -306,6 +306,16 @@ def _bwd_check(lib, dd, dt, G, what, tol=TOL, **kw):
     assert max(errs.values()) <= tol, errs
 
 
+@pytest.mark.parametrize("power,dt,bias", [(-60, "f32", "normal"), (-45, "bf16", "causal"), (45, "f32", "causal"), (60, "bf16", "normal")])
+def test_direct_backward_value_scale(gpu_lib, power, dt, bias):
+    """Gradients do not depend on the scale of the values (dv), or by that factor (the others)."""
+    n, d, m = 150, 64, 64
+    dd = synth.custom(2, 2, n, d, m, seed=3, qkv_dtype=dt, bias=bias)
+    dd["v"] = (dd["v"] * 2.0 ** power).astype(np.float32)
+    G = np.random.default_rng(3).standard_normal((2, 2, n, d)).astype(np.float32)
+    _bwd_check(gpu_lib, dd, dt, G, f"value scale 2^{power} {dt} {bias}", route="direct")
+
+
 @pytest.mark.parametrize("d,n,m,bias", [(64, 200, 64, "normal"), (64, 130, 128, "causal"), (30, 100, 200, "normal")])
 def test_direct_backward_denominators_far_apart(gpu_lib, d, n, m, bias):
     """Rows of one block whose denominators (in units of their queries) differ by 2^20 and more: every
