@@ -17,7 +17,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libkrpe.so")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "grad_bias.hip", "direct.hip", "bwd_direct.hip", "toeplitz.hip", "phi.hip",
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "grad_bias.hip", "direct.hip", "bwd_direct.hip", "bwd_exact.hip", "toeplitz.hip", "phi.hip",
                                                    "long_seq.hip", "api.hip")]
 # The convolution kernel at N = 16384, compiled on its own with LLVM's
 # maximum-ILP machine scheduler (measured faster for that length only).

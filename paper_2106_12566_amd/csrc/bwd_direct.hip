@@ -11,8 +11,9 @@
 // phi(q_i).phi(k_j) and takes the other factor as a second product.  phi(q_i)
 // stands without its power of two throughout: D_i is then in the same units
 // and the power cancels.  Launches: the forward's two, k_bwd_ops (operands from
-// dz, z, D and v), k_turn (phi as Z operands), k_wterms, three k_direct, two
-// k_feature_grad, k_db.
+// dz, z, D and v), k_turn (phi as Z operands, W's terms), k_bwd_exact (the heads
+// that the forward pass flagged, which the others then skip: bwd_exact.hip), three
+// k_direct, k_db, two k_feature_grad.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -20,6 +21,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "bwd_exact.hpp"
 #include "direct_kernel.hpp"
 #include "launch.hpp"
 #include "wprod.hpp"
@@ -198,16 +200,43 @@ __global__ __launch_bounds__(128) void k_bwd_ops(OpsArgs a) {
   record(a.recd + block * kRecWords, ex + dp, any, 0);
 }
 
+// W as Z fragments in three bf16 terms: [H][ks][d tile][3][64], lane: column
+// 32 dt + lr, features 16 ks + 8 (t / 4) + 4 lh + t % 4.  One wave a fragment.
+struct WTerms {
+  const float* W;
+  uint4* wf;
+  int H, d, m, KS, dts;
+};
+__device__ __forceinline__ void wterms(const WTerms& a, int item) {
+  const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
+  const int dt = item % a.dts, ks = item / a.dts % a.KS, h = item / a.dts / a.KS, c = 32 * dt + lr;
+  if (h >= a.H) return;
+  float v8[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const int l = 16 * ks + 8 * (t >> 2) + 4 * lh + (t & 3);
+    v8[t] = l < a.m && c < a.d ? a.W[(static_cast<size_t>(h) * a.m + l) * a.d + c] : 0.f;
+  }
+  uint4 t3[3];
+  split_bf16x8(v8, t3);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) a.wf[(static_cast<size_t>(item) * 3 + s) * kFragLanes + lane] = t3[s];
+}
+
 // S fragments of phi turned into Z fragments (the same values; powers are the
-// records' matter): one wave per 32 positions x 32 features through LDS.
+// records' matter): one wave per 32 positions x 32 features through LDS.  The
+// waves past these form W's terms (a launch of its own took 5 us).
 __global__ __launch_bounds__(256) void k_turn(const uint4* __restrict__ s0, const uint4* __restrict__ s1,
                                               uint4* __restrict__ z0, uint4* __restrict__ z1, int KS, int ct_total,
-                                              long long waves, long long blocks) {
+                                              long long waves, long long blocks, WTerms wt) {
   __shared__ uint16_t t[4][2][32][36];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 31, lh = lane >> 5;
   const long long id = static_cast<long long>(blockIdx.x) * 4 + wave;
-  if (id >= waves) return;  // uniform per wave; waves share nothing
+  if (id >= waves) {  // uniform per wave; waves share nothing
+    wterms(wt, static_cast<int>(id - waves));
+    return;
+  }
   const int ct = static_cast<int>(id % ct_total);
   long long block = id / ct_total;
   const bool second = block >= blocks;
@@ -238,27 +267,6 @@ __global__ __launch_bounds__(256) void k_turn(const uint4* __restrict__ s0, cons
 }
 
 // ----------------------------------------------------- feature gradient --
-// W as Z fragments in three bf16 terms: [H][ks][d tile][3][64], lane: column
-// 32 dt + lr, features 16 ks + 8 (t / 4) + 4 lh + t % 4.
-__global__ __launch_bounds__(64) void k_wterms(const float* __restrict__ W, uint4* __restrict__ wf, int d, int m,
-                                               int KS, int dts) {
-  const int lane = threadIdx.x, lr = lane & 31, lh = lane >> 5;
-  int b = blockIdx.x;
-  const int dt = b % dts;
-  b /= dts;
-  const int ks = b % KS, h = b / KS, c = 32 * dt + lr;
-  float v8[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int l = 16 * ks + 8 * (t >> 2) + 4 * lh + (t & 3);
-    v8[t] = l < m && c < d ? W[(static_cast<size_t>(h) * m + l) * d + c] : 0.f;
-  }
-  uint4 t3[3];
-  split_bf16x8(v8, t3);
-#pragma unroll
-  for (int s = 0; s < 3; ++s) wf[(static_cast<size_t>(blockIdx.x) * 3 + s) * kFragLanes + lane] = t3[s];
-}
-
 // dx of 32 positions per wave: p = dphi o phi (times the position's power for
 // the keys), dx = p W - x sum(p) with six bf16 products per term, and the
 // projection of the row norm with NPRF.  dphi is consumed in its fragment
@@ -266,13 +274,14 @@ __global__ __launch_bounds__(64) void k_wterms(const float* __restrict__ W, uint
 template <typename TX, int DT>
 __global__ __launch_bounds__(256) void k_feature_grad(const TX* __restrict__ x, const uint4* __restrict__ wf,
                                                       const uint4* __restrict__ phi, const float* __restrict__ dphi,
-                                                      const int* __restrict__ pow, float* __restrict__ dx, int H, int n,
-                                                      int nblk, int d, int KS, int nprf, int BH) {
+                                                      const int* __restrict__ pow, const unsigned* __restrict__ flag,
+                                                      float* __restrict__ dx, int H, int n, int nblk, int d, int KS,
+                                                      int nprf, int BH) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 31, lh = lane >> 5;
   const int tiles = (nblk + 3) / 4;
   const int bh = blockIdx.x / tiles, blk = 4 * (blockIdx.x % tiles) + wave, h = bh % H;
-  if (blk >= nblk) return;  // uniform per wave; no barrier
+  if (blk >= nblk || flag[bh] != 0u) return;  // uniform per wave; no barrier
   const size_t block = static_cast<size_t>(bh) * nblk + blk;
   const uint4* __restrict__ fp = phi + block * KS * 2 * kFragLanes + lane;
   const float4* __restrict__ gp = reinterpret_cast<const float4*>(dphi) + (block * KS * kFragLanes + lane) * 2;
@@ -307,43 +316,9 @@ __global__ __launch_bounds__(256) void k_feature_grad(const TX* __restrict__ x, 
     }
   }
   sum += __shfl_xor(sum, 32);
-  // lane: row lr, columns 32 t + 8 g + 4 lh + j
   const int i = 32 * blk + lr;
   const TX* __restrict__ xr = x + (static_cast<size_t>(bh) * n + min(i, n - 1)) * d;
-  float xv[DT][16];
-  float sq = 0.f;
-#pragma unroll
-  for (int t = 0; t < DT; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int c = 32 * t + 8 * (e >> 2) + 4 * lh + (e & 3);
-      xv[t][e] = c < d ? to_f32(xr[c]) : 0.f;
-      sq = fmaf(xv[t][e], xv[t][e], sq);
-    }
-  sq += __shfl_xor(sq, 32);
-  const float scale = nprf ? (sq > 0.f ? rsqrtf(sq) : 0.f) : 1.f;
-  float dot = 0.f;
-#pragma unroll
-  for (int t = 0; t < DT; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      xv[t][e] *= scale;                      // the x phi was taken of
-      acc[t][e] = fmaf(-xv[t][e], sum, acc[t][e]);  // dL/dx
-      dot = fmaf(xv[t][e], acc[t][e], dot);
-    }
-  dot += __shfl_xor(dot, 32);
-  if (i >= n) return;
-  float* __restrict__ o = dx + (static_cast<size_t>(bh) * n + i) * d;
-#pragma unroll
-  for (int t = 0; t < DT; ++t)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float r[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        r[j] = nprf ? fmaf(-xv[t][4 * g + j], dot, acc[t][4 * g + j]) * scale : acc[t][4 * g + j];
-      store4(o, 32 * t + 8 * g + 4 * lh, d, r[0], r[1], r[2], r[3]);
-    }
+  store_gradient<TX, DT>(xr, acc, sum, dx + (static_cast<size_t>(bh) * n + min(i, n - 1)) * d, i < n, d, nprf);
 }
 
 // db_t = c_t x the diagonal sums over the row blocks of every batch entry, in
@@ -408,17 +383,17 @@ hipError_t go_dphi(const DirectArgs& a, int ct, hipStream_t st) {
 }
 
 template <typename TX>
-hipError_t feature_grad(const void* x, const uint4* wf, const uint4* phi, const float* dphi, const int* pow, float* dx,
-                        int BH, int H, int n, int nblk, int d, int KS, bool nprf, hipStream_t st) {
+hipError_t feature_grad(const void* x, const uint4* wf, const uint4* phi, const float* dphi, const int* pow,
+                        const unsigned* flag, float* dx, int BH, int H, int n, int nblk, int d, int KS, bool nprf, hipStream_t st) {
   const dim3 grid(static_cast<unsigned>(static_cast<long long>(BH) * ((nblk + 3) / 4))), block(256);
   const TX* xt = static_cast<const TX*>(x);
   const int np = nprf ? 1 : 0;
   if (d <= 32)
-    hipLaunchKernelGGL((k_feature_grad<TX, 1>), grid, block, 0, st, xt, wf, phi, dphi, pow, dx, H, n, nblk, d, KS, np, BH);
+    hipLaunchKernelGGL((k_feature_grad<TX, 1>), grid, block, 0, st, xt, wf, phi, dphi, pow, flag, dx, H, n, nblk, d, KS, np, BH);
   else if (d <= 64)
-    hipLaunchKernelGGL((k_feature_grad<TX, 2>), grid, block, 0, st, xt, wf, phi, dphi, pow, dx, H, n, nblk, d, KS, np, BH);
+    hipLaunchKernelGGL((k_feature_grad<TX, 2>), grid, block, 0, st, xt, wf, phi, dphi, pow, flag, dx, H, n, nblk, d, KS, np, BH);
   else
-    hipLaunchKernelGGL((k_feature_grad<TX, 4>), grid, block, 0, st, xt, wf, phi, dphi, pow, dx, H, n, nblk, d, KS, np, BH);
+    hipLaunchKernelGGL((k_feature_grad<TX, 4>), grid, block, 0, st, xt, wf, phi, dphi, pow, flag, dx, H, n, nblk, d, KS, np, BH);
   return hipGetLastError();
 }
 
@@ -478,6 +453,7 @@ hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, c
   auto I = [&](size_t o) { return reinterpret_cast<int*>(w + o); };
   int2* rrange = reinterpret_cast<int2*>(w + L.rrange);
   double* den = reinterpret_cast<double*>(w + L.den);
+  unsigned* flag = reinterpret_cast<unsigned*>(w + F.flag);
   const int nblk = F.nblk;
   if (hipError_t e = launch_direct_prep(F, w, q, k, v, bf16, b, W, BH, H, n, d, m, nprf, kFeatPrf, I(L.kpow),
                                         Fl(L.crev), rrange, st);
@@ -499,14 +475,21 @@ hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, c
     hipLaunchKernelGGL(k_bwd_ops<float>, ogrid, dim3(128), 0, st, o);
   const int ctt = L.passq * L.ctq, dts = d_tiles(d);
   const long long blocks = static_cast<long long>(BH) * nblk, waves = 2 * blocks * ctt;
-  hipLaunchKernelGGL(k_turn, dim3(static_cast<unsigned>((waves + 3) / 4)), dim3(256), 0, st, U(F.x), U(F.y), U(L.zq),
-                     U(L.zk), F.ks, ctt, waves, blocks);
-  hipLaunchKernelGGL(k_wterms, dim3(static_cast<unsigned>(H * F.ks * dts)), dim3(64), 0, st, W, U(L.wf), d, m, F.ks,
-                     dts);
+  const WTerms wt{W, U(L.wf), H, d, m, F.ks, dts};
+  const long long all = waves + static_cast<long long>(H) * F.ks * dts;
+  hipLaunchKernelGGL(k_turn, dim3(static_cast<unsigned>((all + 3) / 4)), dim3(256), 0, st, U(F.x), U(F.y), U(L.zq),
+                     U(L.zk), F.ks, ctt, waves, blocks, wt);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
 
+  // the heads whose phi two fp16 terms do not hold (the launches below skip them)
+  BwdExactArgs x{};
+  direct_exact_args(F, w, q, k, v, bf16, W, BH, H, n, d, m, nprf, kFeatPrf, x.f);
+  x.dz = dz, x.z = Fl(L.z), x.den = den, x.kpow = I(L.kpow), x.crev = Fl(L.crev), x.rrange = rrange;
+  x.dq = dq, x.dk = dk, x.dv = dv, x.pdc = db ? Fl(L.pdc) : nullptr;
+  if (hipError_t e = launch_bwd_exact(x, F.ks, bf16, st); e != hipSuccess) return e;
+
   DirectArgs a{};
-  a.BH = BH, a.H = H, a.n = n, a.nblk = nblk, a.d = d, a.nparts = 1;
+  a.BH = BH, a.H = H, a.n = n, a.nblk = nblk, a.d = d, a.nparts = 1, a.flag = flag;
   a.remap = direct_remap(BH);
   // dv_j = sum_i P_ij Gh_i (rows j, keys i: the reversed table), and the
   // diagonal sums of (v_j.Gh_i + gamma_i) (phi(k_j).phi(q_i))
@@ -526,8 +509,8 @@ hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, c
     return L.ks2 == 3 ? go_dphi<3>(x, L.ctq, st) : L.ks2 == 5 ? go_dphi<5>(x, L.ctq, st) : go_dphi<9>(x, L.ctq, st);
   };
   auto grad = [&](const void* x, size_t phi, const int* pow, float* dx) {
-    return bf16 ? feature_grad<uint16_t>(x, U(L.wf), U(phi), Fl(L.dphi), pow, dx, BH, H, n, nblk, d, F.ks, nprf, st)
-                : feature_grad<float>(x, U(L.wf), U(phi), Fl(L.dphi), pow, dx, BH, H, n, nblk, d, F.ks, nprf, st);
+    return bf16 ? feature_grad<uint16_t>(x, U(L.wf), U(phi), Fl(L.dphi), pow, flag, dx, BH, H, n, nblk, d, F.ks, nprf, st)
+                : feature_grad<float>(x, U(L.wf), U(phi), Fl(L.dphi), pow, flag, dx, BH, H, n, nblk, d, F.ks, nprf, st);
   };
   // dphi(q_i) = sum_j R_ij phi(k_j) (rows i, keys j), then dq
   a.X = U(L.gs), a.Y = U(L.vs), a.Z = U(L.zk), a.krec = Fl(L.recb), a.rpow = I(L.gpow);

@@ -537,6 +537,18 @@ hipError_t launch_direct_prep(const DirectLayout& L, char* w, const void* q, con
   return bf16 ? prep_go<uint16_t>(p, st) : prep_go<float>(p, st);
 }
 
+void direct_exact_args(const DirectLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
+                       const float* W, int BH, int H, int n, int d, int m, bool nprf, int kind, DirectArgs& a) {
+  a.q = q, a.k = k, a.v = v, a.W = W, a.m = m, a.kind = kind, a.nprf = nprf ? 1 : 0;
+  a.BH = BH, a.H = H, a.n = n, a.nblk = L.nblk, a.d = d;
+  a.ctab = reinterpret_cast<const float*>(w + L.ctab);
+  a.crange = reinterpret_cast<const int2*>(w + L.crange);
+  a.qpow = reinterpret_cast<const int*>(w + L.qpow);
+  a.qsum = reinterpret_cast<const float*>(w + L.qsum);
+  a.flag = reinterpret_cast<unsigned*>(w + L.flag);
+  a.inv_sqrt_m = inv_sqrt(m), a.log2_m = log2_scale(m);
+}
+
 hipError_t launch_direct(const DirectLayout& L, char* w, const void* q, const void* k, const void* v, bool bf16,
                          const float* W, float* z, double* den, int BH, int H, int n, int d, int m, bool nprf, int kind,
                          hipStream_t st) {
@@ -545,20 +557,14 @@ hipError_t launch_direct(const DirectLayout& L, char* w, const void* q, const vo
   a.Y = reinterpret_cast<const uint4*>(w + L.y);
   a.Z = reinterpret_cast<const uint4*>(w + L.z);
   a.vflag = reinterpret_cast<const unsigned*>(w + L.vflag);
-  a.ctab = reinterpret_cast<const float*>(w + L.ctab);
-  a.crange = reinterpret_cast<const int2*>(w + L.crange);
-  a.v = v, a.z = z, a.den = den, a.part = reinterpret_cast<double*>(w + L.part);
-  a.BH = BH, a.H = H, a.n = n, a.nblk = L.nblk, a.d = d, a.ct_total = L.ct_total;
+  a.z = z, a.den = den, a.part = reinterpret_cast<double*>(w + L.part);
+  a.ct_total = L.ct_total;
   a.krec = reinterpret_cast<const float*>(w + L.krec);
   const int rows = 32 * direct_waves(L.ks);
   a.tiles = (n + rows - 1) / rows;
   a.passes = L.passes, a.nparts = L.nparts;
   a.remap = direct_remap(BH);
-  a.q = q, a.k = k, a.W = W, a.m = m, a.kind = kind, a.nprf = nprf ? 1 : 0;
-  a.qpow = reinterpret_cast<const int*>(w + L.qpow);
-  a.qsum = reinterpret_cast<const float*>(w + L.qsum);
-  a.flag = reinterpret_cast<unsigned*>(w + L.flag);
-  a.inv_sqrt_m = inv_sqrt(m), a.log2_m = log2_scale(m);
+  direct_exact_args(L, w, q, k, v, bf16, W, BH, H, n, d, m, nprf, kind, a);
   if (L.ct_total >= 2)
     return bf16 ? direct_ks<1, 2>(L.ks, a, st) : direct_ks<2, 2>(L.ks, a, st);
   return bf16 ? direct_ks<1, 1>(L.ks, a, st) : direct_ks<2, 1>(L.ks, a, st);

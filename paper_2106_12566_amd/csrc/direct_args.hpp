@@ -59,7 +59,7 @@ struct DirectArgs {
   const float* W;
   const int* qpow;  // powers of phi(q) [BH][32 nblk]
   const float* qsum;  // and sums in their units
-  unsigned* flag;   // [BH + 1] heads with such a tile; any head
+  unsigned* flag;   // [BH + 1] heads with such a tile; any head (written, MODE 1, 2: these heads are skipped)
   int m, kind, nprf;
   float inv_sqrt_m;
   double log2_m;

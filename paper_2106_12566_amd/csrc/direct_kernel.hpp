@@ -131,6 +131,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
   const int tile = a.tiles - 1 - b % a.tiles;  // (under a causal mask the last rows see the most keys)
   b /= a.tiles;
   const int pass = b % a.passes, bh = b / a.passes, h = bh % a.H;
+  if (MODE > 0 && a.flag[a.BH] != 0u && a.flag[bh] != 0u) return;  // (bwd_exact.hip)
   const int n = a.n, row0 = tile * kRows, wrow0 = row0 + 32 * wave;
   const int2 br = head_range(a.crange + static_cast<size_t>(h) * ctab_chunks(n), ctab_chunks(n), lane);
   int b0, b1, wlo = 0, whi = 0;

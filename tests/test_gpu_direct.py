@@ -331,6 +331,21 @@ def test_direct_backward_denominators_far_apart(gpu_lib, d, n, m, bias):
     _bwd_check(gpu_lib, dd, "f32", G, f"denominators far apart d={d} n={n} m={m} {bias}", route="direct")
 
 
+@pytest.mark.parametrize("d,scale,kind,mask,n,m,dt", OPPOSED[:11] + [(128, 0.6, "aligned", "none", 600, 256, "f32")])
+def test_direct_backward_opposed(gpu_lib, d, scale, kind, mask, n, m, dt):
+    """The four gradients where the forward's rows are not held by two fp16 terms, on the default route and
+    with the gradients of other heads beside them.  Bound: that of test_direct_opposed, twice for
+    the features on both sides of a product."""
+    dd = _opposed(d, scale, kind, mask, n, m, dt)
+    # head 0: ordinary queries and keys; both heads of a second batch entry like head 1
+    for x in ("q", "k", "v"):
+        dd[x] = np.concatenate([dd[x], dd[x][:, ::-1]], axis=0)
+    other = synth.custom(1, 1, n, d, m, seed=7, qkv_dtype=dt)
+    dd["q"][0, 0], dd["k"][0, 0] = other["q"][0, 0], other["k"][0, 0]
+    G = np.random.default_rng([n, d]).standard_normal((2, 2, n, d)).astype(np.float32)
+    _bwd_check(gpu_lib, dd, dt, G, f"backward opposed d={d} scale={scale} {kind} {mask} n={n} m={m} {dt}", tol=4 * TOL)
+
+
 @pytest.mark.parametrize("n,d,m,dt,bias,nprf", BWD_CASES)
 def test_direct_backward(gpu_lib, n, d, m, dt, bias, nprf):
     """The gradients of the direct products against the fp64 chain rule.  Tolerance 2e-5 of a
