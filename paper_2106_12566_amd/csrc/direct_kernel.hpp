@@ -271,7 +271,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
         for (int j = 0; j < 4; ++j) p[4 * g + j] *= k4[j];
       }
     }
-    if constexpr (MODE == 2) {
+    if constexpr (MODE == 2) if (pass == 0) {  // uniform
       // the products (X2 Y2^T) o (X Y^T) of this block summed along its
       // diagonals: entry (key) of diagonal 32 + row - key, one diagonal per
       // lane to sum (slots that hold no entry stay zero; LDS float atomics
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
   if (wrow0 >= n) return;  // uniform per wave; no barrier follows
   if constexpr (MODE > 0) {
     const float rs = ldexpf(1.f, a.rpow[xblk * kBlk + lr]);
-    if (MODE == 2 && lh == 0 && whi > wlo)  // the diagonals below the last block's
+    if (MODE == 2 && pass == 0 && lh == 0 && whi > wlo)  // the diagonals below the last block's
       a.pdc[((hb + (wrow0 >> 5)) * (a.nblk + 1) + whi) * 32 + lr] = dcarry;
     if (a.ldz == 0) {
       float4* __restrict__ o = reinterpret_cast<float4*>(a.z) + (xblk * a.out_ks * kFragLanes + lane) * 2;
