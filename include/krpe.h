@@ -258,7 +258,9 @@ krpe_status_t krpe_attention_fwd_profiled(const void* q, const void* k, const vo
 
 /*
  * Bytes of workspace krpe_attention_bwd needs (0 if the sizes or flags are
- * invalid or unsupported).
+ * invalid or unsupported): for KRPE_ROUTE_FFT the transforms' alone, else a
+ * size that serves either route.  A call whose workspace holds the
+ * transforms' but not the direct products' runs the transforms.
  */
 size_t krpe_attention_bwd_workspace(int B, int H, int n, int d, int m, unsigned flags);
 

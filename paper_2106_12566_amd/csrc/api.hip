@@ -886,9 +886,11 @@ int krpe_attention_fwd_route(int B, int H, int n, int d, int m, unsigned flags) 
 size_t krpe_attention_bwd_workspace(int B, int H, int n, int d, int m, unsigned flags) {
   if (B < 0 || H < 0 || n < 1 || n > (1 << kMaxLog2N) || d < 1 || d > kMaxD || m < 1 || m > kMaxM) return 0;
   if (flags & ~kBwdFlags) return 0;
-  // serves either route, whatever the route bits and the hint of a call
+  // Without the FFT bit the size serves either route, whatever the other bits of
+  // a call; one that fits the transforms alone has them (krpe_attention_bwd).
   const size_t fft = bwd_layout(B, H, n, d, m).total;
-  const size_t direct = direct_bwd_ksteps(m) ? direct_bwd_layout(B, H, n, d, m).total : 0;
+  const size_t direct =
+      direct_bwd_ksteps(m) && !(flags & KRPE_ROUTE_FFT) ? direct_bwd_layout(B, H, n, d, m).total : 0;
   return fft > direct ? fft : direct;
 }
 
@@ -912,8 +914,12 @@ krpe_status_t krpe_attention_bwd(const void* q, const void* k, const void* v, in
     if (misaligned(p)) return fail(KRPE_ERR_ALIGN, "all pointers must be 16-byte aligned");
   const BwdLayout L = bwd_layout(B, H, n, d, m);
   const bool direct = use_fp32_direct(flags, static_cast<long long>(B) * H, n, m, d);
-  const bool products = direct_bwd_ksteps(m) != 0 && use_direct_products(flags, static_cast<long long>(B) * H, n, m, d);
-  const size_t need = products ? direct_bwd_layout(B, H, n, d, m).total : L.total;
+  bool products = direct_bwd_ksteps(m) != 0 && use_direct_products(flags, static_cast<long long>(B) * H, n, m, d);
+  size_t need = products ? direct_bwd_layout(B, H, n, d, m).total : L.total;
+  if (products && ws_bytes < need && ws_bytes >= L.total) {  // (a workspace sized for the transforms has them)
+    products = false;
+    need = L.total;
+  }
   if (!ws || ws_bytes < need)
     return fail(KRPE_ERR_WORKSPACE, "workspace needs " + std::to_string(need) + " bytes");
   const size_t qkv_bytes = bh * n * d * dtype_size(qkv_dtype), g_bytes = bh * n * d * sizeof(float);

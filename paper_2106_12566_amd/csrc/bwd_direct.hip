@@ -11,9 +11,9 @@
 // phi(q_i).phi(k_j) and takes the other factor as a second product.  phi(q_i)
 // stands without its power of two throughout: D_i is then in the same units
 // and the power cancels.  Launches: the forward's two, k_bwd_ops (operands from
-// dz, z, D and v), k_turn (phi as Z operands, W's terms), k_bwd_exact (the heads
-// that the forward pass flagged, which the others then skip: bwd_exact.hip), three
-// k_direct, k_db, two k_feature_grad.
+// dz, z, D and v), k_bwd_exact (the heads that the forward pass flagged, which the
+// others then skip: bwd_exact.hip), k_direct for dv, k_db, k_turn (phi as Z operands,
+// W's terms), k_direct and k_feature_grad for dq and for dk.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -429,8 +429,6 @@ DirectBwdLayout direct_bwd_layout(int B, int H, int n, int d, int m) {
   L.gs = take(bh * nb * L.ks2 * 2 * kFrag);
   L.vs = take(bh * nb * L.ks2 * 2 * kFrag);
   L.gz = take(bh * nb * L.f.ct_total * 4 * kFrag);
-  L.zq = take(bh * nb * L.passq * L.ctq * 4 * kFrag);
-  L.zk = take(bh * nb * L.passq * L.ctq * 4 * kFrag);
   L.reca = take(bh * nb * kRecWords * sizeof(float));
   L.recb = take(bh * nb * kRecWords * sizeof(float));
   L.recc = take(bh * nb * kRecWords * sizeof(float));
@@ -438,8 +436,14 @@ DirectBwdLayout direct_bwd_layout(int B, int H, int n, int d, int m) {
   L.gpow = take(bh * nb * kBlk * sizeof(int));
   L.vpow = take(bh * nb * kBlk * sizeof(int));
   L.wf = take(static_cast<size_t>(H) * ks * d_tiles(d) * 3 * kFrag);
-  L.dphi = take(bh * nb * ks * kFragLanes * 8 * sizeof(float));
-  L.pdc = take(bh * nb * (nb + 1) * 32 * sizeof(float));
+  // the diagonal sums are read before phi's Z operands and dphi are written: they
+  // take the same place (they grow with n^2, the others with n m)
+  const size_t phz = bh * nb * L.passq * L.ctq * 4 * kFrag, dphi = bh * nb * ks * kFragLanes * 8 * sizeof(float);
+  const size_t pdc = bh * nb * (nb + 1) * 32 * sizeof(float);
+  L.zq = L.pdc = off;
+  L.zk = L.zq + phz;
+  L.dphi = L.zk + phz;
+  take(pdc > 2 * phz + dphi ? pdc : 2 * phz + dphi);
   L.total = off;
   return L;
 }
@@ -473,12 +477,6 @@ hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, c
     hipLaunchKernelGGL(k_bwd_ops<uint16_t>, ogrid, dim3(128), 0, st, o);
   else
     hipLaunchKernelGGL(k_bwd_ops<float>, ogrid, dim3(128), 0, st, o);
-  const int ctt = L.passq * L.ctq, dts = d_tiles(d);
-  const long long blocks = static_cast<long long>(BH) * nblk, waves = 2 * blocks * ctt;
-  const WTerms wt{W, U(L.wf), H, d, m, F.ks, dts};
-  const long long all = waves + static_cast<long long>(H) * F.ks * dts;
-  hipLaunchKernelGGL(k_turn, dim3(static_cast<unsigned>((all + 3) / 4)), dim3(256), 0, st, U(F.x), U(F.y), U(L.zq),
-                     U(L.zk), F.ks, ctt, waves, blocks, wt);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
 
   // the heads whose phi two fp16 terms do not hold (the launches below skip them)
@@ -505,6 +503,14 @@ hipError_t launch_direct_bwd(const DirectBwdLayout& L, char* w, const void* q, c
                        st, Fl(L.pdc), Fl(F.ctab), rrange, db, BH / H, H, n, nblk);
     if (e = hipGetLastError(); e != hipSuccess) return e;
   }
+  // (not before: its operands take the place of the diagonal sums)
+  const int ctt = L.passq * L.ctq, dts = d_tiles(d);
+  const long long blocks = static_cast<long long>(BH) * nblk, waves = 2 * blocks * ctt;
+  const WTerms wt{W, U(L.wf), H, d, m, F.ks, dts};
+  const long long all = waves + static_cast<long long>(H) * F.ks * dts;
+  hipLaunchKernelGGL(k_turn, dim3(static_cast<unsigned>((all + 3) / 4)), dim3(256), 0, st, U(F.x), U(F.y), U(L.zq),
+                     U(L.zk), F.ks, ctt, waves, blocks, wt);
+  if (e = hipGetLastError(); e != hipSuccess) return e;
   auto dphi = [&](const DirectArgs& x) {
     return L.ks2 == 3 ? go_dphi<3>(x, L.ctq, st) : L.ks2 == 5 ? go_dphi<5>(x, L.ctq, st) : go_dphi<9>(x, L.ctq, st);
   };

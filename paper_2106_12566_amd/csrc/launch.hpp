@@ -139,7 +139,7 @@ struct DirectBwdLayout {
   size_t gpow, vpow; // int   [BH][32 nblk]
   size_t wf;        // W as Z fragments, three bf16 terms [H][ks][d tiles][3]
   size_t dphi;      // float  S fragments [BH][nblk][ks][64][8], one product at a time
-  size_t pdc;       // float  [BH][nblk][32 (nblk + 1)] diagonal sums per row block
+  size_t pdc;       // float  [BH][nblk][32 (nblk + 1)] diagonal sums per row block (in the place of zq, zk, dphi)
   size_t total;
 };
 int direct_bwd_ksteps(int m);  // 0: not covered

@@ -371,3 +371,23 @@ def test_direct_backward(gpu_lib, n, d, m, dt, bias, nprf):
     # without the bias gradient dv comes from another kernel: the same values up to rounding
     dv = gpu_lib.attention_bwd(*args, nprf=nprf, route="direct")[2].cpu().numpy()
     assert np.linalg.norm(dv - got[2].cpu().numpy()) <= 2e-6 * np.linalg.norm(ref[2])
+
+
+def test_backward_workspace_of_the_transforms(gpu_lib):
+    """A workspace sized for the transforms (KRPE_ROUTE_FFT's query) serves a call on any route, which then
+    has the transforms' bits; one byte less is refused."""
+    B, H, n, d, m = 1, 2, 4000, 8, 16  # (the direct products need more)
+    dd = synth.custom(B, H, n, d, m, seed=8)
+    G = np.random.default_rng(8).standard_normal((B, H, n, d)).astype(np.float32)
+    args = (*(to_gpu(dd[x]) for x in ("q", "k", "v", "b", "W")), to_gpu(G))
+    lib = gpu_lib.load()
+    small = int(lib.krpe_attention_bwd_workspace(B, H, n, d, m, gpu_lib.ROUTE_FFT))
+    assert small < int(lib.krpe_attention_bwd_workspace(B, H, n, d, m, 0))
+    want = gpu_lib.attention_bwd(*args, with_db=True, route="fft")
+    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    for route in ("fft", "auto"):
+        got = gpu_lib.attention_bwd(*args, workspace=ws, with_db=True, route=route)
+        for g, w in zip(got, want):
+            assert torch.norm(g - w) <= 2e-4 * torch.norm(w), route
+    with pytest.raises(gpu_lib.KrpeError):
+        gpu_lib.attention_bwd(*args, workspace=ws[:-1], with_db=True)
