@@ -84,7 +84,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) void k
       const int pw = (keys ? a.kpow : f.qpow)[hb * kBlk + r];
 #pragma unroll 1
       for (int t = 0; t < kTiles; ++t) {
-        exact_features(f, (keys ? k : q) + static_cast<size_t>(rc) * d, r < n, Wh, t, pw, ft);
+        exact_features(f, (keys ? k : q) + static_cast<size_t>(rc) * d, r < n, Wh, t, false, pw, ft);
         put(t);
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) void k
       {
         const int pw = (keys ? f.qpow : a.kpow)[hb * kBlk + key];
         for (int t = wave; t < kTiles; t += NW) {
-          exact_features(f, (keys ? q : k) + static_cast<size_t>(kc) * d, key < n, Wh, t, pw, ft);
+          exact_features(f, (keys ? q : k) + static_cast<size_t>(kc) * d, key < n, Wh, t, false, pw, ft);
           put(t);
         }
       }

@@ -24,15 +24,27 @@ __device__ __forceinline__ T at_bytes(const T* __restrict__ base, uint32_t offse
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + offset);
 }
 
+// sin x or cos x: x less its multiple of pi / 2 in fp64, then Taylor's series (up to
+// r^9 and r^10, |r| <= pi / 4: below 2^-25).  sincosf takes 50 registers more.
+__device__ __forceinline__ float sine(float x, bool cosine) {
+  const double k = rint(static_cast<double>(x) * 0.63661977236758134);
+  const float r = static_cast<float>(fma(k, -1.5707963267948966, static_cast<double>(x))), r2 = r * r;
+  const int quarter = static_cast<int>(static_cast<long long>(k) & 3) + (cosine ? 1 : 0);
+  const float s = fmaf(r * r2, fmaf(r2, fmaf(r2, fmaf(r2, 2.7557319e-6f, -1.9841270e-4f), 8.3333333e-3f), -0.16666667f), r);
+  const float c = fmaf(
+      r2, fmaf(r2, fmaf(r2, fmaf(r2, fmaf(r2, -2.7557319e-7f, 2.4801587e-5f), -1.3888889e-3f), 4.1666667e-2f), -0.5f), 1.f);
+  const float y = (quarter & 1) != 0 ? c : s;
+  return (quarter & 2) != 0 ? -y : y;
+}
+
 // Features of a lane's position (row xr of x, d values; `ok` false: zeros) over
 // 2^pw: tile ti of 32 projections (of 32 elements of x for elu + 1), register e
 // feature 32 ti + 8 (e / 4) + 4 lh + e % 4, the order of the accumulators, so
 // that registers 0 .. 7 and 8 .. 15 are k steps 2 ti and 2 ti + 1 of an S
-// operand.  (PRF and elu + 1: the trigonometric features of a position share
-// their size, and no row of theirs is evaluated again.)
+// operand.  Trigonometric map: sines, or cosines with `cosines`.
 template <typename TX>
 __device__ __forceinline__ void exact_features(const DirectArgs& a, const TX* __restrict__ xr, bool ok,
-                                               const float* __restrict__ Wh, int ti, int pw,
+                                               const float* __restrict__ Wh, int ti, bool cosines, int pw,
                                                float (&out)[16]) {
   const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5, d = a.d, f0 = 32 * ti;
   const bool vx = d % 8 == 0, vw = d % 4 == 0;
@@ -60,6 +72,17 @@ __device__ __forceinline__ void exact_features(const DirectArgs& a, const TX* __
   const double half_sq = a.nprf ? (nz ? 0.5 : 0.0) : 0.5 * sq;
   const double scale = a.nprf ? (nz ? 1.0 / sqrt(sq) : 0.0) : 1.0;
   const int rows = proj ? a.m : d;
+  if (a.kind == kFeatTrf) {
+    const float amp = ldexpf(static_cast<float>(exp(half_sq)) * a.inv_sqrt_m, -pw);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int f = f0 + 8 * (e >> 2) + 4 * lh + (e & 3);
+      const float y = sine(acc[e] * static_cast<float>(scale), cosines) * amp;
+      out[e] = ok && f < rows ? y : 0.f;
+      __builtin_amdgcn_sched_barrier(0);  // (few registers)
+    }
+    return;
+  }
   const float rs = static_cast<float>(proj ? scale * kLog2e : scale);
   const double e0d = a.log2_m - half_sq * kLog2e - pw;
   const float e0 = static_cast<float>(e0d), ef = rounding_factor(e0d, e0);
@@ -107,8 +130,9 @@ __device__ __forceinline__ bool rows_held(const DirectArgs& a, int bh, int wrow0
   const size_t hb = static_cast<size_t>(bh) * a.nblk;
   const uint4* __restrict__ xp = a.X + (hb + (wrow0 >> 5)) * KS * 2 * kFragLanes + lane;
   const float* __restrict__ ct = a.ctab + static_cast<size_t>(bh % a.H) * ctab_stride(n);
-  const double xs = a.qsum[(hb + (wrow0 >> 5)) * kBlk + lr];
-  {
+  const bool trf = a.kind == kFeatTrf;
+  const double xs = trf ? 0.0 : a.qsum[(hb + (wrow0 >> 5)) * kBlk + lr];
+  if (!trf) {
     float ys = 0.f;
     for (int blk = lo + lane; blk < hi; blk += 64) ys = fmaxf(ys, a.krec[(hb + blk) * kRecWords + kRecSum]);
 #pragma unroll
@@ -131,7 +155,7 @@ __device__ __forceinline__ bool rows_held(const DirectArgs& a, int bh, int wrow0
     }
     const float* __restrict__ rec = a.krec + (hb + blk) * kRecWords;
     const int kexp = __float_as_int(rec[kRecE]), vexp = __float_as_int(rec[kRecV]);
-    const double err = kTermErr * (xs + rec[kRecSum]);
+    const double err = trf ? 0.0 : kTermErr * (xs + rec[kRecSum]);
     const float doubt = static_cast<float>(kDoubt * err);
     double w = 0.0, most = 0.0;
 #pragma unroll
@@ -145,7 +169,7 @@ __device__ __forceinline__ bool rows_held(const DirectArgs& a, int bh, int wrow0
       // (a key of a power so far below its block's that its record is zero: at
       // most 2^38 2^-149)
       w += (r == 0.0 ? c : c > 0.0 ? 1.0 : 0.0) * kUnderflow;
-      most = fmax(most, se * r * c);
+      most = fmax(most, fabs(se * r * c));
     }
     dd = fma(w, exp2_int(kexp), dd);
     dn = fma(w + most * kSplitFloor, exp2_int(kexp + vexp + 15), dn);
@@ -153,7 +177,7 @@ __device__ __forceinline__ bool rows_held(const DirectArgs& a, int bh, int wrow0
   dd += __shfl_xor(dd, 32);
   dn += __shfl_xor(dn, 32);
   // (a sum that is not finite is not held)
-  return !__any(i < n && !(isfinite(dsum) && dd <= kRowTau * dsum && dn <= kRowTau * num));
+  return !__any(i < n && !(isfinite(dsum) && dd <= kRowTau * fabs(dsum) && dn <= kRowTau * num));
 }
 
 // Partial sums of part pi of a split row tile: [columns of the pass + 1][rows].
@@ -205,8 +229,9 @@ __device__ __forceinline__ void exact_rows(const DirectArgs& a, float4* __restri
                                            int bh, int pass, int tile, int pi, int w, int b0, int b1) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 31, lh = lane >> 5, n = a.n, d = a.d, h = bh % a.H;
-  constexpr int kTiles = KS / 2;
-  static_assert(KS % 2 == 0, "whole tiles of 32 features");
+  // (trigonometric map: the tiles of sines, then of cosines)
+  const bool trf = a.kind == kFeatTrf;
+  const int ksp = trf ? KS / 2 : KS, ftiles = (ksp + 1) / 2, all = trf ? 2 * ftiles : ftiles;
   const size_t hb = static_cast<size_t>(bh) * a.nblk, hn = static_cast<size_t>(bh) * n;
   const float* __restrict__ Wh = a.W + static_cast<size_t>(h) * a.m * d;
   const TV* __restrict__ q = static_cast<const TV*>(a.q) + hn * d;
@@ -224,11 +249,14 @@ __device__ __forceinline__ void exact_rows(const DirectArgs& a, float4* __restri
   float f[16];
   const int qp = a.qpow[(hb + (wrow0 >> 5)) * kBlk + lr];
   __syncthreads();  // xs and den are free
-  for (int ti = wave; ti < kTiles; ti += NW) {
-    exact_features(a, q + static_cast<size_t>(min(i, n - 1)) * d, i < n, Wh, ti, qp, f);
+  for (int ti = wave; ti < all; ti += NW) {
+    const bool cosines = ti >= ftiles;
+    const int tt = cosines ? ti - ftiles : ti;
+    exact_features(a, q + static_cast<size_t>(min(i, n - 1)) * d, i < n, Wh, tt, cosines, qp, f);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      float4* __restrict__ o = xs + ((2 * ti + j) * kFragLanes + lane) * 2;
+      if (2 * tt + j >= ksp) continue;  // uniform
+      float4* __restrict__ o = xs + ((2 * tt + j + (cosines ? ksp : 0)) * kFragLanes + lane) * 2;
       o[0] = make_float4(f[8 * j], f[8 * j + 1], f[8 * j + 2], f[8 * j + 3]);
       o[1] = make_float4(f[8 * j + 4], f[8 * j + 5], f[8 * j + 6], f[8 * j + 7]);
     }
@@ -247,11 +275,14 @@ __device__ __forceinline__ void exact_rows(const DirectArgs& a, float4* __restri
     const int key = 32 * blk + lr;
     floatx16 s = zero16();
 #pragma unroll 1
-    for (int ti = 0; ti < kTiles; ++ti) {
-      exact_features(a, k + static_cast<size_t>(min(key, n - 1)) * d, key < n, Wh, ti, pw, f);
+    for (int ti = 0; ti < all; ++ti) {
+      const bool cosines = ti >= ftiles;
+      const int tt = cosines ? ti - ftiles : ti;
+      exact_features(a, k + static_cast<size_t>(min(key, n - 1)) * d, key < n, Wh, tt, cosines, pw, f);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const float4* __restrict__ o = xs + ((2 * ti + j) * kFragLanes + lane) * 2;
+        if (2 * tt + j >= ksp) continue;  // uniform
+        const float4* __restrict__ o = xs + ((2 * tt + j + (cosines ? ksp : 0)) * kFragLanes + lane) * 2;
         const float4 u = o[0], y = o[1];
         const float x8[8] = {u.x, u.y, u.z, u.w, y.x, y.y, y.z, y.w};
 #pragma unroll
@@ -270,7 +301,7 @@ __device__ __forceinline__ void exact_rows(const DirectArgs& a, float4* __restri
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const float c = c_of(e);
-      if (s[e] > 0.f && c > 0.f)
+      if (s[e] != 0.f && c > 0.f)
         ex = max(ex, __builtin_amdgcn_frexp_expf(s[e]) + __builtin_amdgcn_frexp_expf(c));
       if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }

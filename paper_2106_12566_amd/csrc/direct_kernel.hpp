@@ -379,15 +379,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kDirect
     // a lane's sums cover this half-wave's keys, its columns those of its half
     dsum += __shfl_xor(dsum, 32);
     wsum += __shfl_xor(wsum, 32);
-    // The test with every S taken as doubtful and a few columns (trigonometric
-    // features are as large as their position's amplitude allows and S cancels:
-    // its size does not say that a term was not held) ...
+    // The test with every S taken as doubtful and a few columns ...
+    // (Trigonometric features are as large as their position's amplitude allows
+    // and S cancels: its size does not say that a term was not held, nor the
+    // denominator how large P's entries are.)
+    const bool trf = a.kind == kFeatTrf;
     const double beside = kUnderflow * exp2_int(kmost + 11);  // (2^11 blocks at most)
-    const double off = fma(kDoubtErr<KS>, wsum, beside);
-    const double offn = fma(kSplitFloor, fabs(dsum), off) * exp2_int(vmost + 15);
+    const double off = fma(trf ? 0.0 : kDoubtErr<KS>, wsum, beside), mass = trf ? wsum * (16.0 * KS * 0x1p30) : dsum;
+    const double offn = fma(kSplitFloor, mass, off) * exp2_int(vmost + 15);
     double num = fmax(fmax(fabs(zt[0][0]), fabs(zt[0][1])), fmax(fabs(zt[0][2]), fabs(zt[0][3])));
     bool again = false;
-    if (__builtin_expect(a.kind != kFeatTrf && __any(i < n && !(off <= kRowTau * dsum && offn <= kRowTau * num)), 0)) {
+    if (__builtin_expect(__any(i < n && !(off <= kRowTau * fabs(dsum) && offn <= kRowTau * num)), 0)) {
       // ... and in full, where that does not pass
 #pragma unroll
       for (int t = 0; t < CT; ++t)

@@ -87,14 +87,19 @@ def test_direct_powers_far_apart(gpu_lib):
     assert err <= 8 * TOL, err
 
 
-@pytest.mark.parametrize("n,d,m,offset", [(100, 64, 64, -85.5), (70, 20, 16, -86.0), (1300, 40, 128, -85.5)])
-def test_direct_weights_small(gpu_lib, n, d, m, offset):
+@pytest.mark.parametrize("n,d,m,offset,kw", [
+    (100, 64, 64, -85.5, {}), (70, 20, 16, -86.0, {}), (1300, 40, 128, -85.5, {}),
+    (100, 64, 40, -85.5, {"features": "trf", "nprf": True}), (150, 33, 8, -86.0, {"features": "trf", "nprf": True}),
+    (100, 48, 48, -85.5, {"features": "elu"}),
+])
+def test_direct_weights_small(gpu_lib, n, d, m, offset, kw):
     """A bias near the end of fp32's range (c = exp(b) of 2^-123): z does not depend on the scale of c."""
     dd = synth.custom(1, 2, n, d, m, seed=n, bias="normal", bias_sigma=0.2)
     dd["b"] = (dd["b"] + np.float32(offset)).astype(np.float32)
-    print(f"weights small n={n} d={d} m={m}", flush=True)
-    z = gpu_lib.attention_fwd(*(to_gpu(dd[x]) for x in ("q", "k", "v", "b", "W")), route="direct").cpu().numpy()
-    ref, _ = oracle.attention(dd["q"], dd["k"], dd["v"], dd["b"], dd["W"])
+    print(f"weights small n={n} d={d} m={m} {kw}", flush=True)
+    z = gpu_lib.attention_fwd(*(to_gpu(dd[x]) for x in ("q", "k", "v", "b", "W")), route="direct", **kw).cpu().numpy()
+    ref, _ = oracle.attention(dd["q"], dd["k"], dd["v"], dd["b"], dd["W"], nprf=kw.get("nprf", False),
+                              kind=kw.get("features", "prf"))
     err = rownorm_err(z, ref)
     print(f"  {err:.3e}", flush=True)
     # (c itself is an fp32 number of 2^-123 and up, normal: rounded to 2^-24)
@@ -130,8 +135,8 @@ def test_direct_keys_hidden(gpu_lib, mask):
     assert err <= 8 * TOL, err
 
 
-@pytest.mark.parametrize("dt", ["f32", "bf16"])
-def test_direct_weights_far_apart(gpu_lib, dt):
+@pytest.mark.parametrize("dt,features", [("f32", "prf"), ("bf16", "prf"), ("f32", "trf")])
+def test_direct_weights_far_apart(gpu_lib, dt, features):
     """Rows in which a small weight meets a large value: entries of P 2^24 to 2^40 below the row's largest
     in the block, with values as much larger, count as much in z as the others.  Positive weights and
     values: element by element."""
@@ -146,9 +151,13 @@ def test_direct_weights_far_apart(gpu_lib, dt):
     if dt == "bf16":
         v = torch.from_numpy(v).to(torch.bfloat16).float().numpy()
     dd["v"] = v
-    ref, _ = oracle.attention(dd["q"], dd["k"], v, dd["b"], dd["W"])
+    # (TRF of unit rows that are nearly alike: S = phi(q).phi(k) is near its largest, m of the amplitudes' product)
+    nprf = features == "trf"
+    if nprf:
+        dd["q"], dd["k"] = (np.float32(1.0) + np.float32(0.1) * dd[x] for x in ("q", "k"))
+    ref, _ = oracle.attention(dd["q"], dd["k"], v, dd["b"], dd["W"], nprf=nprf, kind=features)
     z = gpu_lib.attention_fwd(to_gpu(dd["q"], dt), to_gpu(dd["k"], dt), to_gpu(v, dt), to_gpu(dd["b"]), to_gpu(dd["W"]),
-                              route="direct").cpu().numpy()
+                              route="direct", nprf=nprf, features=features).cpu().numpy()
     err = float(np.max(np.abs(z - ref) / np.abs(ref)))
     print(f"weights far apart {dt}: {err:.3e}", flush=True)
     assert err <= TOL, err
