@@ -67,12 +67,15 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
   const int h = bh % a.H, n = a.n, d = a.d;
   const TX* __restrict__ x = static_cast<const TX*>(src == 0 ? a.q : a.k) + static_cast<size_t>(bh) * n * d;
   const int p0 = pt * 128, rows = min(128, n - p0);
+  __shared__ int wodd;
+  if (tid == 0) wodd = 0;
   stage_x<TX, DK>(x, p0, rows, d, smem);
   __syncthreads();
   // this lane's position: its operand and squared norm
   uint4 xf[DK][NSX];
   const float* __restrict__ row = smem + (32 * wave + lr) * XS;
   const double sqd = x_operand<DK, NSX>(row, lh, xf);
+  const bool xodd = __any(unsplit(sqd));  // uniform
   // phi of x / ||x|| when normalising (Algorithm 1, first step): the
   // projections scale by 1 / ||x|| and ||x||^2 / 2 becomes 1/2 (a zero row
   // stays zero).
@@ -94,8 +97,16 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
   uint4* __restrict__ wf = reinterpret_cast<uint4*>(smem);
   auto stage_tiles = [&](int t0) {
     __syncthreads();  // x rows / the previous features consumed
-    stage_w<DK>(Wh, 32 * t0, min(GT, ftiles - t0), a.m, d, wf);
+    stage_w<DK>(Wh, 32 * t0, min(GT, ftiles - t0), a.m, d, wf, &wodd);
     __syncthreads();
+  };
+  auto project_tile = [&](int ti, int t0, floatx16& acc, floatx16& lo) {
+    project<DK, NSX, false>(wf + (ti - t0) * DK * 3 * kFragLanes, xf, acc, lo);
+    if (__builtin_expect(xodd || wodd != 0, 0)) {
+      project_plain(Wh + static_cast<size_t>(min(32 * ti + lr, a.m - 1)) * d,
+                    x + static_cast<size_t>(min(p0 + 32 * wave + lr, n - 1)) * d, d, acc);
+      lo = zero16();
+    }
   };
   auto emit = [&](int ks, const float (&v8)[8]) {
     uint4 hh, ll;
@@ -116,7 +127,7 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
       stage_tiles(t0);
       for (int tt = 0; tt < min(GT, ftiles - t0) && store; ++tt) {
         floatx16 acc, lo;
-        project<DK, NSX, false>(wf + tt * DK * 3 * kFragLanes, xf, acc, lo);
+        project_tile(t0 + tt, t0, acc, lo);
         float s16[16], c16[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
@@ -158,7 +169,7 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
         if (ti >= ftiles) return;  // uniform
         if constexpr (ti == t0) stage_tiles(t0);
         floatx16 acc, lo;
-        project<DK, NSX, false>(wf + (ti - t0) * DK * 3 * kFragLanes, xf, acc, lo);
+        project_tile(ti, t0, acc, lo);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           val[ti][e] = pos_ok ? phi_prf(acc[e], lo[e], rs, e0, ef) : 0.f;

@@ -92,21 +92,50 @@ __device__ __forceinline__ double x_operand(const float* __restrict__ row, int l
   }
   return sq + __shfl_xor(sq, 32);
 }
+// Elements that bf16 terms do not split (infinite, NaN, or rounded to infinity).
+__device__ __forceinline__ bool unsplit(double sq) { return !(sq < 0x1p254); }
 
 // Rows f0 .. of W [m][d] (`tiles` tiles of 32, zeros past m) as operands:
-// wf[tile][ks][term][64].
+// wf[tile][ks][term][64].  `odd` (LDS) is set where an element is one that terms
+// do not split.
 template <int DK>
 __device__ __forceinline__ void stage_w(const float* __restrict__ W, int f0, int tiles, int m, int d,
-                                        uint4* __restrict__ wf) {
+                                        uint4* __restrict__ wf, int* __restrict__ odd) {
   for (int e = threadIdx.x; e < tiles * 32 * 2 * DK; e += 256) {
     const int fl = e / (2 * DK), c = e % (2 * DK), f = f0 + fl;
     float v8[8];
     load8(W + static_cast<size_t>(min(f, m - 1)) * d + 8 * c, f < m ? d - 8 * c : 0, d % 4 == 0, v8);
     uint4 t3[3];
     split_bf16x8(v8, t3);
+    float most = 0.f;
+    bool nan = false;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      most = fmaxf(most, fabsf(v8[t]));
+      nan |= v8[t] != v8[t];
+    }
+    if (nan || most >= 0x1p127f) *odd = 1;
     uint4* __restrict__ o = wf + ((fl >> 5) * DK + (c >> 1)) * 3 * kFragLanes + (c & 1) * 32 + (fl & 31);
 #pragma unroll
     for (int s = 0; s < 3; ++s) o[s * kFragLanes] = t3[s];
+  }
+}
+
+// The same projections on the fp32 matrix cores from memory, where an element is one
+// that terms do not split (inf - inf would make every feature NaN; W x = -inf has
+// phi = 0).  The lane's row of the product's A operand and of its B operand, as in
+// project's layouts; rare.
+template <typename TA, typename TB>
+__device__ __forceinline__ void project_plain(const TA* __restrict__ ra, const TB* __restrict__ rb, int d, floatx16& acc) {
+  const int lh = (threadIdx.x & 63) >> 5;
+  acc = zero16();
+#pragma unroll 1
+  for (int c = 0; c < d; c += 16) {
+    float av[8], bv[8];
+    load8(ra + c + 8 * lh, d - c - 8 * lh, false, av);
+    load8(rb + c + 8 * lh, d - c - 8 * lh, false, bv);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[t], bv[t], acc, 0, 0, 0);
   }
 }
 

@@ -30,24 +30,30 @@ struct PhiArgs {
 // exponentials about 20 us each of theirs and the VALU.  (At three and four
 // waves per SIMD: 116 and 107 us.)
 template <typename TX, int DK, bool TRF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_phi(PhiArgs a) {
+constexpr int kPhiWaves = !TRF && (DK <= 2 || (DK <= 4 && sizeof(TX) == 2)) ? 3 : 2;
+template <typename TX, int DK, bool TRF>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPhiWaves<TX, DK, TRF>))) void k_phi(PhiArgs a) {
   constexpr int NSX = sizeof(TX) == 2 ? 1 : 3;
   constexpr int GT = DK <= 4 ? 4 : 2;  // tiles of W staged at a time
   constexpr int kX = 128 * x_stride(DK), kW = GT * DK * 3 * 256;
   __shared__ __align__(16) float smem[kX > kW ? kX : kW];
   // the positions' factors (PRF: phi_prf's; TRF: row scale, amplitude)
   __shared__ __align__(16) float f0[128], f1[128], f2[128];
+  __shared__ int wodd;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lh = lane >> 5, n = a.n, d = a.d, m = a.m;
   const int pt = blockIdx.x % a.tiles, bh = blockIdx.x / a.tiles, h = bh % a.H;
   const int p0 = pt * 128;
-  stage_x<TX, DK>(static_cast<const TX*>(a.x) + static_cast<size_t>(bh) * n * d, p0, min(128, n - p0), d, smem);
+  const TX* __restrict__ x = static_cast<const TX*>(a.x) + static_cast<size_t>(bh) * n * d;
+  if (tid == 0) wodd = 0;
+  stage_x<TX, DK>(x, p0, min(128, n - p0), d, smem);
   __syncthreads();
   uint4 xf[DK][NSX];
   const double sqd = x_operand<DK, NSX>(smem + (32 * wave + lr) * x_stride(DK), lh, xf);
   // phi of x / ||x|| when normalising (Algorithm 1, first step): the
   // projections scale by 1 / ||x|| and ||x||^2 / 2 becomes 1/2 (a zero row
   // stays zero)
+  const bool xodd = __any(unsplit(sqd));  // uniform
   const bool nz = sqd > 0.0;
   const double half_sq = a.nprf ? (nz ? 0.5 : 0.0) : 0.5 * sqd;
   const double scale = a.nprf ? (nz ? 1.0 / sqrt(sqd) : 0.0) : 1.0;
@@ -73,13 +79,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   for (int t0 = 0; t0 < ftiles; t0 += GT) {
     __syncthreads();  // x rows / the previous features consumed, the factors written
     const int gt = min(GT, ftiles - t0);
-    stage_w<DK>(Wh, 32 * t0, gt, m, d, wf);
+    stage_w<DK>(Wh, 32 * t0, gt, m, d, wf, &wodd);
     __syncthreads();
     if (i0 >= n) continue;
     for (int tt = 0; tt < gt; ++tt) {
       floatx16 acc, lo;
       project<DK, NSX, true>(wf + tt * DK * 3 * kFragLanes, xf, acc, lo);
       const int l = 32 * (t0 + tt) + lr;
+      if (__builtin_expect(xodd || wodd != 0, 0)) {
+        project_plain(x + static_cast<size_t>(min(i0 + lr, n - 1)) * d, Wh + static_cast<size_t>(min(l, m - 1)) * d, d, acc);
+        lo = zero16();
+      }
       const bool full = i0 + 32 <= n && 32 * (t0 + tt) + 32 <= m;  // uniform
       // register e: position i0 + 8 (e / 4) + 4 lh + e % 4
 #pragma unroll

@@ -219,6 +219,45 @@ def test_direct_values_not_finite(gpu_lib, dt, n, d, parts):
     assert np.max(np.where(want, 0.0, np.abs(np.where(want, 0.0, z) - clean)) / scale) <= TOL
 
 
+@pytest.mark.parametrize("dt,d,m,n", [("f32", 64, 130, 200), ("bf16", 33, 20, 40), ("f32", 128, 64, 129)])
+def test_features_not_finite(gpu_lib, dt, d, m, n):
+    """An infinite or enormous element of x, or of W, reaches the features it is in: phi = 0 where
+    W x - |x|^2 / 2 is -inf, NaN only where the formula's terms are of both signs."""
+    dd = synth.custom(1, 1, n, d, m, seed=d, qkv_dtype=dt)
+    x, W = dd["q"].copy(), dd["W"].copy()
+    W[W == 0] = 0.1
+    clean = gpu_lib.feature_map(to_gpu(x, dt), to_gpu(W)).cpu().numpy()
+    big = float(np.float32(3.3895e38))  # (bf16's largest)
+    for j, v in ((3, np.inf), (n - 1, -np.inf), (35, big), (7, np.nan)):
+        x[0, 0, j, d - 2] = v
+    if dt == "bf16":
+        x = torch.from_numpy(x).to(torch.bfloat16).float().numpy()
+    xt = torch.from_numpy(x).to(torch.bfloat16).cuda() if dt == "bf16" else to_gpu(x)
+    phi = gpu_lib.feature_map(xt, to_gpu(W)).cpu().numpy()
+    up = W[0, :, d - 2] > 0
+    assert np.all(np.isnan(phi[0, 0, 3, up])) and np.all(phi[0, 0, 3, ~up] == 0)
+    assert np.all(np.isnan(phi[0, 0, n - 1, ~up])) and np.all(phi[0, 0, n - 1, up] == 0)
+    assert np.all(np.isnan(phi[0, 0, 7]))
+    assert np.all((phi[0, 0, 35] == 0) | ((np.abs(W[0, :, d - 2]) > 1) & np.isnan(phi[0, 0, 35])))
+    rest = np.setdiff1d(np.arange(n), [3, 7, 35, n - 1])
+    np.testing.assert_allclose(phi[:, :, rest], clean[:, :, rest], rtol=TOL)
+    W[0, 5, 1] = -np.inf
+    got = gpu_lib.feature_map(to_gpu(dd["q"], dt), to_gpu(W)).cpu().numpy()
+    want = np.where(dd["q"][..., 1:2] > 0, 0.0, np.where(dd["q"][..., 1:2] < 0, np.inf, np.nan))[..., 0]
+    np.testing.assert_array_equal(got[..., 5], want.astype(np.float32))
+    others = [l for l in range(m) if l != 5]
+    np.testing.assert_allclose(got[..., others], clean[..., others], rtol=TOL)
+    # a key whose every feature is zero has no weight
+    W = -np.abs(dd["W"]).astype(np.float32)
+    W[W == 0] = -0.1
+    k, kz = dd["k"].copy(), dd["k"].copy()
+    k[0, 0, 9, 0], kz[0, 0, 9, 0] = np.inf, 1e4
+    kt = torch.from_numpy(k).to(torch.bfloat16).cuda() if dt == "bf16" else to_gpu(k)
+    z = gpu_lib.attention_fwd(to_gpu(dd["q"], dt), kt, to_gpu(dd["v"], dt), to_gpu(dd["b"]), to_gpu(W), route="direct")
+    ref, _ = oracle.attention(dd["q"], kz, dd["v"], dd["b"], W)
+    assert rownorm_err(z.cpu().numpy(), ref) <= TOL
+
+
 def _opposed(d, scale, kind, mask, n=200, m=128, dt="f32"):
     """Queries and keys for which every product phi_l(q) phi_l(k) a row sums pairs a large feature with
     one far below its position's largest: k = -q, a common direction with `kind`'s share of noise, or
