@@ -379,7 +379,7 @@ hipError_t go_dv(const DirectArgs& a, int ks2, bool db, hipStream_t st) {
 // dphi: rows and keys of d + 1 contracted columns, columns phi
 template <int KS2>
 hipError_t go_dphi(const DirectArgs& a, int ct, hipStream_t st) {
-  return ct == 1 ? go<1, KS2, 0, 1>(a, st) : ct == 2 ? go<1, KS2, 0, 2>(a, st) : go<1, KS2, 0, 4>(a, st);
+  return ct == 2 ? go<1, KS2, 0, 2>(a, st) : go<1, KS2, 0, 4>(a, st);
 }
 
 template <typename TX>
@@ -411,8 +411,8 @@ DirectBwdLayout direct_bwd_layout(int B, int H, int n, int d, int m) {
   const size_t bh = static_cast<size_t>(B) * H, nb = static_cast<size_t>(L.f.nblk);
   const int want = (d + 1 + 15) / 16;
   L.ks2 = want <= 3 ? 3 : want <= 5 ? 5 : 9;
-  const int ct = (ks + 1) / 2;
-  L.ctq = ct == 1 ? 1 : ct == 2 ? 2 : 4;
+  const int ct = ks / 2;  // 2, 4 or 8
+  L.ctq = ct == 2 ? 2 : 4;
   L.passq = (ct + L.ctq - 1) / L.ctq;
   size_t off = L.f.total;
   auto take = [&off](size_t bytes) {
