@@ -166,11 +166,11 @@ __device__ __forceinline__ void stage_lds(__amdgpu_buffer_rsrc_t r, uint32_t lds
   if constexpr (BYTES == 16)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff),
                  "s"(r), "s"(soff)
-                 : "memory", "m0");
+                 : "memory");
   else
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(r),
                  "s"(soff)
-                 : "memory", "m0");
+                 : "memory");
 }
 __device__ __forceinline__ void stage_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
