@@ -76,6 +76,7 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
   const float* __restrict__ row = smem + (32 * wave + lr) * XS;
   const double sqd = x_operand<DK, NSX>(row, lh, xf);
   const bool xodd = __any(unsplit(sqd));  // uniform
+  bool plain = xodd;
   // phi of x / ||x|| when normalising (Algorithm 1, first step): the
   // projections scale by 1 / ||x|| and ||x||^2 / 2 becomes 1/2 (a zero row
   // stays zero).
@@ -99,10 +100,11 @@ __device__ __forceinline__ void prep_phi(const PrepArgs& a, int bid, float* __re
     __syncthreads();  // x rows / the previous features consumed
     stage_w<DK>(Wh, 32 * t0, min(GT, ftiles - t0), a.m, d, wf, &wodd);
     __syncthreads();
+    plain = xodd || __builtin_amdgcn_readfirstlane(wodd) != 0;
   };
   auto project_tile = [&](int ti, int t0, floatx16& acc, floatx16& lo) {
     project<DK, NSX, false>(wf + (ti - t0) * DK * 3 * kFragLanes, xf, acc, lo);
-    if (__builtin_expect(xodd || wodd != 0, 0)) {
+    if (__builtin_expect(plain, 0)) {
       project_plain(Wh + static_cast<size_t>(min(32 * ti + lr, a.m - 1)) * d,
                     x + static_cast<size_t>(min(p0 + 32 * wave + lr, n - 1)) * d, d, acc);
       lo = zero16();

@@ -108,13 +108,9 @@ __device__ __forceinline__ void stage_w(const float* __restrict__ W, int f0, int
     uint4 t3[3];
     split_bf16x8(v8, t3);
     float most = 0.f;
-    bool nan = false;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      most = fmaxf(most, fabsf(v8[t]));
-      nan |= v8[t] != v8[t];
-    }
-    if (nan || most >= 0x1p127f) *odd = 1;
+    for (int t = 0; t < 8; ++t) most = fmaxf(most, fabsf(v8[t]));
+    if (most >= 0x1p127f) *odd = 1;  // (a NaN is in its own row's products alone)
     uint4* __restrict__ o = wf + ((fl >> 5) * DK + (c >> 1)) * 3 * kFragLanes + (c & 1) * 32 + (fl & 31);
 #pragma unroll
     for (int s = 0; s < 3; ++s) o[s * kFragLanes] = t3[s];

@@ -81,12 +81,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPhiWaves<T
     const int gt = min(GT, ftiles - t0);
     stage_w<DK>(Wh, 32 * t0, gt, m, d, wf, &wodd);
     __syncthreads();
+    const bool plain = xodd || __builtin_amdgcn_readfirstlane(wodd) != 0;
     if (i0 >= n) continue;
     for (int tt = 0; tt < gt; ++tt) {
       floatx16 acc, lo;
       project<DK, NSX, true>(wf + tt * DK * 3 * kFragLanes, xf, acc, lo);
       const int l = 32 * (t0 + tt) + lr;
-      if (__builtin_expect(xodd || wodd != 0, 0)) {
+      if (__builtin_expect(plain, 0)) {
         project_plain(x + static_cast<size_t>(min(i0 + lr, n - 1)) * d, Wh + static_cast<size_t>(min(l, m - 1)) * d, d, acc);
         lo = zero16();
       }
