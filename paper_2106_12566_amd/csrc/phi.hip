@@ -24,7 +24,7 @@ struct PhiArgs {
 // 128 positions of one (batch, head) and every feature.  A 32 x 32 tile leaves
 // the matrix cores with lanes along the features, so that a row of phi is
 // stored 128 bytes at a time; the positions' factors lie along the registers
-// and come from LDS.  At 96 heads, n = 4096, m = 128, d = 64: 154 -> 102 us (0.3
+// and come from LDS.  At 96 heads, n = 4096, m = 128, d = 64: 154 -> 89 us (0.3
 // GB in and out, 63 us at a plain copy's rate); the fp32 matrix products it
 // replaces took 82 us of the matrix cores by themselves, the bf16 ones and the
 // exponentials about 20 us each of theirs and the VALU.  (At three and four

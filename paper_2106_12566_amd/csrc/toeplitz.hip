@@ -47,7 +47,7 @@ __global__ void k_thread_twiddles(float2* __restrict__ tw, float2* __restrict__ 
 // written once.  Through the forward's convolution kernel (one feature equal
 // to 1) the channels were read for their maxima, read and written packed, read
 // once per class, and the classes' partial sums written, read and added.  At
-// 96 heads, 64 channels, n = 4096: 345 -> 139 us per call, 115 this kernel.
+// 96 heads, 64 channels, n = 4096: 345 -> 131 us per call, 115 this kernel.
 // The channels once in and out are 0.2 GB, 42 us at a plain copy's rate, the
 // transforms about 50 us of the VALU; the rest is the latency of each unit's
 // serial chain at two work-groups per CU.  Measured and not kept: twiddles and
