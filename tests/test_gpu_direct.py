@@ -1,7 +1,9 @@
 """GPU tests of the direct route's kernels (csrc/direct.hip) at the sizes where they can go wrong:
 edges of the 32-key blocks and of the row tiles, feature counts around the 16-feature steps and the
 compiled step counts, column tiles and passes of v, row tiles split over work-groups, powers of two
-that differ by far more than fp16 holds, and values that are not finite.
+that differ by far more than fp16 holds, what two fp16 terms do not hold at all (opposed queries and
+keys, small weights beside large values, values and denominators far apart), and elements that are
+not finite; and of the direct backward likewise.
 
 Tolerance: 2e-5 of a row's largest entry.  z is a ratio of sums of positive weights (PRF, elu + 1):
 its error is at most twice the relative error of a weight phi(q).phi(k) c plus that of a value.  A
@@ -65,8 +67,9 @@ def test_direct_feature_maps(gpu_lib, features, n, d, m):
 
 
 def test_direct_powers_far_apart(gpu_lib):
-    """Keys, queries and values whose sizes differ by far more than fp16 holds inside one 32-key
-    block (phi(k) from 2^-103 to 2^7): each position's features carry a power of their own, so the
+    """Keys and queries whose sizes differ by far more than fp16 holds inside one 32-key block (phi(k)
+    from 2^-103 to 2^7), and the values of one block from the others' (within a block:
+    test_direct_values_far_apart): each position's features carry a power of their own, so the
     first rows of a causal mask, which see only small ones, keep their accuracy (row 0 is v_0
     whatever its weight).  The exponents of phi reach 2^7 here, where their rounding is eight times
     that of the other tests."""
